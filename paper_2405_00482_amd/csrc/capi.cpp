@@ -123,9 +123,6 @@ LimbMap qp_map(const pvfl_ctx* c, int lv, bool with_p) {
     for (int k = 0; k < c->alpha; ++k) m.idx[m.n++] = c->n_q + k;
   return m;
 }
-LimbMap key_limb_map(const pvfl_ctx* c, int lv) {
-  return qp_map(c, lv, true);  // key limbs follow the context's prime order
-}
 LaunchCtx launch_ctx(const pvfl_ctx* c, void* stream) { return LaunchCtx{(hipStream_t)stream, c->tabs, c->logN}; }
 }  // namespace pvfl
 
@@ -528,17 +525,80 @@ pvfl_status ctx_scratch(pvfl_ctx* c, size_t bytes, double** out) {
   return PVFL_OK;
 }
 
-// key switch of the hoisted digits of c1 (or of an already-rotated c1 with
-// rot = 0), then ModDown; writes (v0, v1) to v [2][lv+1][N].
-pvfl_status keyswitch_digits(pvfl_ctx* c, const pvfl_rotkeys* keys, int lv, const double* digits, int rot_digits,
-                             int key_rot, double* u, double* ydown, double* v, void* stream) {
-  const int slot = keys->slot_of_rot[key_rot];
-  if (slot < 0) return fail(PVFL_E_NOKEY, "missing rotation key for rotation " + std::to_string(key_rot));
+// Scratch of the calls that rotate many ciphertexts side by side (the
+// transposed conversion, ROW): `per` doubles for each of *n items, *n as many
+// of `want` as kRotScratchCap holds.  The block is the context's, grows in
+// powers of two up to the cap and is given back with the context; a smaller
+// block that it replaces is kept until then, since a captured graph may still
+// name it (together at most twice the cap).  *n = 0: run the items one at a
+// time on the single-operation scratch -- only one item is wanted, the memory
+// is not to be had, or the stream is being captured and nothing may be
+// allocated.
+static constexpr size_t kRotScratchCap = (size_t(256) << 20) / sizeof(double);
+pvfl_status ctx_rot_scratch(pvfl_ctx* c, size_t per, int want, void* stream, double** out, int* n) {
+  *out = nullptr;
+  *n = 0;
+  const size_t fit = kRotScratchCap / per;
+  size_t target = std::min<size_t>(fit, (size_t)std::max(want, 0));
+  if (target < 2) return PVFL_OK;
+  if (c->rot_scratch_n < target * per) {
+    hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
+    const bool free_stream = hipStreamIsCapturing((hipStream_t)stream, &cs) == hipSuccess && cs == hipStreamCaptureStatusNone;
+    if (!free_stream) (void)hipGetLastError();
+    void* p = nullptr;
+    size_t size = (size_t(16) << 20) / sizeof(double);
+    while (size < target * per) size *= 2;
+    if (free_stream && hipMalloc(&p, size * sizeof(double)) == hipSuccess) {
+      c->dev_allocs.push_back(p);
+      c->rot_scratch = (double*)p;
+      c->rot_scratch_n = size;
+    } else {
+      if (free_stream) (void)hipGetLastError();
+      target = c->rot_scratch_n / per;
+      if (target < 2) return PVFL_OK;
+    }
+  }
+  *out = c->rot_scratch;
+  *n = (int)target;
+  return PVFL_OK;
+}
+
+size_t rot_scratch_doubles(const pvfl_ctx* c, int lv) {
   const KsLevel& kl = c->ks_host[lv];
+  return ((size_t)(lv + 1) + (size_t)kl.beta * kl.K + 2 * (size_t)c->alpha) * c->N;
+}
+
+pvfl_status run_rotations(pvfl_ctx* c, const pvfl_rotkeys* keys, int lv, const RotJob* jobs, int n, bool pre, bool add,
+                          double* scratch, int at_once, const double* shared_digits, void* stream) {
+  const KsLevel& kl = c->ks_host[lv];
+  const size_t N = c->N, DG = (size_t)kl.beta * kl.K * N;
+  for (int k = 0; k < n; ++k)
+    if (keys->slot_of_rot[jobs[k].rot] < 0)
+      return fail(PVFL_E_NOKEY, "missing rotation key for rotation " + std::to_string(jobs[k].rot));
+  at_once = std::max(1, std::min(at_once, kRotsPerLaunch));
+  RotRun r{};
+  r.kl_dev = c->ks_dev + lv;
+  r.lv = lv;
+  r.alpha = c->alpha;
+  r.n_tasks = kl.n_tasks;
+  r.key_limbs = keys->key_limbs;
+  r.pre = pre ? 1 : 0;
+  r.add = add ? 1 : 0;
+  r.shared_digits = shared_digits != nullptr;
+  r.ydown = scratch;
+  r.digits = shared_digits ? const_cast<double*>(shared_digits) : scratch + (size_t)at_once * 2 * c->alpha * N;
+  r.dig_stride = shared_digits ? 0 : DG;
+  r.yup = shared_digits ? nullptr : r.digits + (size_t)at_once * DG;
   LaunchCtx L = launch_ctx(c, stream);
-  HIP_TRY(launch_key_inner(L, digits, kl.beta, kl.K, c->N, rot_digits, keys->keys + (size_t)slot * keys->key_stride,
-                           keys->key_limbs, qp_map(c, lv, true), key_limb_map(c, lv), u));
-  HIP_TRY(launch_moddown(L, u, 2, lv, c->alpha, c->ks_dev + lv, ydown, v));
+  for (int k0 = 0; k0 < n; k0 += at_once) {
+    RotBatch b{};
+    b.n = std::min(at_once, n - k0);
+    for (int u = 0; u < b.n; ++u) {
+      const RotJob& j = jobs[k0 + u];
+      b.it[u] = RotItem{j.ct, j.out, keys->keys + (size_t)keys->slot_of_rot[j.rot] * keys->key_stride, j.rot, 0};
+    }
+    HIP_TRY(launch_rotations(L, b, r));
+  }
   return PVFL_OK;
 }
 }  // namespace pvfl
@@ -551,40 +611,25 @@ extern "C" pvfl_status pvfl_rotate(pvfl_ctx* c, const pvfl_rotkeys* keys, int32_
   if (galois >= (uint32_t)(2 * N) || c->log5[galois] < 0) return fail(PVFL_E_INVALID, "Galois element not in <5>");
   const int rot = c->log5[galois];
   if (keys->slot_of_rot[rot] < 0) return fail(PVFL_E_NOKEY, "missing rotation key");
-  const KsLevel& kl = c->ks_host[level];
-  const size_t Q = (size_t)(level + 1) * N;
-  const size_t need = (size_t)kl.beta * kl.K * N + Q + 2 * (size_t)kl.K * N + 2 * (size_t)c->alpha * N + 2 * Q + 2 * Q;
+  const size_t Q = (size_t)(level + 1) * N, per = rot_scratch_doubles(c, level);
   double* ws;
-  pvfl_status st = ctx_scratch(c, need * sizeof(double), &ws);
+  pvfl_status st = ctx_scratch(c, (per + 2 * Q) * sizeof(double), &ws);
   if (st != PVFL_OK) return st;
-  double* digits = ws;
-  double* yup = digits + (size_t)kl.beta * kl.K * N;
-  double* u = yup + Q;
-  double* ydown = u + 2 * (size_t)kl.K * N;
-  double* v = ydown + 2 * (size_t)c->alpha * N;
-  double* rct = v + 2 * Q;
   const double* ct = (const double*)ct_v;
   double* out = (double*)out_v;
-  LaunchCtx L = launch_ctx(c, stream);
-  if (hoisted) {
-    HIP_TRY(launch_modup(L, ct, 0, 1, level, c->ks_dev + level, kl.n_tasks, yup, digits, 0));
-    if ((st = keyswitch_digits(c, keys, level, digits, rot, rot, u, ydown, v, stream)) != PVFL_OK) return st;
-    HIP_TRY(launch_automorph(L, ct, level + 1, N, rot, rct));
-  } else {
-    HIP_TRY(launch_automorph(L, ct, 2 * (level + 1), N, rot, rct));
-    HIP_TRY(launch_modup(L, rct, 0, 1, level, c->ks_dev + level, kl.n_tasks, yup, digits, 0));
-    if ((st = keyswitch_digits(c, keys, level, digits, 0, rot, u, ydown, v, stream)) != PVFL_OK) return st;
+  if (out < ct + 2 * Q && ct < out + 2 * Q) {  // in place: the last kernel reads the input through the rotation
+    HIP_TRY(hipMemcpyAsync(ws + per, ct, 2 * Q * sizeof(double), hipMemcpyDeviceToDevice, (hipStream_t)stream));
+    ct = ws + per;
   }
-  // out = (phi(c0) + v0, v1)
-  HIP_TRY(launch_ct_add(L, rct, v, level, N, out));  // adds both halves; fix c1 below
-  HIP_TRY(hipMemcpyAsync(out + Q, v + Q, Q * sizeof(double), hipMemcpyDeviceToDevice, (hipStream_t)stream));
-  return PVFL_OK;
+  const RotJob job{ct, out, rot};
+  return run_rotations(c, keys, level, &job, 1, hoisted == 0, false, ws, 1, nullptr, stream);
 }
 
 extern "C" pvfl_status pvfl_rescale(pvfl_ctx* c, int32_t level, const void* ct, void* out, void* stream) {
   if (!c || !ct || !out) return fail(PVFL_E_INVALID, "null argument");
   if (bad_level(c, level) || level < 1) return fail(PVFL_E_LEVEL, "rescale needs level >= 1");
-  HIP_TRY(launch_rescale(launch_ctx(c, stream), (const double*)ct, 2, level, c->rescale[level], (double*)out));
+  HIP_TRY(launch_rescale(launch_ctx(c, stream), (const double*)ct, 2, level, c->rescale[level], (double*)out,
+                         0));
   return PVFL_OK;
 }
 

@@ -34,6 +34,8 @@ struct pvfl_ctx {
   std::vector<void*> dev_allocs;
   double* scratch = nullptr;
   size_t scratch_bytes = 0;
+  double* rot_scratch = nullptr;            // of calls that rotate many ciphertexts (ctx_rot_scratch); in dev_allocs
+  size_t rot_scratch_n = 0;                 // doubles
   // encoder tables (slot <-> FFT index, twiddles), created on first use
   void* enc_tabs = nullptr;
   void (*enc_tabs_free)(void*) = nullptr;
@@ -125,10 +127,22 @@ struct KernelTimer {
   }
 };
 LimbMap qp_map(const pvfl_ctx* c, int lv, bool with_p);
-LimbMap key_limb_map(const pvfl_ctx* c, int lv);
 LaunchCtx launch_ctx(const pvfl_ctx* c, void* stream);
 pvfl_status ctx_scratch(pvfl_ctx* c, size_t bytes, double** out);
 pvfl_status noalloc_scratch_init(int device);  // plan.cpp
-pvfl_status keyswitch_digits(pvfl_ctx* c, const pvfl_rotkeys* keys, int lv, const double* digits, int rot_digits,
-                             int key_rot, double* u, double* ydown, double* v, void* stream);
+pvfl_status ctx_rot_scratch(pvfl_ctx* c, size_t per, int want, void* stream, double** out, int* n);
+// doubles of scratch one rotation at level lv needs
+size_t rot_scratch_doubles(const pvfl_ctx* c, int lv);
+struct RotJob {
+  const double* ct;  // [2][lv+1][N]
+  double* out;       // [2][lv+1][N], overlapping no input
+  int rot;           // slots, 0 <= rot < N/2
+};
+// out = RotL(ct) (add: ct + RotL(ct)) for n jobs, at_once of them side by
+// side on scratch of at_once * rot_scratch_doubles.  pre: the automorphism
+// precedes the ModUp (O3), else the hoisted order (O4).  With shared_digits
+// (O4, every job rotates the one ciphertext whose ModUp they hold) a job
+// needs only 2 alpha N doubles of scratch.
+pvfl_status run_rotations(pvfl_ctx* c, const pvfl_rotkeys* keys, int lv, const RotJob* jobs, int n, bool pre, bool add,
+                          double* scratch, int at_once, const double* shared_digits, void* stream);
 }  // namespace pvfl

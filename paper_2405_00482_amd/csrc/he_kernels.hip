@@ -349,13 +349,14 @@ NTT_KERNEL(LOGN) void k_modup_conv(const double* __restrict__ y, const double* _
   constexpr int N = 1 << LOGN, T = NttShape<LOGN>::T;
   NTT_LDS(LOGN);
   const int nt = kl->n_tasks;
-  const KsTask task = kl->up_task[blockIdx.x % nt];
+  const KsTask& task = kl->up_task[blockIdx.x % nt];  // by reference: a copy indexed at run time would go to scratch memory
+  const int nsrc = task.nsrc, src0 = task.src0;
   const int c = blockIdx.x / nt;
   const int K = kl->K, lv = kl->lv;
   const int pi = task.prime;
   const ModQ m = tb.mods[pi];
   double* dst = digits + (size_t)c * dig_stride + ((size_t)task.digit * K + task.limb) * N;
-  if (task.nsrc == 0) {  // limb of the digit itself: residues kept as they are
+  if (nsrc == 0) {  // limb of the digit itself: residues kept as they are
     const double* src = (ct_tab ? ct_tab[c] : ct + (size_t)c * ct_stride) + (size_t)(lv + 1 + task.limb) * N;
     for (int t = threadIdx.x; t < N; t += T) dst[t] = src[t];
     return;
@@ -363,7 +364,7 @@ NTT_KERNEL(LOGN) void k_modup_conv(const double* __restrict__ y, const double* _
   const double* yc = y + (size_t)c * (lv + 1) * N;
   ntt_fwd_out<LOGN>(s, [&](int j) {
       double acc = 0.0;
-      for (int u = 0; u < task.nsrc; ++u) acc += mulmod(yc[(size_t)(task.src0 + u) * N + j], task.hat[u], m);
+      for (int u = 0; u < nsrc; ++u) acc += mulmod(yc[(size_t)(src0 + u) * N + j], task.hat[u], m);
       return reduce(acc, m);
     }, tb.fwd_tw + (size_t)pi * N, tb.perm, m, [&](int t, double v) { dst[t] = v; });
 }
@@ -406,36 +407,78 @@ NTT_KERNEL(LOGN) void k_moddown_q(const double* __restrict__ u, const double* __
   const double pinv = kl->down_pinv[i];
   const double* ui = u + ((size_t)x * K + i) * N;
   double* oi = out_tab ? out_tab[x >> 1] + ((size_t)(x & 1) * (lv + 1) + i) * N : out + ((size_t)x * (lv + 1) + i) * N;
-  ntt_fwd_out<LOGN>(s, [&](int c) {
-      double acc = -h;
-      for (int k = 0; k < alpha; ++k) acc += mulmod(yx[(size_t)k * N + c], kl->down_hat[k * kMaxLimbs + i], m);
-      return reduce(acc, m);
-    }, tb.fwd_tw + (size_t)i * N, tb.perm, m, [&](int t, double v) { oi[t] = reduce(mulmod(ui[t] - v, pinv, m), m); });
+  auto conv = [&](int c) {
+    double acc = -h;
+    for (int k = 0; k < alpha; ++k) acc += mulmod(yx[(size_t)k * N + c], kl->down_hat[k * kMaxLimbs + i], m);
+    return reduce(acc, m);
+  };
+  if constexpr (LOGN <= 14) {
+    constexpr int T = NttShape<LOGN>::T;
+    double c[16], v[16], uv[16];  // u loaded before the transform: one memory latency instead of eight
+#pragma unroll
+    for (int w = 0; w < 16; ++w) uv[w] = ui[(int)opaque_tid() + (w >> 1) * T + (w & 1) * (N / 2)];
+#pragma unroll
+    for (int w = 0; w < 16; ++w) c[w] = conv((int)opaque_tid() + w * T);
+    ntt_fwd_regs<LOGN>(s, c, tb.fwd_tw + (size_t)i * N, m);
+    slots_from_lds<LOGN>(s, v);
+#pragma unroll
+    for (int w = 0; w < 16; ++w)
+      oi[(int)opaque_tid() + (w >> 1) * T + (w & 1) * (N / 2)] = reduce(mulmod(uv[w] - v[w], pinv, m), m);
+  } else {
+    ntt_fwd_out<LOGN>(s, conv, tb.fwd_tw + (size_t)i * N, tb.perm, m,
+                      [&](int t, double v) { oi[t] = reduce(mulmod(ui[t] - v, pinv, m), m); });
+  }
 }
 
-// Rescale by q_lv (drop the last limb, coefficient-wise rounding) on `npoly`
-// polys [npoly][lv+1][N] -> [npoly][lv][N].  Same formula as ModDown with P = q_lv.
+// Rescale by q_lv (drop the last limb, coefficient-wise rounding) on polys
+// x = 2 pair + half, limbs [lv+1][N] at in + pair in_stride + half (lv+1) N,
+// out [x][lv][N].  Same formula as ModDown with P = q_lv.  With pt, the input
+// is ct * pt (pt at pt + pair pt_stride): the product never goes to memory.
 template <int LOGN>
-NTT_KERNEL(LOGN) void k_rescale(const double* __restrict__ in, int lv, const RescaleArgs ra, double* __restrict__ out,
-                                 DevTabs tb) {
-  constexpr int N = 1 << LOGN, PER = NttShape<LOGN>::PER;
+NTT_KERNEL(LOGN) void k_rescale(const double* __restrict__ in, size_t in_stride, const double* __restrict__ pt,
+                                 size_t pt_stride, int lv, const RescaleArgs ra, double* __restrict__ out, DevTabs tb) {
+  constexpr int N = 1 << LOGN, PER = NttShape<LOGN>::PER, T = NttShape<LOGN>::T;
   NTT_LDS(LOGN);
   const int i = blockIdx.x % lv, x = blockIdx.x / lv;
   const ModQ ml = tb.mods[lv];
   const ModQ m = tb.mods[i];
+  const double* poly = in + (size_t)(x >> 1) * in_stride + (size_t)(x & 1) * (lv + 1) * N;
+  const double* pp = pt ? pt + (size_t)(x >> 1) * pt_stride : nullptr;
   // INTT of the dropped limb (every block recomputes it; the limb is L2-resident)
-  const double* last = in + ((size_t)x * (lv + 1) + lv) * N;
+  const double* last = poly + (size_t)lv * N;
+  const double* plast = pp + (size_t)lv * N;
   double c[PER];
-  ntt_inv_in_regs<LOGN>(s, [&](int t) { return last[t]; }, tb.inv_tw + (size_t)lv * N, tb.perm, ml, tb.ninv[lv], c);
+  if (pp)
+    ntt_inv_in_regs<LOGN>(s, [&](int t) { return mulmod(last[t], plast[t], ml); }, tb.inv_tw + (size_t)lv * N, tb.perm,
+                          ml, tb.ninv[lv], c);
+  else
+    ntt_inv_in_regs<LOGN>(s, [&](int t) { return last[t]; }, tb.inv_tw + (size_t)lv * N, tb.perm, ml, tb.ninv[lv], c);
   const double hl = ra.half_mod_last, hi = ra.half_mod[i];
   // [c + h]_{q_l} lifted to q_i, minus h mod q_i
 #pragma unroll
   for (int w = 0; w < PER; ++w) c[w] = reduce(canon(c[w] + hl, ml) - hi, m);
   const double inv = ra.inv_last[i];
-  const double* ui = in + ((size_t)x * (lv + 1) + i) * N;
+  const double* ui = poly + (size_t)i * N;
+  const double* pi = pp + (size_t)i * N;
   double* oi = out + ((size_t)x * lv + i) * N;
-  ntt_fwd_regs_out<LOGN>(s, c, tb.fwd_tw + (size_t)i * N, tb.perm, m,
-                         [&](int t, double v) { oi[t] = reduce(mulmod(ui[t] - v, inv, m), m); });
+  if constexpr (LOGN <= 14) {
+    double u[16], v[16];  // loaded before the transform: one memory latency instead of eight
+#pragma unroll
+    for (int w = 0; w < 16; ++w) {
+      const int t = (int)opaque_tid() + (w >> 1) * T + (w & 1) * (N / 2);
+      u[w] = pp ? mulmod(ui[t], pi[t], m) : ui[t];
+    }
+    ntt_fwd_regs<LOGN>(s, c, tb.fwd_tw + (size_t)i * N, m);
+    slots_from_lds<LOGN>(s, v);
+#pragma unroll
+    for (int w = 0; w < 16; ++w)
+      oi[(int)opaque_tid() + (w >> 1) * T + (w & 1) * (N / 2)] = reduce(mulmod(u[w] - v[w], inv, m), m);
+  } else {
+    ntt_fwd_regs_out<LOGN>(s, c, tb.fwd_tw + (size_t)i * N, tb.perm, m, [&](int t, double v) {
+      const double u = pp ? mulmod(ui[t], pi[t], m) : ui[t];
+      oi[t] = reduce(mulmod(u - v, inv, m), m);
+    });
+  }
 }
 
 // ---------------------------------------------------------------------------
@@ -540,75 +583,6 @@ __global__ __launch_bounds__(256) void k_ct_add(const double* __restrict__ a, co
   if (idx >= tot) return;
   const int i = (int)((idx / N) % (lv + 1));
   out[idx] = reduce(a[idx] + b[idx], mods[i]);
-}
-
-// automorphism X -> X^(5^rot) on npoly polys of nl limbs: an orbit shift
-__global__ __launch_bounds__(256) void k_automorph(const double* __restrict__ in, int npoly_limbs, int N, int rot,
-                                                   double* __restrict__ out) {
-  const size_t idx = (size_t)blockIdx.x * 256 + threadIdx.x;
-  if (idx >= (size_t)npoly_limbs * N) return;
-  const int t = (int)(idx % N);
-  out[idx] = in[idx - t + orbit_shift(t, rot, N >> 1)];
-}
-
-// (u0, u1) = sum_j D_j * (b_j, a_j) over K limbs, digits optionally shifted by
-// `rot` (hoisted rotation) -- the unfused key inner product of the eager plan.
-__global__ __launch_bounds__(256) void k_key_inner(const double* __restrict__ digits, int beta, int K, int N, int rot,
-                                                   const double* __restrict__ key, int key_limbs,
-                                                   LimbMap limb_prime, LimbMap key_limb,
-                                                   const ModQ* __restrict__ mods, double* __restrict__ u) {
-  const int t = blockIdx.x * 256 + threadIdx.x;
-  const int r = blockIdx.y;
-  const ModQ m = mods[limb_prime.idx[r]];
-  const int ts = orbit_shift(t, rot, N >> 1);
-  const int kl = key_limb.idx[r];
-  double u0 = 0.0, u1 = 0.0;
-  for (int j = 0; j < beta; ++j) {
-    const double d = digits[((size_t)j * K + r) * N + ts];
-    const double* kj = key + (size_t)j * 2 * key_limbs * N;
-    u0 += mulmod(d, kj[(size_t)kl * N + t], m);
-    u1 += mulmod(d, kj[(size_t)(key_limbs + kl) * N + t], m);
-  }
-  u[(size_t)r * N + t] = reduce(u0, m);
-  u[(size_t)(K + r) * N + t] = reduce(u1, m);
-}
-
-__global__ __launch_bounds__(256) void k_fill_zero(double* __restrict__ p, size_t n) {
-  const size_t idx = (size_t)blockIdx.x * 256 + threadIdx.x;
-  if (idx < n) p[idx] = 0.0;
-}
-
-__global__ __launch_bounds__(256) void k_add_limbs(const double* __restrict__ a, const double* __restrict__ b, int nlimbs,
-                                                   int N, LimbMap map, const ModQ* __restrict__ mods,
-                                                   double* __restrict__ out) {
-  const size_t idx = (size_t)blockIdx.x * 256 + threadIdx.x;
-  if (idx >= (size_t)nlimbs * N) return;
-  const int l = (int)(idx / N) % map.n;
-  out[idx] = reduce(a[idx] + b[idx], mods[map.idx[l]]);
-}
-
-// one term of the eager (per-rotation ModDown) plan:
-//   acc0 += (c0[shift] + v0) * pt,  acc1 += v1 * pt      (v != null)
-//   acc0 += c0 * pt,                acc1 += c1 * pt      (v == null)
-__global__ __launch_bounds__(256) void k_eager_term(const double* __restrict__ c0, const double* __restrict__ c1,
-                                                    const double* __restrict__ v, int rot, const double* __restrict__ pt,
-                                                    int lv, int N, const ModQ* __restrict__ mods, double* __restrict__ acc) {
-  const size_t idx = (size_t)blockIdx.x * 256 + threadIdx.x;
-  const size_t Q = (size_t)(lv + 1) * N;
-  if (idx >= Q) return;
-  const int i = (int)(idx / N), t = (int)(idx % N);
-  const ModQ m = mods[i];
-  const double p = pt[idx];
-  double x0, x1;
-  if (v) {
-    x0 = reduce(c0[idx - t + orbit_shift(t, rot, N >> 1)] + v[idx], m);
-    x1 = v[Q + idx];
-  } else {
-    x0 = c0[idx];
-    x1 = c1[idx];
-  }
-  acc[idx] = reduce(acc[idx] + mulmod(x0, p, m), m);
-  acc[Q + idx] = reduce(acc[Q + idx] + mulmod(x1, p, m), m);
 }
 
 // Alg. 3 ciphertext-matrix product: thread = (coefficient t, limb r, output k)
@@ -779,11 +753,15 @@ hipError_t launch_moddown(const LaunchCtx& L, const double* u, int npoly, int lv
 }
 
 template <int LOGN>
-static void rescale_impl(const LaunchCtx& L, const double* in, int npoly, int lv, const RescaleArgs& ra, double* out) {
-  hipLaunchKernelGGL(k_rescale<LOGN>, dim3(npoly * lv), dim3(NttShape<LOGN>::T), 0, L.stream, in, lv, ra, out, L.tb);
+static void rescale_impl(const LaunchCtx& L, const double* in, int npoly, int lv, const RescaleArgs& ra, double* out,
+                         size_t in_stride, const double* pt, size_t pt_stride) {
+  hipLaunchKernelGGL(k_rescale<LOGN>, dim3(npoly * lv), dim3(NttShape<LOGN>::T), 0, L.stream, in, in_stride, pt, pt_stride,
+                     lv, ra, out, L.tb);
 }
-hipError_t launch_rescale(const LaunchCtx& L, const double* in, int npoly, int lv, const RescaleArgs& ra, double* out) {
-  DISPATCH_LOGN(L, rescale_impl, L, in, npoly, lv, ra, out);
+hipError_t launch_rescale(const LaunchCtx& L, const double* in, int npoly, int lv, const RescaleArgs& ra, double* out,
+                          size_t in_stride, const double* pt, size_t pt_stride) {
+  if (npoly <= 0) return hipSuccess;
+  DISPATCH_LOGN(L, rescale_impl, L, in, npoly, lv, ra, out, in_stride, pt, pt_stride);
   return hipGetLastError();
 }
 
@@ -811,26 +789,6 @@ hipError_t launch_ctmat(const LaunchCtx& L, const double* ct, const double* pt, 
   return hipGetLastError();
 }
 
-hipError_t launch_fill_zero(const LaunchCtx& L, double* p, size_t n) {
-  hipLaunchKernelGGL(k_fill_zero, dim3(blocks_for(n)), dim3(256), 0, L.stream, p, n);
-  return hipGetLastError();
-}
-
-hipError_t launch_add_limbs(const LaunchCtx& L, const double* a, const double* b, int nlimbs, int N, LimbMap map,
-                            double* out) {
-  const size_t tot = (size_t)nlimbs * N;
-  hipLaunchKernelGGL(k_add_limbs, dim3(blocks_for(tot)), dim3(256), 0, L.stream, a, b, nlimbs, N, map, L.tb.mods, out);
-  return hipGetLastError();
-}
-
-hipError_t launch_eager_term(const LaunchCtx& L, const double* c0, const double* c1, const double* v, int rot,
-                             const double* pt, int lv, int N, double* acc) {
-  const size_t tot = (size_t)(lv + 1) * N;
-  hipLaunchKernelGGL(k_eager_term, dim3(blocks_for(tot)), dim3(256), 0, L.stream, c0, c1, v, rot, pt, lv, N, L.tb.mods,
-                     acc);
-  return hipGetLastError();
-}
-
 hipError_t launch_scale_by_p(const LaunchCtx& L, const double* ct, int lv, int N, const double* pmod_dev, double* out,
                              int nct, const double* const* ct_tab) {
   const size_t tot = (size_t)2 * (lv + 1) * N;
@@ -848,19 +806,6 @@ hipError_t launch_ct_mul_pt(const LaunchCtx& L, const double* ct, const double* 
 hipError_t launch_ct_add(const LaunchCtx& L, const double* a, const double* b, int lv, int N, double* out) {
   const size_t tot = (size_t)2 * (lv + 1) * N;
   hipLaunchKernelGGL(k_ct_add, dim3(blocks_for(tot)), dim3(256), 0, L.stream, a, b, lv, N, L.tb.mods, out);
-  return hipGetLastError();
-}
-
-hipError_t launch_automorph(const LaunchCtx& L, const double* in, int npoly_limbs, int N, int rot, double* out) {
-  const size_t tot = (size_t)npoly_limbs * N;
-  hipLaunchKernelGGL(k_automorph, dim3(blocks_for(tot)), dim3(256), 0, L.stream, in, npoly_limbs, N, rot, out);
-  return hipGetLastError();
-}
-
-hipError_t launch_key_inner(const LaunchCtx& L, const double* digits, int beta, int K, int N, int rot, const double* key,
-                            int key_limbs, LimbMap limb_prime, LimbMap key_limb, double* u) {
-  hipLaunchKernelGGL(k_key_inner, dim3(N / 256, K), dim3(256), 0, L.stream, digits, beta, K, N, rot, key, key_limbs,
-                     limb_prime, key_limb, L.tb.mods, u);
   return hipGetLastError();
 }
 

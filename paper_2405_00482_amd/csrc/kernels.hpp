@@ -67,6 +67,32 @@ struct RotKeyList {
   uint32_t galois[kKeysPerLaunch];
 };
 
+// Single rotations run side by side: rotation `it[k]` reads ciphertext ct
+// [2][lv+1][N], writes out (not overlapping any input), uses key
+// [beta][2][key_limbs][N] of its Galois element.  Passed by value.
+constexpr int kRotsPerLaunch = 64;
+struct RotItem {
+  const double* ct;
+  double* out;
+  const double* key;
+  int rot, pad;
+};
+struct RotBatch {
+  int n;
+  RotItem it[kRotsPerLaunch];
+};
+struct RotRun {
+  const KsLevel* kl_dev;
+  int lv, alpha, n_tasks, key_limbs;
+  int pre;             // 1: the automorphism precedes the ModUp (O3); 0: hoisted order (O4)
+  int add;             // 1: out = ct + RotL(ct); 0: out = RotL(ct)
+  bool shared_digits;  // digits already hold the ModUp of the one ciphertext every item rotates (dig_stride 0)
+  double* yup;         // [n][lv+1][N]
+  double* digits;      // item k at digits + k * dig_stride, [beta][K][N]
+  size_t dig_stride;
+  double* ydown;       // [n][2][alpha][N]
+};
+
 struct RescaleArgs {
   double half_mod_last;            // floor(q_l / 2)
   double half_mod[kMaxLimbs];      // floor(q_l / 2) mod q_i
@@ -112,7 +138,14 @@ hipError_t launch_modup(const LaunchCtx& L, const double* ct, size_t ct_stride, 
 // out_tab (optional): output of poly x at out_tab[x/2] + (x%2)*(lv+1)*N
 hipError_t launch_moddown(const LaunchCtx& L, const double* u, int npoly, int lv, int alpha, const KsLevel* kl_dev,
                           double* y, double* out, double* const* out_tab = nullptr);
-hipError_t launch_rescale(const LaunchCtx& L, const double* in, int npoly, int lv, const RescaleArgs& ra, double* out);
+// npoly polys (pairs of one ciphertext at in + pair * in_stride; 0 polys apart = one shared ciphertext), each
+// limb times pt + pair * pt_stride first when pt is given
+hipError_t launch_rescale(const LaunchCtx& L, const double* in, int npoly, int lv, const RescaleArgs& ra, double* out,
+                          size_t in_stride, const double* pt = nullptr, size_t pt_stride = 0);
+hipError_t launch_rotations(const LaunchCtx& L, const RotBatch& b, const RotRun& r);
+// out = (out_add ? out : 0) + sum_k ct_k pt_k (pt null: plain sum), ct_k at ct + k ct_stride, pt_k at pt + k pt_stride
+hipError_t launch_sum_cts(const LaunchCtx& L, const double* ct, size_t ct_stride, const double* pt, size_t pt_stride,
+                          int n, int lv, int N, bool out_add, double* out);
 hipError_t launch_diag_lazy(const LaunchCtx& L, const DiagArgs& a, int nchunk);
 // part[y][nchunk][2][K][N] summed over the chunks into acc[y][2][K][N], y < ngroups
 hipError_t launch_sum_partials(const LaunchCtx& L, const double* part, int nchunk, int K, int N, LimbMap limb_prime,
@@ -120,18 +153,8 @@ hipError_t launch_sum_partials(const LaunchCtx& L, const double* part, int nchun
 // Alg. 3: out[k] = sum_i ct[i] * pt[i][k]   (ct [nct][2][lv+1][N], pt [nct][nout][lv+1][N])
 hipError_t launch_ctmat(const LaunchCtx& L, const double* ct, const double* pt, int nct, int nout, int lv, int N,
                         double* out);
-hipError_t launch_fill_zero(const LaunchCtx& L, double* p, size_t n);
-hipError_t launch_add_limbs(const LaunchCtx& L, const double* a, const double* b, int nlimbs, int N, LimbMap map,
-                            double* out);
-// acc (ct at lv) += (c0[shift rot] + v0, v1) * pt   (v0 = v1 = null: (c0, c1) unshifted)
-hipError_t launch_eager_term(const LaunchCtx& L, const double* c0, const double* c1, const double* v, int rot, const double* pt,
-                             int lv, int N, double* acc);
 hipError_t launch_scale_by_p(const LaunchCtx& L, const double* ct, int lv, int N, const double* pmod_dev, double* out,
                              int nct = 1, const double* const* ct_tab = nullptr);
 hipError_t launch_ct_mul_pt(const LaunchCtx& L, const double* ct, const double* pt, int lv, int N, double* out);
 hipError_t launch_ct_add(const LaunchCtx& L, const double* a, const double* b, int lv, int N, double* out);
-hipError_t launch_automorph(const LaunchCtx& L, const double* in, int npoly_limbs, int N, int rot, double* out);
-hipError_t launch_key_inner(const LaunchCtx& L, const double* digits, int beta, int K, int N, int rot, const double* key,
-                            int key_limbs, LimbMap limb_prime, LimbMap key_limb, double* u);
-
 }  // namespace pvfl

@@ -378,6 +378,31 @@ struct OrbitWalk {
   }
 };
 
+// The 16 slots of a thread, v[2w] and v[2w + 1] at t = tid + w N/16 and
+// t + N/2 (w < 8), into LDS at their bit-reversed places (centred) and back.
+template <int LOGN>
+__device__ __forceinline__ void slots_to_lds(double* s, const double (&v)[16], ModQ m) {
+  OrbitWalk ow = OrbitWalk::start<LOGN>();
+#pragma unroll
+  for (int w = 0; w < 8; ++w) {
+    const int j = ow.brv_index<LOGN>();
+    s[lds_pad(j)] = reduce(v[2 * w], m);
+    s[lds_pad(j ^ ((1 << LOGN) - 1))] = reduce(v[2 * w + 1], m);
+    ow.next<LOGN>();
+  }
+}
+template <int LOGN>
+__device__ __forceinline__ void slots_from_lds(const double* s, double (&v)[16]) {
+  OrbitWalk ow = OrbitWalk::start<LOGN>();
+#pragma unroll
+  for (int w = 0; w < 8; ++w) {
+    const int j = ow.brv_index<LOGN>();
+    v[2 * w] = s[lds_pad(j)];
+    v[2 * w + 1] = s[lds_pad(j ^ ((1 << LOGN) - 1))];
+    ow.next<LOGN>();
+  }
+}
+
 // ---------------------------------------------------------------------------
 // Size-generic entry points.  Thread tid owns coefficients j = tid + w*T,
 // w < PER, and the evaluation-domain (orbit-order) slots t = tid + u*T.
@@ -459,14 +484,14 @@ __device__ __forceinline__ void ntt_inv_in_regs(double* s, In in, const double* 
                                                 double (&c)[NttShape<LOGN>::PER]) {
   constexpr int N = 1 << LOGN, T = NttShape<LOGN>::T;
   if constexpr (LOGN <= 14) {
-    OrbitWalk ow = OrbitWalk::start<LOGN>();
-#pragma unroll 2
+    double v[16];  // all loads of the thread's slots in flight together
+#pragma unroll
     for (int w = 0; w < 8; ++w) {
-      const int t = (int)opaque_tid() + w * T, j = ow.brv_index<LOGN>();
-      s[lds_pad(j)] = reduce(in(t), m);
-      s[lds_pad(j ^ (N - 1))] = reduce(in(t + N / 2), m);
-      ow.next<LOGN>();
+      const int t = (int)opaque_tid() + w * T;
+      v[2 * w] = in(t);
+      v[2 * w + 1] = in(t + N / 2);
     }
+    slots_to_lds<LOGN>(s, v, m);
     __syncthreads();
     ntt_inv_regs<LOGN>(s, c, itw, m, ninv);
   } else {

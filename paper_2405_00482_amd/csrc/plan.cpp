@@ -305,16 +305,40 @@ static size_t ws_doubles(const pvfl_plan* p, int count = 1) {
   }
   return 0;
 }
-extern "C" size_t pvfl_bytes_workspace(const pvfl_plan* p) { return p ? sizeof(double) * std::max<size_t>(ws_doubles(p), 1) : 0; }
+
+// Per-rotation ModDown: the rotations of a block run side by side, as many as
+// the workspace holds.  One fits the smallest workspace (ws_doubles); the
+// size that the query recommends holds all of a block, up to kRotBatchBytes
+// in all (the fixed array of the allocation-free product).  A 256 x 512
+// product at N = 2^13 (31 rotations, 16 MiB) took 1.16 ms with its rotations
+// one after the other and takes 0.11 ms side by side.
+static constexpr size_t kRotBatchBytes = size_t(64) << 20;
+static size_t eager_fixed(const pvfl_plan* p) {  // hoisted: the shared digits and their ModUp
+  return p->opts.unhoisted ? 0 : ((size_t)p->beta * p->K + p->lv + 1) * p->ctx->N;
+}
+static size_t eager_per(const pvfl_plan* p) {  // one rotation: its result and its scratch
+  const size_t N = p->ctx->N, own = p->opts.unhoisted ? rot_scratch_doubles(p->ctx, p->lv) : 2 * (size_t)p->ctx->alpha * N;
+  return own + 2 * (size_t)(p->lv + 1) * N;
+}
+static size_t ws_preferred(const pvfl_plan* p, int count) {
+  const size_t need = std::max<size_t>(ws_doubles(p, count), 1);
+  const bool eager = (p->opts.kind == PVFL_PLAN_HYBRID || p->opts.kind == PVFL_PLAN_DIAG) && !p->opts.lazy_moddown;
+  if (!eager) return need;
+  const size_t cap = kRotBatchBytes / sizeof(double), per = eager_per(p), fixed = eager_fixed(p);
+  if (cap <= need) return need;
+  const size_t n = std::min<size_t>({(size_t)std::max(1, p->info.mprime - 1), (size_t)kRotsPerLaunch, (cap - fixed) / per});
+  return std::max(need, fixed + n * per);
+}
+extern "C" size_t pvfl_bytes_workspace(const pvfl_plan* p) { return p ? sizeof(double) * ws_preferred(p, 1) : 0; }
 extern "C" size_t pvfl_bytes_workspace_sum(const pvfl_plan* p, int32_t count) {
-  return p && count >= 1 ? sizeof(double) * std::max<size_t>(ws_doubles(p, count), 1) : 0;
+  return p && count >= 1 ? sizeof(double) * ws_preferred(p, count) : 0;
 }
 
 // the caller's workspace (plans with no workspace -- CTMAT, COL -- take NULL)
 static pvfl_status get_ws(const pvfl_plan* p, void* ws, size_t ws_bytes, double** out, int count = 1) {
   *out = (double*)ws;
   if (ws_doubles(p, count) == 0) return PVFL_OK;
-  const size_t need = pvfl_bytes_workspace_sum(p, count);
+  const size_t need = sizeof(double) * ws_doubles(p, count);
   if (!ws) return fail(PVFL_E_INVALID, "the plan needs a workspace of " + std::to_string(need) + " bytes");
   if (ws_bytes < need) return fail(PVFL_E_SHAPE, "workspace too small");
   return PVFL_OK;
@@ -339,6 +363,7 @@ static pvfl_status run_diag_lazy(const pvfl_plan* p, int count, const double* co
                                  const pvfl_rotkeys* keys, double* out, double* ws, void* stream) {
   pvfl_ctx* c = p->ctx;
   const int N = c->N, lv = p->lv, K = p->K;
+  const size_t rot_per = rot_scratch_doubles(c, lv) + 2 * (size_t)(lv + 1) * N;  // one giant rotation and its result
   const int CB1 = p->info.col_blocks, CB = count * CB1, RB = p->info.row_blocks;
   const int bs = p->info.bsgs, g = bs ? p->nchunk / p->chunks_per_giant : 1;
   const size_t Q = (size_t)(lv + 1) * N, KN = (size_t)K * N, DG = (size_t)p->beta * KN;
@@ -356,9 +381,9 @@ static pvfl_status run_diag_lazy(const pvfl_plan* p, int count, const double* co
   double* acc = part + (size_t)CB * p->nchunk * 2 * KN; // [g][2][K][N]
   double* ydown = acc + (size_t)g * 2 * KN;             // [2g][alpha][N]
   double* cj = ydown + (size_t)2 * g * c->alpha * N;    // BSGS: [g][2][lv+1][N] giant-step inner sums
-  double* dig2 = cj + (bs ? g * 2 * Q : 0);             // BSGS: digits of one inner sum
-  double* v = dig2 + (bs ? DG : 0);                     // BSGS: key-switched part [2][lv+1][N]
-  double* rct = v + (bs ? 2 * Q : 0);                   // BSGS: phi(c0) [lv+1][N]
+  // BSGS: the giant rotations run side by side on the memory of the partial
+  // sums and the accumulators, which are spent by then
+  const int giants_at_once = bs ? std::min(g - 1, (int)((ydown - part) / rot_per)) : 0;
   LaunchCtx L = launch_ctx(c, stream);
   const int mprime = p->info.mprime;
   if (mprime == 1 && c->alpha == 1) {
@@ -368,11 +393,7 @@ static pvfl_status run_diag_lazy(const pvfl_plan* p, int count, const double* co
     // conversion may add P, and the Q u P form's result differs by one.
     for (int b = 0; b < RB; ++b) {
       double* ob = out + (size_t)b * 2 * Q;
-      HIP_TRY(launch_fill_zero(L, ob, 2 * Q));
-      for (int cb = 0; cb < CB; ++cb) {
-        const double* ct = ct_of(cb);
-        HIP_TRY(launch_eager_term(L, ct, ct + Q, nullptr, 0, pt_of(b, cb), lv, N, ob));
-      }
+      for (int cb = 0; cb < CB; ++cb) HIP_TRY(launch_sum_cts(L, ct_of(cb), 0, pt_of(b, cb), 0, 1, lv, N, cb > 0, ob));
     }
     return PVFL_OK;
   }
@@ -395,7 +416,6 @@ static pvfl_status run_diag_lazy(const pvfl_plan* p, int count, const double* co
   a.chunk = p->chunk;
   a.mods = c->tabs.mods;
   const LimbMap lp = qp_map(c, lv, true);
-  const LimbMap qm = qp_map(c, lv, false);
   for (int r = 0; r < K; ++r) {
     a.limb_prime[r] = lp.idx[r];
     a.key_limb[r] = lp.idx[r];
@@ -415,7 +435,6 @@ static pvfl_status run_diag_lazy(const pvfl_plan* p, int count, const double* co
                                    (double)p->nchunk * 2 * KN);
   for (int b = 0; b < RB; ++b) {
     double* ob = out + (size_t)b * 2 * Q;
-    if (bs) HIP_TRY(launch_fill_zero(L, ob, 2 * Q));
     int z = 0;
     for (int cb = 0; cb < CB; ++cb) {
       a.digits = digits + cb * DG;
@@ -439,16 +458,19 @@ static pvfl_status run_diag_lazy(const pvfl_plan* p, int count, const double* co
         HIP_TRY(launch_moddown(L, acc, 2 * g, lv, c->alpha, c->ks_dev + lv, ydown, cj));
         kt.stop();
       }
-      HIP_TRY(launch_add_limbs(L, ob, cj, 2 * (lv + 1), N, qm, ob));
-      for (int j = 1; j < g; ++j) {
-        const double* cjj = cj + (size_t)j * 2 * Q;
-        const int rot = j * bs;
-        HIP_TRY(launch_modup(L, cjj, 0, 1, lv, c->ks_dev + lv, kl.n_tasks, yup, dig2, 0));
-        pvfl_status st = keyswitch_digits(c, keys, lv, dig2, rot, rot, acc, ydown, v, stream);  // acc reused: summed above
+      HIP_TRY(launch_sum_cts(L, cj, 0, nullptr, 0, 1, lv, N, cb > 0, ob));
+      // fewer than one there: the single giant rotation's own memory after cj
+      double* rws = giants_at_once > 0 ? part : cj + (size_t)g * 2 * Q;
+      const int at_once = std::max(1, giants_at_once);
+      double* rct = rws + (size_t)at_once * (rot_per - 2 * Q);
+      for (int j0 = 1; j0 < g; j0 += at_once) {
+        const int cnt = std::min(at_once, g - j0);
+        std::vector<RotJob> jobs(cnt);
+        for (int u = 0; u < cnt; ++u)
+          jobs[u] = RotJob{cj + (size_t)(j0 + u) * 2 * Q, rct + (size_t)u * 2 * Q, (j0 + u) * bs};
+        pvfl_status st = run_rotations(c, keys, lv, jobs.data(), cnt, false, false, rws, at_once, nullptr, stream);
         if (st != PVFL_OK) return st;
-        HIP_TRY(launch_automorph(L, cjj, lv + 1, N, rot, rct));
-        HIP_TRY(launch_add_limbs(L, ob, rct, lv + 1, N, qm, ob));
-        HIP_TRY(launch_add_limbs(L, ob, v, 2 * (lv + 1), N, qm, ob));
+        HIP_TRY(launch_sum_cts(L, rct, 2 * Q, nullptr, 0, cnt, lv, N, true, ob));
       }
     }
     if (bs) continue;
@@ -462,97 +484,115 @@ static pvfl_status run_diag_lazy(const pvfl_plan* p, int count, const double* co
   return PVFL_OK;
 }
 
+// Alg. 1 as printed: every rotation has its own ModDown.  The rotations of a
+// block run side by side (see ws_preferred), then their products with the
+// plaintexts are summed.
 static pvfl_status run_diag_eager(const pvfl_plan* p, const double* ct_in, const double* pts, const pvfl_rotkeys* keys,
-                                  double* out, double* ws, void* stream) {
+                                  double* out, double* ws, size_t ws_bytes, void* stream) {
   pvfl_ctx* c = p->ctx;
-  const int N = c->N, lv = p->lv, K = p->K;
-  const size_t Q = (size_t)(lv + 1) * N, KN = (size_t)K * N;
+  const int N = c->N, lv = p->lv, mprime = p->info.mprime;
+  const size_t Q = (size_t)(lv + 1) * N;
   const KsLevel& kl = c->ks_host[lv];
-  double* digits = ws;
-  double* yup = digits + (size_t)p->beta * KN;
-  double* u = yup + Q;
-  double* ydown = u + 2 * KN;
-  double* v = ydown + 2 * (size_t)c->alpha * N;
-  // an unhoisted rotation's phi_i(c1) sits at rct + Q = v + 2Q, past v: ModUp reads
-  // only the c1 half of the ciphertext it is given
-  double* rct = v + Q;
+  const bool o3 = p->opts.unhoisted != 0;  // the automorphism first, then a ModUp of its own (Sec. 2)
+  const size_t fixed = eager_fixed(p), per = eager_per(p);
+  const int at_once = (int)std::min<size_t>({(ws_bytes / sizeof(double) - fixed) / per, (size_t)kRotsPerLaunch,
+                                             (size_t)std::max(1, mprime - 1)});
+  double* digits = ws;                                  // hoisted: [beta][K][N], then ModUp's [lv+1][N]
+  double* scratch = ws + fixed;
+  double* rct = scratch + (size_t)at_once * (per - 2 * Q);  // [at_once][2][lv+1][N] rotated ciphertexts
   LaunchCtx L = launch_ctx(c, stream);
-  const int mprime = p->info.mprime;
-  const bool o3 = p->opts.unhoisted != 0;
+  std::vector<RotJob> jobs(at_once);
   for (int b = 0; b < p->info.row_blocks; ++b) {
     double* acc = out + (size_t)b * 2 * Q;
-    HIP_TRY(launch_fill_zero(L, acc, 2 * Q));
     for (int cb = 0; cb < p->info.col_blocks; ++cb) {
       const double* ct = ct_in + (size_t)cb * 2 * Q;
-      if (mprime > 1 && !o3) HIP_TRY(launch_modup(L, ct, 0, 1, lv, c->ks_dev + lv, kl.n_tasks, yup, digits, 0));
-      for (int i = 0; i < mprime; ++i) {
-        const double* pt = pts + ((size_t)(b * p->info.col_blocks + cb) * mprime + i) * Q;
-        if (i == 0) {
-          HIP_TRY(launch_eager_term(L, ct, ct + Q, nullptr, 0, pt, lv, N, acc));
-        } else {
-          if (o3) {
-            // O3: the automorphism first, then this rotation's own ModUp (Sec. 2)
-            HIP_TRY(launch_automorph(L, ct + Q, lv + 1, N, i, rct + Q));
-            HIP_TRY(launch_modup(L, rct, 0, 1, lv, c->ks_dev + lv, kl.n_tasks, yup, digits, 0));
-          }
-          pvfl_status st = keyswitch_digits(c, keys, lv, digits, o3 ? 0 : i, i, u, ydown, v, stream);
-          if (st != PVFL_OK) return st;
-          HIP_TRY(launch_eager_term(L, ct, nullptr, v, i, pt, lv, N, acc));
-        }
+      const double* pt = pts + (size_t)(b * p->info.col_blocks + cb) * mprime * Q;
+      if (mprime > 1 && !o3)
+        HIP_TRY(launch_modup(L, ct, 0, 1, lv, c->ks_dev + lv, kl.n_tasks, digits + (size_t)p->beta * p->K * N, digits, 0));
+      HIP_TRY(launch_sum_cts(L, ct, 0, pt, 0, 1, lv, N, cb > 0, acc));
+      for (int i0 = 1; i0 < mprime; i0 += at_once) {
+        const int cnt = std::min(at_once, mprime - i0);
+        for (int u = 0; u < cnt; ++u) jobs[u] = RotJob{ct, rct + (size_t)u * 2 * Q, i0 + u};
+        pvfl_status st = run_rotations(c, keys, lv, jobs.data(), cnt, o3, false, scratch, at_once, o3 ? nullptr : digits, stream);
+        if (st != PVFL_OK) return st;
+        HIP_TRY(launch_sum_cts(L, rct, 2 * Q, pt + (size_t)i0 * Q, Q, cnt, lv, N, true, acc));
       }
     }
   }
   return PVFL_OK;
 }
 
-// in-ciphertext rotate-and-sum (DIAG, m < n): ct += RotL(ct, k) for each k
+// in-ciphertext rotate-and-sum (DIAG, m < n): ct += RotL(ct, k) for each k,
+// each step from one of (ct, tmp) to the other
 static pvfl_status run_ras_in_ct(const pvfl_plan* p, const pvfl_rotkeys* keys, double* ct, double* tmp, void* stream) {
   pvfl_ctx* c = p->ctx;
   const size_t Q = (size_t)(p->lv + 1) * c->N;
+  double* ws;
+  pvfl_status st = ctx_scratch(c, rot_scratch_doubles(c, p->lv) * sizeof(double), &ws);
+  if (st != PVFL_OK) return st;
+  double* src = ct;
+  double* dst = tmp;
   for (int k : p->ras_rots) {
-    pvfl_status st = pvfl_rotate(c, keys, p->lv, ct, galois_rotl(k, c->N), 0, tmp, stream);
-    if (st != PVFL_OK) return st;
-    HIP_TRY(launch_ct_add(launch_ctx(c, stream), ct, tmp, p->lv, c->N, ct));
+    const RotJob job{src, dst, k % (c->N / 2)};
+    if ((st = run_rotations(c, keys, p->lv, &job, 1, true, true, ws, 1, nullptr, stream)) != PVFL_OK) return st;
+    std::swap(src, dst);
   }
-  (void)Q;
+  if (src != ct) HIP_TRY(hipMemcpyAsync(ct, src, 2 * Q * sizeof(double), hipMemcpyDeviceToDevice, (hipStream_t)stream));
   return PVFL_OK;
 }
 
 // ---------------------------------------------------------------------------
-// ROW (Sec. 3.1)
+// ROW (Sec. 3.1): the rows are independent until the final sum, so every step
+// (product and rescale, each rotate-and-sum rotation, indicator and rescale,
+// placement) is run for many rows side by side.
 // ---------------------------------------------------------------------------
 static pvfl_status run_row(const pvfl_plan* p, const double* ct, const double* pts, const pvfl_rotkeys* keys,
                            double* out, double* ws, void* stream) {
   pvfl_ctx* c = p->ctx;
-  const int N = c->N, lv = p->lv;
+  const int N = c->N, lv = p->lv, m = p->info.m, half = N / 2;
   const size_t Q2 = (size_t)(lv + 1) * N, Q1 = (size_t)lv * N, Q0 = (size_t)(lv - 1) * N;
-  double* t2 = ws;              // product at lv
-  double* t1 = t2 + 2 * Q2;     // after the first rescale (lv - 1)
-  double* r1 = t1 + 2 * Q2;     // rotation temporary
-  double* t0 = r1 + 2 * Q2;     // after the indicator rescale (lv - 2)
+  // one row: t1 and its rotate-and-sum partner at lv - 1; the indicator's
+  // product t0 and its placement at lv - 2; the rotations' scratch
+  const size_t bufs = 4 * Q1 + 4 * Q0, rot = rot_scratch_doubles(c, lv - 1);
+  double* base;
+  int rows;
+  pvfl_status st = ctx_rot_scratch(c, bufs + rot, std::min(m, kRotsPerLaunch), stream, &base, &rows);
+  if (st != PVFL_OK) return st;
+  double* scratch = base ? base + (size_t)rows * bufs : nullptr;
+  if (rows == 0) {  // one row at a time: its buffers fit the caller's workspace
+    rows = 1;
+    base = ws;
+    if ((st = ctx_scratch(c, rot * sizeof(double), &scratch)) != PVFL_OK) return st;
+  }
+  double* ta = base;                            // [rows][2][lv][N]
+  double* tb = ta + (size_t)rows * 2 * Q1;      // [rows][2][lv][N]
+  double* t0 = tb + (size_t)rows * 2 * Q1;      // [rows][2][lv-1][N]
+  double* r0 = t0 + (size_t)rows * 2 * Q0;      // [rows][2][lv-1][N]
   LaunchCtx L = launch_ctx(c, stream);
-  const int m = p->info.m;
-  const double* ind = pts + (size_t)m * Q2;  // indicator plaintext (level lv - 1 limbs used)
-  HIP_TRY(launch_fill_zero(L, out, 2 * Q0));
-  pvfl_status st;
-  for (int r = 0; r < m; ++r) {
-    HIP_TRY(launch_ct_mul_pt(L, ct, pts + (size_t)r * Q2, lv, N, t2));
-    HIP_TRY(launch_rescale(L, t2, 2, lv, c->rescale[lv], t1));
+  const double* ind = pts + (size_t)m * Q2;  // stored with lv+1 limbs; its first lv are used
+  std::vector<RotJob> jobs(rows);
+  for (int b = 0; b < m; b += rows) {
+    const int cnt = std::min(rows, m - b);
+    HIP_TRY(launch_rescale(L, ct, 2 * cnt, lv, c->rescale[lv], ta, 0, pts + (size_t)b * Q2, Q2));
+    double* src = ta;
+    double* dst = tb;
     for (int k : p->ras_rots) {
-      if ((st = pvfl_rotate(c, keys, lv - 1, t1, galois_rotl(k, N), 0, r1, stream)) != PVFL_OK) return st;
-      HIP_TRY(launch_ct_add(L, t1, r1, lv - 1, N, t1));
+      for (int u = 0; u < cnt; ++u) jobs[u] = RotJob{src + (size_t)u * 2 * Q1, dst + (size_t)u * 2 * Q1, k % half};
+      if ((st = run_rotations(c, keys, lv - 1, jobs.data(), cnt, true, true, scratch, rows, nullptr, stream)) != PVFL_OK)
+        return st;
+      std::swap(src, dst);
     }
-    // the indicator plaintext is stored with lv+1 limbs; its first lv are used here
-    HIP_TRY(launch_ct_mul_pt(L, t1, ind, lv - 1, N, r1));
-    HIP_TRY(launch_rescale(L, r1, 2, lv - 1, c->rescale[lv - 1], t0));
-    if (r > 0) {
-      if ((st = pvfl_rotate(c, keys, lv - 2, t0, galois_rotl(-r, N), 0, r1, stream)) != PVFL_OK) return st;
-      HIP_TRY(launch_ct_add(L, out, r1, lv - 2, N, out));
-    } else {
-      HIP_TRY(launch_ct_add(L, out, t0, lv - 2, N, out));
+    HIP_TRY(launch_rescale(L, src, 2 * cnt, lv - 1, c->rescale[lv - 1], t0, 2 * Q1, ind, 0));
+    const int first = b == 0 ? 1 : 0;  // row 0 stays in place
+    if (first) HIP_TRY(launch_sum_cts(L, t0, 0, nullptr, 0, 1, lv - 2, N, false, out));
+    for (int u = first; u < cnt; ++u) jobs[u] = RotJob{t0 + (size_t)u * 2 * Q0, r0 + (size_t)u * 2 * Q0, (half - b - u) & (half - 1)};
+    if (cnt > first) {
+      if ((st = run_rotations(c, keys, lv - 2, jobs.data() + first, cnt - first, true, false, scratch, rows, nullptr, stream)) !=
+          PVFL_OK)
+        return st;
+      HIP_TRY(launch_sum_cts(L, r0 + (size_t)first * 2 * Q0, 2 * Q0, nullptr, 0, cnt - first, lv - 2, N, true, out));
     }
   }
-  (void)Q1;
   return PVFL_OK;
 }
 
@@ -574,7 +614,7 @@ extern "C" pvfl_status pvfl_matmul_ct_pt(const pvfl_plan* p, const void* ct_v, c
     case PVFL_PLAN_HYBRID:
     case PVFL_PLAN_DIAG: {
       st = p->opts.lazy_moddown ? run_diag_lazy(p, 1, &ct, &pt, keys, out, ws, stream)
-                                : run_diag_eager(p, ct, pt, keys, out, ws, stream);
+                                : run_diag_eager(p, ct, pt, keys, out, ws, ws_bytes, stream);
       if (st != PVFL_OK) return st;
       if (p->opts.kind == PVFL_PLAN_DIAG && !p->ras_rots.empty()) {
         const size_t Q = (size_t)(p->lv + 1) * p->ctx->N;
@@ -652,7 +692,7 @@ extern "C" pvfl_status pvfl_matmul_ct_pt_noalloc(const pvfl_plan* p, const void*
     case PVFL_PLAN_HYBRID:
     case PVFL_PLAN_DIAG:
       st = p->opts.lazy_moddown ? run_diag_lazy(p, 1, &ct, &pt, keys, out, ws, stream)
-                                : run_diag_eager(p, ct, pt, keys, out, ws, stream);
+                                : run_diag_eager(p, ct, pt, keys, out, ws, kNoAllocBytes, stream);
       break;
     default: {
       LaunchCtx L = launch_ctx(p->ctx, stream);
@@ -736,18 +776,26 @@ extern "C" pvfl_status pvfl_ctmat_transpose(const pvfl_plan* p, const void* ct_i
   if (st != PVFL_OK) return st;
   if (ct_in == ct_out) return fail(PVFL_E_INVALID, "the conversion cannot run in place");
   pvfl_ctx* c = p->ctx;
-  const size_t Q = (size_t)(p->lv + 1) * c->N;
+  const size_t Q = (size_t)(p->lv + 1) * c->N, per = rot_scratch_doubles(c, p->lv);
+  std::vector<RotJob> jobs;
   for (int i = 0; i < p->info.mprime; ++i) {
     int k, r;
     transpose_step(p, i, &k, &r);
     const double* src = (const double*)ct_in + (size_t)k * 2 * Q;
     double* dst = (double*)ct_out + (size_t)i * 2 * Q;
-    if (r == 0) {
+    if (r == 0)
       HIP_TRY(hipMemcpyAsync(dst, src, 2 * Q * sizeof(double), hipMemcpyDeviceToDevice, (hipStream_t)stream));
-    } else {
-      if (!keys) return fail(PVFL_E_NOKEY, "the conversion needs rotation keys");
-      if ((st = pvfl_rotate(c, keys, p->lv, src, galois_rotl(r, c->N), 0, dst, stream)) != PVFL_OK) return st;
-    }
+    else
+      jobs.push_back(RotJob{src, dst, r % (c->N / 2)});
   }
-  return PVFL_OK;
+  if (jobs.empty()) return PVFL_OK;
+  if (!keys) return fail(PVFL_E_NOKEY, "the conversion needs rotation keys");
+  double* scratch;
+  int at_once;
+  if ((st = ctx_rot_scratch(c, per, (int)jobs.size(), stream, &scratch, &at_once)) != PVFL_OK) return st;
+  if (at_once == 0) {
+    at_once = 1;
+    if ((st = ctx_scratch(c, per * sizeof(double), &scratch)) != PVFL_OK) return st;
+  }
+  return run_rotations(c, keys, p->lv, jobs.data(), (int)jobs.size(), true, false, scratch, at_once, nullptr, stream);
 }
