@@ -325,7 +325,8 @@ pvfl_status pvfl_ct_add(pvfl_ctx* ctx, int32_t level, const void* a_dev, const v
 typedef struct {
   int32_t group;        /* products sharing one key stream per work item: 1, 2 or 4 */
   int32_t chunk;        /* diagonals per work item (one partial sum each), 1..1024 */
-  int32_t vec;          /* evaluation indices per thread: 1 or 2 */
+  int32_t vec;          /* 1, or 2: twice `group` products share the key stream, where they are at most four and
+                            their staged windows fit */
   int32_t chunk_major;  /* 1: work items ordered by diagonal chunk first, so that work items
                            running together share rotation-key lines in L2; 0: product-major */
 } pvfl_batch_opts;

@@ -27,8 +27,9 @@ EncodeArgs geometry_of(const pvfl_plan* p, const double* X, int64_t ld);  // cod
 struct pvfl_batch {
   pvfl_ctx* ctx = nullptr;
   const pvfl_rotkeys* keys = nullptr;
-  int count = 0, pg = 4, CH = 64, vec = 1, lv = 0, K = 0, beta = 0, max_rows = 0;
+  int count = 0, pg = 4, CH = 64, lv = 0, K = 0, beta = 0, max_rows = 0;
   int n_enc_work = 0, n_work = 0, n_slots = 0;
+  size_t lds_asked = 0;  // stage of `group` products at 256 * vec indices: the options' limit
   double inv_scale = 1.0;
   // every device pointer below lies in the caller's workspace
   BatchProd* prods = nullptr;
@@ -82,6 +83,16 @@ pvfl_status read_opts(const pvfl_batch_opts* opts, BatchOpts* o) {
   return PVFL_OK;
 }
 
+// Products that share one key stream in the fused kernel: group * vec of them,
+// up to four, where their staged windows fit the LDS beside each other.  Two
+// indices of two products per thread read every key byte twice as often as
+// one index of four (64 products at N = 2^14: 3.83 against 3.48 ms).
+int products_per_item(const BatchOpts& o, int beta) {
+  const int both = o.group * o.vec;
+  const size_t lds = sizeof(double) * (size_t)both * (beta + 1) * (256 + std::max(o.chunk, kDiagFixedChunk));
+  return both <= 4 && lds <= kDiagMaxLds ? both : o.group;
+}
+
 // the plans a batch accepts: lazy, hoisted HYBRID (or DIAG without in-ciphertext
 // RaS) plans of one context, level and plaintext scale, one input and one output
 pvfl_status check_plans(pvfl_ctx* c, int count, const pvfl_plan* const* plans) {
@@ -114,15 +125,16 @@ struct Schedule {
   int max_mp = 0;
 };
 
-Schedule make_schedule(const std::vector<int>& mprime, int K, int N, const BatchOpts& o) {
+Schedule make_schedule(const std::vector<int>& mprime, int K, int N, int beta, const BatchOpts& o) {
   Schedule S;
+  const int group = products_per_item(o, beta);
   const int count = (int)mprime.size();
   std::vector<int> order(count);
   std::iota(order.begin(), order.end(), 0);
   std::stable_sort(order.begin(), order.end(), [&](int a, int z) { return mprime[a] > mprime[z]; });
-  for (int g0 = 0; g0 < count; g0 += o.group) {
+  for (int g0 = 0; g0 < count; g0 += group) {
     DiagGroup G{};
-    G.np = std::min(o.group, count - g0);
+    G.np = std::min(group, count - g0);
     int mx = 0;
     for (int u = 0; u < G.np; ++u) {
       G.prod[u] = order[g0 + u];
@@ -143,7 +155,7 @@ Schedule make_schedule(const std::vector<int>& mprime, int K, int N, const Batch
     std::stable_sort(S.work.begin(), S.work.end(), [](const DiagWork& a, const DiagWork& z) { return a.i0 < z.i0; });
   // task list: for each chunk (in order), tile, limb: the work items of that
   // chunk, so that consecutive tasks read the same rotation-key tile
-  const int ntile = N / (256 * o.vec);
+  const int ntile = N / 256;
   size_t w0 = 0;
   while (w0 < S.work.size()) {
     size_t w1 = w0;
@@ -231,7 +243,7 @@ extern "C" pvfl_status pvfl_batch_workspace_bytes(pvfl_ctx* c, int32_t count, co
   if (st != PVFL_OK) return st;
   if ((st = check_plans(c, count, plans)) != PVFL_OK) return st;
   const pvfl_plan* p0 = plans[0];
-  const Schedule S = make_schedule(mprimes_of(count, plans), p0->K, c->N, o);
+  const Schedule S = make_schedule(mprimes_of(count, plans), p0->K, c->N, p0->beta, o);
   *bytes = make_layout(c, count, total_pts(count, plans), S, p0->lv, p0->K, p0->beta).total;
   return PVFL_OK;
 }
@@ -252,13 +264,13 @@ extern "C" pvfl_status pvfl_batch_create(pvfl_ctx* c, int32_t count, const pvfl_
   b->ctx = c;
   b->keys = keys;
   b->count = count;
-  b->pg = o.group;
-  b->vec = o.vec;
   b->CH = o.chunk;
   const pvfl_plan* p0 = plans[0];
   b->lv = p0->lv;
   b->K = p0->K;
   b->beta = p0->beta;
+  b->pg = products_per_item(o, b->beta);
+  b->lds_asked = sizeof(double) * (size_t)o.group * (b->beta + 1) * (256 * o.vec + o.chunk + 1);
   const int N = c->N;
   std::vector<BatchProd> prods(count);
   std::vector<EncodeArgs> apt(count), act(count);
@@ -299,7 +311,7 @@ extern "C" pvfl_status pvfl_batch_create(pvfl_ctx* c, int32_t count, const pvfl_
   b->has_X = X_dev != nullptr;
   b->has_v = v_dev != nullptr;
   b->has_y = y_dev != nullptr;
-  const Schedule S = make_schedule(mprimes_of(count, plans), b->K, N, o);
+  const Schedule S = make_schedule(mprimes_of(count, plans), b->K, N, b->beta, o);
   for (int k = 0; k < count; ++k) prods[k].part0 = S.part0[k];
   b->key_bytes = S.key_reads * 8.0 * 2 * b->beta * b->K * N;
   // algorithmic minimum: every distinct rotation key of the batch streamed once
@@ -433,8 +445,9 @@ static pvfl_status batch_product(pvfl_batch* b, void* stream) {
     // writes instead are an intermediate of this kernel's own design, not counted)
     const double bytes = b->key_bytes_min + b->pt_bytes + 8.0 * (double)b->count * ((size_t)b->beta * KN + 2 * Q) +
                          8.0 * (double)b->count * 2 * KN;
+    if (b->lds_asked > kDiagMaxLds) return hip_fail(hipErrorInvalidValue, "batch options: group and chunk exceed the LDS");
     KernelTimer kt(c, stream, PVFL_TIMING_DIAG, bytes);
-    HIP_TRY(launch_diag_batch(L, a, b->pg, b->beta, b->vec));
+    HIP_TRY(launch_diag_batch(L, a, b->pg, b->beta));
     kt.stop();
   }
   HIP_TRY(launch_sum_partials_batch(L, b->part, b->prods, b->count, b->CH, K, N, lp, b->acc));

@@ -14,23 +14,50 @@ namespace pvfl {
 // ---------------------------------------------------------------------------
 // fused hoisted rotations x diagonals, lazy ModDown, shared keys.
 // Block (tile, limb r, work item w): work item = (product group, diagonals
-// [i0, i1)); the tile holds 256*V consecutive evaluation indices (one half of
-// the orbit order).  For each diagonal the key limbs (b_j, a_j)[r][t] are
-// loaded once and applied to every product of the group that has it:
+// [i0, i1)); the tile holds 256 consecutive evaluation indices (one half of
+// the orbit order), one per thread.  For each diagonal the key limbs
+// (b_j, a_j)[r][t] are loaded once and applied to every product of the group
+// that has it:
 //   acc0_p += pt_{p,i} (P phi_i(c0_p) + sum_j phi_i(D_{p,j}) b_{i,j})
 //   acc1_p += pt_{p,i} (                sum_j phi_i(D_{p,j}) a_{i,j})
 // phi_i is a shift by i inside the orbit half, so every digit (and P c0) row
 // a work item reads is the window [t0 + i0, t0 + tile + i1) of that row: it
 // is staged in LDS once and the shifted reads of the loop become LDS reads.
 // Partial sums per (product, chunk) go to part[prod.part0 + i0 / CH].
+//
+// What bounds it: per (product, diagonal, index) 49 binary64 operations, 40
+// bytes from LDS and, over PG products, 8 plaintext bytes plus 16 BETA / PG
+// key bytes through the vector cache, which takes one wave load per 16
+// cycles.  At PG = 4 the three are near balance, and the chip's clock falls to
+// 1.9 - 2.1 GHz under the load.  Four products of one index share the key
+// loads; two products of two indices (half the products per key load)
+// measured slower.  64 products at N = 2^14, BETA = 4 (15.9 GB from memory,
+// 2.6 ms at the read rate): 3.83 -> 3.48 ms; 16 products of 512 diagonals at
+// 2^15 (keys from L2, operations 4.7 ms): 8.6 -> 6.9 ms.  Tried: loads one, two
+// and three diagonals ahead of their use (3.5 - 3.8 and 6.7 - 7.6 ms), two
+// indices per thread with 16-byte loads (3.6 - 4.3 and 7.4 - 9.2 ms).
 // ---------------------------------------------------------------------------
-typedef double dbl2 __attribute__((ext_vector_type(2)));
+// Row stride of the staged windows (doubles): a compile-time constant for the
+// usual chunk lengths, so that every row of the stage is one LDS address plus
+// an immediate offset.
+template <int CHX>
+__host__ __device__ constexpr int stage_row(int ch) {
+  return 256 + (CHX ? CHX : ch);
+}
 
+// A row address that is the same for the whole workgroup, kept in scalar
+// registers: the loads take it as their base and share one 32-bit thread
+// offset, instead of a 64-bit vector addition per row.
+__device__ __forceinline__ const __attribute__((address_space(1))) double* scalar_base(const double* p) {
+  uint64_t x = (uint64_t)p;
+  asm("" : "+s"(x));
+  return (const __attribute__((address_space(1))) double*)x;
+}
 
-template <int PG, int BETA, int V>
+template <int PG, int BETA, int CHX>
 __global__ __launch_bounds__(256) void k_diag_batch(BatchDiagArgs a) {
   extern __shared__ double stage[];  // [PG][BETA + 1][win]
-  constexpr int TILE = 256 * V;
+  constexpr int TILE = 256;
   // Workgroups are dispatched round-robin over the 8 XCDs; give each XCD a
   // contiguous range of the task list so that tasks sharing a key tile (same
   // chunk, tile and limb, different product groups) run on one L2.
@@ -43,55 +70,61 @@ __global__ __launch_bounds__(256) void k_diag_batch(BatchDiagArgs a) {
   const DiagGroup& G = a.groups[w.grp];
   const int N = a.N, half = N >> 1, K = a.K;
   const int t0 = task.tile * TILE;
-  const int tl = threadIdx.x * V;        // first local index of this thread
+  const unsigned tl = threadIdx.x;
   const size_t limbN = (size_t)r * N;
   const int pi = a.limb_prime[r];
   const int klimb = a.key_limb[r];
   const bool isq = r <= a.lv;
   const ModQ m = a.mods[pi];
   const int np = G.np;
-  // Staged row layout.  With V = 2 a thread reads elements 2 tid + s and
-  // 2 tid + s + 1: stride 2 across the wave, two lanes on every LDS bank.
-  // The rows hold even and odd elements in separate halves instead (element
-  // x at (x & 1) hw + x / 2), so every read of the loop is stride 1.
-  const int hw = (TILE + a.CH + 1) / 2;
-  const int win = V == 2 ? 2 * hw : TILE + a.CH;  // row stride (doubles)
-  auto spos = [&](int x) { return V == 2 ? (x & 1) * hw + (x >> 1) : x; };
+  const int win = stage_row<CHX>(a.CH);
   const int span = TILE + (w.i1 - w.i0);
   const size_t KN = (size_t)K * N;
   const size_t Qoff = (size_t)(a.lv + 1) * N;
-  // stage the digit rows (and P c0 for the Q limbs) of every product
-  for (int p = 0; p < np; ++p) {
-    const int prod = G.prod[p];
-    const double* dig = a.digits + (size_t)prod * a.dig_stride + limbN;
-    const double* pc = a.pc + (size_t)prod * a.pc_stride + limbN;
-    for (int j = 0; j <= BETA; ++j) {
-      if (j == BETA && !isq) break;
-      const double* src = (j < BETA) ? dig + (size_t)j * KN : pc;
-      double* dst = stage + (size_t)(p * (BETA + 1) + j) * win;
-      for (int x = threadIdx.x; x < span; x += 256)  // read once per task: streamed past L2 as well
-        dst[spos(x)] = __builtin_nontemporal_load(gmem(src) + ((t0 & half) | ((t0 + w.i0 + x) & (half - 1))));
+  // Stage the digit rows and P c0 (zero on the special limbs) of every
+  // product: all of a thread's loads are issued before any is stored, so that
+  // a task waits once for its windows and not once per row.
+  for (int x = (int)tl; x < span; x += TILE) {
+    const size_t at = (size_t)((t0 & half) | ((t0 + w.i0 + x) & (half - 1)));
+    double v[PG][BETA + 1];
+#pragma unroll
+    for (int p = 0; p < PG; ++p) {
+      const int prod = G.prod[p < np ? p : 0];
+      const double* dig = a.digits + (size_t)prod * a.dig_stride + limbN;
+      // read once per task: streamed past L2 as well
+#pragma unroll
+      for (int j = 0; j < BETA; ++j) v[p][j] = __builtin_nontemporal_load(gmem(dig + (size_t)j * KN) + at);
+      v[p][BETA] = isq ? __builtin_nontemporal_load(gmem(a.pc + (size_t)prod * a.pc_stride + limbN) + at) : 0.0;
     }
+#pragma unroll
+    for (int p = 0; p < PG; ++p)
+#pragma unroll
+      for (int j = 0; j <= BETA; ++j) stage[(size_t)(p * (BETA + 1) + j) * win + x] = v[p][j];
   }
   __syncthreads();
   int mp[PG];
   const double* ptp[PG];
 #pragma unroll
   for (int p = 0; p < PG; ++p) {
-    if (p < np) {
-      const BatchProd& B = a.prods[G.prod[p]];
-      mp[p] = B.mprime;
-      ptp[p] = B.pt + limbN + t0 + tl;
-    } else {
-      mp[p] = 0;
-      ptp[p] = nullptr;
-    }
+    const BatchProd& B = a.prods[G.prod[p < np ? p : 0]];
+    mp[p] = p < np ? B.mprime : 0;
+    ptp[p] = B.pt + limbN + t0;
   }
-  double acc0[PG][V], acc1[PG][V];
+  int mp_all = mp[0];
 #pragma unroll
-  for (int p = 0; p < PG; ++p)
+  for (int p = 1; p < PG; ++p) mp_all = min(mp_all, mp[p]);
+  // Exact sums of products (fp64_mod.hpp).  Bounds with B = 2^b > q, b <= 48:
+  // keys and converted digits are centred, a digit's own limb is below q, so
+  // |sum_j D_j key_j| <= 1.25 B^2 < 0.43 * 2^(2b + 2) (BETA <= 4) and its fold
+  // is below 1.5 B, 2 B with P c0.  Plaintexts are below q: nine terms stay
+  // below 18 B^2 < 0.43 * 2^(2b + 6), their rounding errors below 9 * 2^49.
+  const double cin = acc_offset(m.q, 2), cout = acc_offset(m.q, 6);
+  double hi0[PG], lo0[PG], hi1[PG], lo1[PG];
 #pragma unroll
-    for (int v = 0; v < V; ++v) acc0[p][v] = acc1[p][v] = 0.0;
+  for (int p = 0; p < PG; ++p) {
+    hi0[p] = hi1[p] = cout;
+    lo0[p] = lo1[p] = 0.0;
+  }
   int cnt = 0;
   int i = w.i0;
   if (i == 0) {  // diagonal 0: no rotation; P c0 on the Q limbs
@@ -100,131 +133,76 @@ __global__ __launch_bounds__(256) void k_diag_batch(BatchDiagArgs a) {
       for (int p = 0; p < PG; ++p) {
         if (p >= np) continue;
         const double* pcs = stage + (size_t)(p * (BETA + 1) + BETA) * win;
-#pragma unroll
-        for (int v = 0; v < V; ++v) {
-          const double pv = gmem(ptp[p])[v];
-          acc0[p][v] += mulmod(pv, pcs[spos(tl + v)], m);
-          acc1[p][v] += mulmod(pv, gmem(a.pc)[(size_t)G.prod[p] * a.pc_stride + Qoff + limbN + t0 + tl + v], m);
-        }
+        const double pv = gmem(ptp[p])[tl];
+        acc_mac(pv, pcs[tl], hi0[p], lo0[p]);
+        acc_mac(pv, gmem(a.pc)[(size_t)G.prod[p] * a.pc_stride + Qoff + limbN + t0 + tl], hi1[p], lo1[p]);
       }
     }
     ++i;
     ++cnt;
   }
-  // key limbs (b_j, a_j) of rotation i at this thread's V indices
-  // the key of rotation ii sits at slot slot_of_rot[ii] of the key set; the
-  // loops read those slots one step ahead, so that no scalar-load wait stands
-  // between a step's compute and the next step's loads
-  auto slot_of = [&](int ii) { return a.slot_of_rot[min(ii, w.i1 - 1)]; };
-  auto load_keys = [&](int slot, double (&kb)[BETA][V], double (&ka)[BETA][V]) {
-    const auto* key = gmem(a.keys) + (size_t)slot * a.key_stride + (size_t)klimb * N + t0 + tl;
+  // The slots of a chunk of at most 64 diagonals sit in one register across
+  // the wave: a scalar load per diagonal would have to be waited for together
+  // with the LDS reads.
+  const int lane_slot = CHX && a.slot_of_rot ? a.slot_of_rot[min(w.i0 + (int)(tl & 63u), w.i1 - 1)] : 0;
+  for (; i < w.i1; ++i) {
+    // key limbs (b_j, a_j) of rotation i, whose key sits at this slot of the key set
+    const int slot = CHX ? __builtin_amdgcn_readlane(lane_slot, i - w.i0) : a.slot_of_rot[i];
+    const double* key = a.keys + (size_t)slot * a.key_stride + (size_t)klimb * N + t0;
+    double kb[BETA], ka[BETA], pv[PG];
 #pragma unroll
     for (int j = 0; j < BETA; ++j) {
-      if (V == 2) {
-        const dbl2 b2 = *(const __attribute__((address_space(1))) dbl2*)(key + (size_t)j * 2 * a.key_limbs * N);
-        const dbl2 a2 = *(const __attribute__((address_space(1))) dbl2*)(key + (size_t)(j * 2 + 1) * a.key_limbs * N);
-        kb[j][0] = b2.x; kb[j][V - 1] = b2.y;
-        ka[j][0] = a2.x; ka[j][V - 1] = a2.y;
-      } else {
-        kb[j][0] = key[(size_t)j * 2 * a.key_limbs * N];
-        ka[j][0] = key[(size_t)(j * 2 + 1) * a.key_limbs * N];
-      }
+      kb[j] = scalar_base(key + (size_t)(2 * j) * a.key_limbs * N)[tl];
+      ka[j] = scalar_base(key + (size_t)(2 * j + 1) * a.key_limbs * N)[tl];
     }
-  };
-  // plaintext values of diagonal i for every product of the group.  A
-  // product without diagonal i (or an empty group slot) reads a row it has
-  // and contributes zero, so the loads are unconditional and the two
-  // diagonals' loads below can all be in flight together.  Plaintexts are
-  // read once: stream them past L2 so that they do not evict the key tile
-  // the other product groups of this chunk still need.
-  auto load_pt = [&](int ii, double (&pv)[PG][V]) {
+    // Plaintexts of diagonal i (row 0 for a product without it, so that the
+    // loads are unconditional).  They are read once: streamed past L2, so that
+    // they do not evict the key tile the other product groups still need.
 #pragma unroll
-    for (int p = 0; p < PG; ++p) {
-      const bool has = p < np && ii < mp[p];
-      const double* src = ptp[p < np ? p : 0] + (size_t)(has ? ii : 0) * KN;
-      if (V == 2) {
-        const dbl2 p2 = __builtin_nontemporal_load(gmem((const dbl2*)src));
-        pv[p][0] = has ? p2.x : 0.0;
-        pv[p][V - 1] = has ? p2.y : 0.0;
-      } else {
-        const double x = __builtin_nontemporal_load(gmem(src));
-        pv[p][0] = has ? x : 0.0;
+    for (int p = 0; p < PG; ++p)
+      pv[p] = __builtin_nontemporal_load(scalar_base(ptp[p] + (size_t)(i < mp[p] ? i : 0) * KN) + tl);
+    const double* st = stage + (tl + (unsigned)(i - w.i0));
+    auto term = [&](int p) {
+      const double d0 = st[(p * (BETA + 1)) * win];
+      double h0, l0, h1, l1;
+      acc_first(d0, kb[0], cin, h0, l0);
+      acc_first(d0, ka[0], cin, h1, l1);
+#pragma unroll
+      for (int j = 1; j < BETA; ++j) {
+        const double dj = st[(p * (BETA + 1) + j) * win];
+        acc_mac(dj, kb[j], h0, l0);
+        acc_mac(dj, ka[j], h1, l1);
       }
-    }
-  };
-  auto apply = [&](int ii, const double (&kb)[BETA][V], const double (&ka)[BETA][V], const double (&pv)[PG][V]) {
-    const int sh = ii - w.i0;  // shift of diagonal ii inside the window
+      l0 += st[(p * (BETA + 1) + BETA) * win];
+      acc_mac(pv[p], acc_fold(h0, l0, m), hi0[p], lo0[p]);
+      acc_mac(pv[p], acc_fold(h1, l1, m), hi1[p], lo1[p]);
+    };
+    if (i < mp_all) {  // every product: one block without branches
 #pragma unroll
-    for (int p = 0; p < PG; ++p) {
-      const double* st = stage + (size_t)(p * (BETA + 1)) * win;
-#pragma unroll
-      for (int v = 0; v < V; ++v) {
-        // spos(tl + sh + v), written out with tl = 2 tid for V = 2
-        const int pos = V == 2 ? ((sh + v) & 1) * hw + (int)threadIdx.x + ((sh + v) >> 1) : tl + sh + v;
-        // the sums start from their first term (adding it to 0.0 would cost an instruction)
-        const double d0 = st[pos];
-        double u0 = mulmod(d0, kb[0][v], m), u1 = mulmod(d0, ka[0][v], m);
-#pragma unroll
-        for (int j = 1; j < BETA; ++j) {
-          const double d = st[(size_t)j * win + pos];
-          u0 += mulmod(d, kb[j][v], m);
-          u1 += mulmod(d, ka[j][v], m);
-        }
-        if (isq) u0 += st[(size_t)BETA * win + pos];
-        acc0[p][v] += mulmod(pv[p][v], u0, m);
-        acc1[p][v] += mulmod(pv[p][v], u1, m);
-      }
-    }
-  };
-  // re-centre after 8 (9 in the chunk holding diagonal 0) terms of |r| < q:
-  // |acc| < 9.5 q < 2^52, the range reduce() takes
-  auto settle = [&]() {
-    if (cnt >= 8) {
+      for (int p = 0; p < PG; ++p) term(p);
+    } else {
 #pragma unroll
       for (int p = 0; p < PG; ++p)
+        if (i < mp[p]) term(p);
+    }
+    if (++cnt >= 8) {  // fold the sums after 8 (9 in the chunk holding diagonal 0) terms
 #pragma unroll
-        for (int v = 0; v < V; ++v) {
-          acc0[p][v] = reduce(acc0[p][v], m);
-          acc1[p][v] = reduce(acc1[p][v], m);
-        }
+      for (int p = 0; p < PG; ++p) {
+        lo0[p] = reduce(acc_fold(hi0[p], lo0[p], m), m);
+        lo1[p] = reduce(acc_fold(hi1[p], lo1[p], m), m);
+        hi0[p] = hi1[p] = cout;
+      }
       cnt = 0;
     }
-  };
-  // (a chunk with no rotated diagonal may come with no key set at all)
-  int sl0 = i < w.i1 ? slot_of(i) : 0, sl1 = i + 1 < w.i1 ? slot_of(i + 1) : 0;
-  // two diagonals per step: both diagonals' key and plaintext loads are
-  // issued before either is used, which doubles the memory requests each
-  // wave has in flight (the LDS stage already limits occupancy to three
-  // waves per SIMD, which leaves the registers for this)
-  for (; i + 1 < w.i1; i += 2) {
-    double kb0[BETA][V], ka0[BETA][V], kb1[BETA][V], ka1[BETA][V], pv0[PG][V], pv1[PG][V];
-    load_keys(sl0, kb0, ka0);
-    load_pt(i, pv0);
-    load_keys(sl1, kb1, ka1);
-    load_pt(i + 1, pv1);
-    sl0 = slot_of(i + 2);
-    sl1 = slot_of(i + 3);
-    apply(i, kb0, ka0, pv0);
-    apply(i + 1, kb1, ka1, pv1);
-    cnt += 2;
-    settle();
-  }
-  if (i < w.i1) {
-    double kb0[BETA][V], ka0[BETA][V], pv0[PG][V];
-    load_keys(sl0, kb0, ka0);
-    load_pt(i, pv0);
-    apply(i, kb0, ka0, pv0);
   }
   const int chunk = w.i0 / a.CH;
 #pragma unroll
   for (int p = 0; p < PG; ++p) {
     if (p >= np || w.i0 >= mp[p]) continue;
     double* part = a.part + (size_t)(a.prods[G.prod[p]].part0 + chunk) * 2 * KN + limbN + t0 + tl;
-#pragma unroll
-    for (int v = 0; v < V; ++v) {  // summed by a later launch: keep them out of L2
-      __builtin_nontemporal_store(reduce(acc0[p][v], m), part + v);
-      __builtin_nontemporal_store(reduce(acc1[p][v], m), part + KN + v);
-    }
+    // summed by a later launch: keep them out of L2
+    __builtin_nontemporal_store(reduce(acc_fold(hi0[p], lo0[p], m), m), part);
+    __builtin_nontemporal_store(reduce(acc_fold(hi1[p], lo1[p], m), m), part + KN);
   }
 }
 
@@ -348,57 +326,38 @@ __global__ __launch_bounds__(NttShape<LOGN>::T) void k_decode_readout_batch(cons
     default: return hipErrorInvalidValue;                 \
   }
 
-template <int PG, int V>
-static hipError_t diag_batch_pgv(const LaunchCtx& L, const BatchDiagArgs& a, int beta) {
-  const dim3 grid(8 * a.per_xcd);
-  const size_t lds = sizeof(double) * (size_t)PG * (beta + 1) * (256 * V + a.CH + 1);  // row stride <= win + 1
-  if (lds > 160 * 1024) return hipErrorInvalidValue;
-  switch (beta) {
-    case 1: hipLaunchKernelGGL((k_diag_batch<PG, 1, V>), grid, dim3(256), lds, L.stream, a); break;
-    case 2: hipLaunchKernelGGL((k_diag_batch<PG, 2, V>), grid, dim3(256), lds, L.stream, a); break;
-    case 3: hipLaunchKernelGGL((k_diag_batch<PG, 3, V>), grid, dim3(256), lds, L.stream, a); break;
-    case 4: hipLaunchKernelGGL((k_diag_batch<PG, 4, V>), grid, dim3(256), lds, L.stream, a); break;
-    default: return hipErrorInvalidValue;
-  }
+template <int PG, int BETA, int CHX>
+static hipError_t diag_batch_run(const LaunchCtx& L, const BatchDiagArgs& a) {
+  const size_t lds = sizeof(double) * (size_t)PG * (BETA + 1) * stage_row<CHX>(a.CH);
+  if (lds > kDiagMaxLds) return hipErrorInvalidValue;
+  // dynamic LDS above the default limit must be opted in once per kernel instance
+  static const hipError_t opt_in = hipFuncSetAttribute((const void*)k_diag_batch<PG, BETA, CHX>,
+                                                       hipFuncAttributeMaxDynamicSharedMemorySize, (int)kDiagMaxLds);
+  if (opt_in != hipSuccess) return opt_in;
+  hipLaunchKernelGGL((k_diag_batch<PG, BETA, CHX>), dim3(8 * a.per_xcd), dim3(256), lds, L.stream, a);
   return hipGetLastError();
 }
-
-// dynamic LDS above the default limit must be opted in per kernel instance
-template <int PG, int V>
-static hipError_t diag_batch_allow_lds() {
-  const int bytes = 160 * 1024;
-  const void* fn[4] = {(const void*)k_diag_batch<PG, 1, V>, (const void*)k_diag_batch<PG, 2, V>,
-                       (const void*)k_diag_batch<PG, 3, V>, (const void*)k_diag_batch<PG, 4, V>};
-  for (const void* f : fn) {
-    const hipError_t e = hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, bytes);
-    if (e != hipSuccess) return e;
+template <int PG, int BETA>
+static hipError_t diag_batch_ch(const LaunchCtx& L, const BatchDiagArgs& a) {
+  return a.CH <= kDiagFixedChunk ? diag_batch_run<PG, BETA, kDiagFixedChunk>(L, a) : diag_batch_run<PG, BETA, 0>(L, a);
+}
+template <int PG>
+static hipError_t diag_batch_pg(const LaunchCtx& L, const BatchDiagArgs& a, int beta) {
+  switch (beta) {
+    case 1: return diag_batch_ch<PG, 1>(L, a);
+    case 2: return diag_batch_ch<PG, 2>(L, a);
+    case 3: return diag_batch_ch<PG, 3>(L, a);
+    case 4: return diag_batch_ch<PG, 4>(L, a);
   }
-  return hipSuccess;
+  return hipErrorInvalidValue;
 }
 
-hipError_t launch_diag_batch(const LaunchCtx& L, const BatchDiagArgs& a, int pg, int beta, int vec) {
+hipError_t launch_diag_batch(const LaunchCtx& L, const BatchDiagArgs& a, int pg, int beta) {
   if (a.n_tasks <= 0) return hipSuccess;
-  static bool lds_opt_in = false;
-  if (!lds_opt_in) {
-    const hipError_t e[6] = {diag_batch_allow_lds<1, 1>(), diag_batch_allow_lds<2, 1>(), diag_batch_allow_lds<4, 1>(),
-                             diag_batch_allow_lds<1, 2>(), diag_batch_allow_lds<2, 2>(), diag_batch_allow_lds<4, 2>()};
-    for (hipError_t x : e)
-      if (x != hipSuccess) return x;
-    lds_opt_in = true;
-  }
-  if (a.N % (256 * vec) != 0) return hipErrorInvalidValue;
-  if (vec == 1) {
-    switch (pg) {
-      case 1: return diag_batch_pgv<1, 1>(L, a, beta);
-      case 2: return diag_batch_pgv<2, 1>(L, a, beta);
-      case 4: return diag_batch_pgv<4, 1>(L, a, beta);
-    }
-  } else if (vec == 2) {
-    switch (pg) {
-      case 1: return diag_batch_pgv<1, 2>(L, a, beta);
-      case 2: return diag_batch_pgv<2, 2>(L, a, beta);
-      case 4: return diag_batch_pgv<4, 2>(L, a, beta);
-    }
+  switch (pg) {
+    case 1: return diag_batch_pg<1>(L, a, beta);
+    case 2: return diag_batch_pg<2>(L, a, beta);
+    case 4: return diag_batch_pg<4>(L, a, beta);
   }
   return hipErrorInvalidValue;
 }

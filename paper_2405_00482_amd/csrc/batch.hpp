@@ -9,6 +9,8 @@
 namespace pvfl {
 
 constexpr int kMaxGroup = 16;
+constexpr int kDiagFixedChunk = 64;           // chunks up to this length get a stage of compile-time row stride
+constexpr size_t kDiagMaxLds = 160 * 1024;
 
 struct BatchProd {
   const double* ct;   // input ciphertext [2][lv+1][N]
@@ -56,8 +58,8 @@ struct BatchDiagArgs {
   double* part;          // [slot][2][K][N]
 };
 
-// pg: products per group (1, 2, 4); vec: evaluation indices per thread (1, 2)
-hipError_t launch_diag_batch(const LaunchCtx& L, const BatchDiagArgs& a, int pg, int beta, int vec);
+// pg: products per group (1, 2, 4)
+hipError_t launch_diag_batch(const LaunchCtx& L, const BatchDiagArgs& a, int pg, int beta);
 hipError_t launch_sum_partials_batch(const LaunchCtx& L, const double* part, const BatchProd* prods, int count, int CH,
                                      int K, int N, LimbMap limb_prime, double* acc);
 hipError_t launch_encode_pt_batch(const LaunchCtx& L, const EncodeArgs* args, const int2* work, int nwork,

@@ -37,7 +37,41 @@ __device__ __forceinline__ double mulmod(double a, double b, ModQ m) {
   return r + l;
 }
 
-// centred representative, |r| <= (q+1)/2, for any integer |x| < 2^52.
+// Sums of products with one reduction.  The pair (hi, lo) holds an exact sum
+// of integer products a*b: hi lives in one binade [2^e, 2^(e+1)) around an
+// offset C that is a multiple of q, so that every product is rounded to the
+// same grid 2^(e-52),
+//   h' = fma(a, b, hi),   lo += fma(a, b, hi - h'),   hi = h'
+// where hi - h' is exact (a multiple of the grid, below 2^53 of its steps) and
+// so is the rounding error fma(a, b, hi - h') (an integer of magnitude <=
+// 2^(e-53)).  Four operations for a product and its sum instead of the seven
+// of mulmod and an addition, plus one acc_fold for the whole sum.
+// acc_offset(q, x): C for sums of magnitude below 0.43 * 2^(2b + x), where
+// 2^b is the power of two above q.  C/2^e lies in [1.43, 1.5], hence the 0.43.
+__device__ __forceinline__ double acc_offset(double q, int x) {
+  const int b = __builtin_amdgcn_frexp_exp(q);
+  int e = 2 * b + x;
+  if (e < 52) e = 52;  // the grid stays at whole numbers, so that C is a multiple of q
+  const double kappa = __builtin_trunc(6755399441055744.0 / q);  // 1.5 * 2^52 / q
+  return __builtin_ldexp(kappa * q, e - 52);
+}
+__device__ __forceinline__ void acc_first(double a, double b, double c, double& hi, double& lo) {
+  hi = __builtin_fma(a, b, c);
+  lo = __builtin_fma(a, b, c - hi);
+}
+__device__ __forceinline__ void acc_mac(double a, double b, double& hi, double& lo) {
+  const double h = __builtin_fma(a, b, hi);
+  lo += __builtin_fma(a, b, hi - h);
+  hi = h;
+}
+// hi + lo mod q.  The quotient estimate is within 0.5 + |hi/q| 2^-52 of hi/q,
+// so the result's magnitude is below (0.5 + 2^(e+1-52)/q) q + |lo|.
+__device__ __forceinline__ double acc_fold(double hi, double lo, ModQ m) {
+  const double k = __builtin_rint(hi * m.qinv);
+  return __builtin_fma(-k, m.q, hi) + lo;
+}
+
+// centred representative, |r| <= (q+1)/2, for any integer |x| < 2^53.
 __device__ __forceinline__ double reduce(double x, ModQ m) {
   double k = __builtin_rint(x * m.qinv);
   return __builtin_fma(-k, m.q, x);
