@@ -478,7 +478,7 @@ extern "C" pvfl_status pvfl_batch_decrypt(pvfl_batch* b, const pvfl_sk* sk, void
   if (c->logN <= 14) {  // the slots never leave LDS
     HIP_TRY(launch_decode_readout_batch(L, b->res, b->count, b->lv, crt, et, b->inv_scale, b->args_ct, b->prods));
   } else {
-    HIP_TRY(launch_decode(L, b->res, b->count, b->lv, crt, et, b->inv_scale, b->z));
+    HIP_TRY(launch_decode15(L, b->res, b->count, b->lv, crt, et, b->inv_scale, b->z));
     HIP_TRY(launch_readout_batch(L, b->z, b->args_ct, b->prods, b->count, b->max_rows, c->N / 2));
   }
   return PVFL_OK;

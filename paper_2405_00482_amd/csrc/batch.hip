@@ -276,16 +276,12 @@ __global__ __launch_bounds__(NttShape<LOGN>::T) void k_encode_ct_batch(const Enc
 // rotate-and-sum, added in slot order
 template <class Slot>
 __device__ __forceinline__ double readout_row(const EncodeArgs& a, int idx, Slot slot) {
-  double acc = 0.0;
   if (a.kind == 0) {
     const int rr = idx, g = rr / a.mprime, rho = rr % a.mprime;
-    for (int t2 = 0; t2 < a.bn / a.mprime; ++t2) acc += slot(g * a.bn + rho + t2 * a.mprime);
-  } else if (a.bm >= a.bn) {
-    acc = slot(idx);
-  } else {
-    for (int t2 = 0; t2 < a.bn / a.bm; ++t2) acc += slot(idx + t2 * a.bm);
+    return sum_in_order(a.bn / a.mprime, [&](int t) { return slot(g * a.bn + rho + t * a.mprime); });
   }
-  return acc;
+  if (a.bm >= a.bn) return slot(idx);
+  return sum_in_order(a.bn / a.bm, [&](int t) { return slot(idx + t * a.bm); });
 }
 
 __global__ __launch_bounds__(256) void k_readout_batch(const double* __restrict__ z, const EncodeArgs* __restrict__ args,
@@ -312,8 +308,8 @@ __global__ __launch_bounds__(NttShape<LOGN>::T) void k_decode_readout_batch(cons
   decode_to_lds<LOGN>(res + (size_t)p * (lv + 1) * N, lv + 1, ct, et, w);
   const EncodeArgs a = args[p];
   double* y = prods[p].y;
-  for (int idx = threadIdx.x; idx < a.m; idx += T)
-    y[idx] = readout_row(a, idx, [&](int j) { return decoded_slot<LOGN>(w, et, j, inv_scale); });
+  const double* z = slots_in_order<LOGN>(w, et, inv_scale);
+  for (int idx = threadIdx.x; idx < a.m; idx += T) y[idx] = readout_row(a, idx, [&](int j) { return z[j]; });
 }
 
 // ---------------------------------------------------------------------------

@@ -202,8 +202,13 @@ extern "C" pvfl_status pvfl_decrypt_decode(const pvfl_plan* p, const pvfl_sk* sk
   if ((st = ctx_scratch(c, sizeof(double) * (res_n + z_n), &scratch)) != PVFL_OK) return st;
   LaunchCtx L = launch_ctx(c, stream);
   HIP_TRY(launch_decrypt_f64(L, (const double*)ct, nct, sk->s, lv, scratch));
-  HIP_TRY(launch_decode(L, scratch, nct, lv, h->crt, h->et, std::pow(2.0, -p->info.out_log2_scale), scratch + res_n));
   EncodeArgs a = geometry_of(p, nullptr, 0);
+  const double inv_scale = std::pow(2.0, -p->info.out_log2_scale);
+  if (c->logN <= 14) {  // the slots never leave LDS
+    HIP_TRY(launch_decode_readout(L, scratch, nct, lv, h->crt, h->et, inv_scale, a, p->opts.ras_in_ct, y));
+    return PVFL_OK;
+  }
+  HIP_TRY(launch_decode15(L, scratch, nct, lv, h->crt, h->et, inv_scale, scratch + res_n));
   const int count = p->info.kind == PVFL_PLAN_CTMAT ? p->info.m * p->info.n_out : p->info.m;
   HIP_TRY(launch_readout(L, scratch + res_n, a, p->opts.ras_in_ct, count, y));
   return PVFL_OK;

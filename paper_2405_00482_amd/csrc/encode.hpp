@@ -45,8 +45,11 @@ hipError_t launch_encode_out(const LaunchCtx& L, const EncodeArgs& a, const doub
 hipError_t launch_out_add_pt(const LaunchCtx& L, const double* ct, const double* pt, double sign, int nct, int lv, int N,
                              double* out);
 hipError_t launch_encode_ct(const LaunchCtx& L, const EncodeArgs& a, const EncTabs& et, int count, int64_t* msg);
-hipError_t launch_decode(const LaunchCtx& L, const double* res, int nct, int lv, const CrtTabs& ct, const EncTabs& et,
-                         double inv_scale, double* z);
+// decode and lazy read-out of a plan's outputs (N <= 2^14); decode alone into slots z[nct][N/2] (N = 2^15)
+hipError_t launch_decode_readout(const LaunchCtx& L, const double* res, int nct, int lv, const CrtTabs& ct,
+                                 const EncTabs& et, double inv_scale, const EncodeArgs& a, int ras_in_ct, double* y);
+hipError_t launch_decode15(const LaunchCtx& L, const double* res, int nct, int lv, const CrtTabs& ct, const EncTabs& et,
+                           double inv_scale, double* z);
 hipError_t launch_readout(const LaunchCtx& L, const double* z, const EncodeArgs& a, int ras_in_ct, int count, double* y);
 
 }  // namespace pvfl

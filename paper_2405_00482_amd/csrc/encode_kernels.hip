@@ -42,28 +42,88 @@ __global__ __launch_bounds__(NttShape<LOGN>::T) void k_encode_ct_msg(EncodeArgs 
   }
 }
 
-// Decode: centred CRT lift of decrypted coefficient residues [nct][l+1][N]
-// (canonical, binary64), twist, DFT with sign +1, slots z[c][j] =
-// Re(.)/scale.
+// Output idx of a plan from its decoded slots slot(c, j) (output ciphertext
+// c, slot j): the lazy rotate-and-sum of Sec. 4.3, added in slot order.
+template <class Slot>
+__device__ __forceinline__ double readout_value(const EncodeArgs& a, int ras_in_ct, int idx, Slot slot) {
+  int c = 0, j0 = idx, step = 0, cnt = 1;
+  switch (a.kind) {
+    case 0: {
+      const int rr = idx % a.bm;
+      c = idx / a.bm;
+      j0 = (rr / a.mprime) * a.bn + rr % a.mprime;
+      step = a.mprime;
+      cnt = a.bn / a.mprime;
+      break;
+    }
+    case 1:
+      if (a.bm < a.bn && !ras_in_ct) {
+        step = a.bm;
+        cnt = a.bn / a.bm;
+      }
+      break;
+    case 3: {
+      const int col = idx % a.n_out;
+      c = col / a.pack;
+      j0 = (col % a.pack) * a.width + idx / a.n_out;
+      if (a.bm < a.bn) {
+        step = a.bm;
+        cnt = a.bn / a.bm;
+      }
+      break;
+    }
+    case 4:  // COL: row block c of N/2 rows, no rotate-and-sum
+      c = idx / a.bm;
+      j0 = idx % a.bm;
+      break;
+  }
+  if (step == 0) return slot(c, j0);
+  return sum_in_order(cnt, [&](int t) { return slot(c, j0 + t * step); });
+}
+
+// Decode and read-out of one output ciphertext per workgroup, N <= 2^14:
+// centred CRT lift of the decrypted coefficient residues [nct][l+1][N]
+// (canonical, binary64), twist, DFT with sign +1; the slots stay in LDS and
+// the outputs that this ciphertext holds are summed from them.
 template <int LOGN>
-__global__ __launch_bounds__(NttShape<LOGN>::T) void k_decode(const double* __restrict__ res, int lv, CrtTabs ct,
+__global__ __launch_bounds__(NttShape<LOGN>::T) void k_decode_readout(const double* __restrict__ res, int lv, CrtTabs ct,
+                                                                      EncTabs et, double inv_scale, EncodeArgs a,
+                                                                      int ras_in_ct, double* __restrict__ y) {
+  constexpr int N = 1 << LOGN, T = NttShape<LOGN>::T;
+  __shared__ double2 w[NttShape<LOGN>::LDS / 2];
+  const int c = blockIdx.x;
+  decode_to_lds<LOGN>(res + (size_t)c * (lv + 1) * N, lv + 1, ct, et, w);
+  const double* z = slots_in_order<LOGN>(w, et, inv_scale);
+  auto slot = [&](int, int j) { return z[j]; };
+  if (a.kind == 3) {  // the columns of this ciphertext, all rows
+    const int col0 = c * a.pack, cols = min(a.pack, a.n_out - col0);
+    for (int l = threadIdx.x; l < a.m * cols; l += T) {
+      const int idx = (l / cols) * a.n_out + col0 + l % cols;
+      y[idx] = readout_value(a, ras_in_ct, idx, slot);
+    }
+  } else {  // HYBRID and COL: row block c; DIAG and ROW have one ciphertext
+    const int per = a.kind == 0 || a.kind == 4 ? a.bm : a.m, lo = c * per, hi = min(a.m, lo + per);
+    for (int idx = lo + (int)threadIdx.x; idx < hi; idx += T) y[idx] = readout_value(a, ras_in_ct, idx, slot);
+  }
+}
+
+// Decode alone at N = 2^15: slots z[c][j] = Re(.)/scale.  The first DIF stage
+// (pairs k, k + M/2) runs in registers, then the two halves in LDS.
+__global__ __launch_bounds__(NttShape<15>::T) void k_decode15(const double* __restrict__ res, int lv, CrtTabs ct,
                                                               EncTabs et, double inv_scale, double* __restrict__ z) {
-  constexpr int N = 1 << LOGN, M = N / 2, T = NttShape<LOGN>::T;
+  constexpr int LOGN = 15, N = 1 << LOGN, M = N / 2, T = NttShape<LOGN>::T, HM = M / 2;
   __shared__ double2 w[NttShape<LOGN>::LDS / 2];
   const int c = blockIdx.x;
   const double* base = res + (size_t)c * (lv + 1) * N;
   const int nl = lv + 1;
-  auto lift = [&](int kk) { return crt_lift<0>(base, kk, N, ct, nl); };
-  // twisted w_k = (m_k + i m_(k+N/2)) zeta^k
-  auto twisted = [&](int k) { return cmul(make_double2(lift(k), lift(k + M)), et.twist[k]); };
   double* zc = z + (size_t)c * M;
-  if constexpr (LOGN <= 14) {
-    decode_to_lds<LOGN>(base, nl, ct, et, w);
-    for (int j = threadIdx.x; j < M; j += T) zc[j] = decoded_slot<LOGN>(w, et, j, inv_scale);
-  } else {
-    // first DIF stage (pairs k, k + M/2) in registers, then the two halves in LDS
-    constexpr int HM = M / 2;
-    double2 v0[HM / T];
+  double2 v0[HM / T];
+  with_limbs(nl, [&](auto nl_c) {
+    constexpr int NL = decltype(nl_c)::value;
+    // twisted w_k = (m_k + i m_(k+N/2)) zeta^k
+    auto twisted = [&](int k) {
+      return cmul(make_double2(crt_lift<NL>(base, k, N, ct, nl), crt_lift<NL>(base, k + M, N, ct, nl)), et.twist[k]);
+    };
 #pragma unroll
     for (int u = 0; u < HM / T; ++u) {
       const int k = threadIdx.x + u * T;
@@ -71,19 +131,19 @@ __global__ __launch_bounds__(NttShape<LOGN>::T) void k_decode(const double* __re
       w[cpad(k)] = make_double2(a0.x + b0.x, a0.y + b0.y);
       v0[u] = cmul(make_double2(a0.x - b0.x, a0.y - b0.y), cconj(et.fft_tw[k]));
     }
+  });
 #pragma unroll 1
-    for (int h = 0; h < 2; ++h) {
-      if (h) {
-        __syncthreads();  // half 0's read-out is done
+  for (int h = 0; h < 2; ++h) {
+    if (h) {
+      __syncthreads();  // half 0's read-out is done
 #pragma unroll
-        for (int u = 0; u < HM / T; ++u) w[cpad(threadIdx.x + u * T)] = v0[u];
-      }
-      __syncthreads();
-      fft_dif_half15(w, et.fft_tw, true);
-      for (int j = threadIdx.x; j < M; j += T) {
-        const int r = brev(et.slot2f[j], LOGN - 1);
-        if ((r >> (LOGN - 2)) == h) zc[j] = w[cpad(r - h * HM)].x * inv_scale;
-      }
+      for (int u = 0; u < HM / T; ++u) w[cpad(threadIdx.x + u * T)] = v0[u];
+    }
+    __syncthreads();
+    fft_dif_half15(w, et.fft_tw, true);
+    for (int j = threadIdx.x; j < M; j += T) {
+      const int r = brev(et.slot2f[j], LOGN - 1);
+      if ((r >> (LOGN - 2)) == h) zc[j] = w[cpad(r - h * HM)].x * inv_scale;
     }
   }
 }
@@ -167,46 +227,11 @@ __global__ __launch_bounds__(256) void k_out_add_pt(const double* __restrict__ c
 }
 
 // lazy rotate-and-sum / read-out of the decoded slots (Sec. 4.3)
-__global__ __launch_bounds__(256) void k_readout(const double* __restrict__ z, EncodeArgs a, int ras_in_ct,
+__global__ __launch_bounds__(256) void k_readout(const double* __restrict__ z, EncodeArgs a, int ras_in_ct, int count,
                                                  double* __restrict__ y) {
-  const int M = a.slots;
   const int idx = blockIdx.x * 256 + threadIdx.x;
-  switch (a.kind) {
-    case 0: {
-      if (idx >= a.m) return;
-      const int b = idx / a.bm, rr = idx % a.bm, g = rr / a.mprime, rho = rr % a.mprime;
-      const double* zb = z + (size_t)b * M;
-      double acc = 0.0;
-      for (int t = 0; t < a.bn / a.mprime; ++t) acc += zb[g * a.bn + rho + t * a.mprime];
-      y[idx] = acc;
-      return;
-    }
-    case 1: {
-      if (idx >= a.m) return;
-      if (a.bm >= a.bn || ras_in_ct) { y[idx] = z[idx]; return; }
-      double acc = 0.0;
-      for (int t = 0; t < a.bn / a.bm; ++t) acc += z[idx + t * a.bm];
-      y[idx] = acc;
-      return;
-    }
-    case 2:
-      if (idx < a.m) y[idx] = z[idx];
-      return;
-    case 4:  // COL: row block b of N/2 rows, no rotate-and-sum
-      if (idx < a.m) y[idx] = z[(size_t)(idx / a.bm) * M + idx % a.bm];
-      return;
-    case 3: {
-      if (idx >= a.m * a.n_out) return;
-      const int r = idx / a.n_out, col = idx % a.n_out;
-      const int kc = col / a.pack, blk = col % a.pack;
-      const double* zk = z + (size_t)kc * M + (size_t)blk * a.width;
-      if (a.bm >= a.bn) { y[idx] = zk[r]; return; }
-      double acc = 0.0;
-      for (int t = 0; t < a.bn / a.bm; ++t) acc += zk[r + t * a.bm];
-      y[idx] = acc;
-      return;
-    }
-  }
+  if (idx >= count) return;
+  y[idx] = readout_value(a, ras_in_ct, idx, [&](int c, int j) { return z[(size_t)c * a.slots + j]; });
 }
 
 // ---------------------------------------------------------------------------
@@ -225,9 +250,11 @@ static void encode_ct_impl(const LaunchCtx& L, const EncodeArgs& a, const EncTab
   hipLaunchKernelGGL(k_encode_ct_msg<LOGN>, dim3(count), dim3(NttShape<LOGN>::T), 0, L.stream, a, et, msg);
 }
 template <int LOGN>
-static void decode_impl(const LaunchCtx& L, const double* res, int nct, int lv, const CrtTabs& ct, const EncTabs& et,
-                        double inv_scale, double* z) {
-  hipLaunchKernelGGL(k_decode<LOGN>, dim3(nct), dim3(NttShape<LOGN>::T), 0, L.stream, res, lv, ct, et, inv_scale, z);
+static void decode_readout_impl(const LaunchCtx& L, const double* res, int nct, int lv, const CrtTabs& ct,
+                                const EncTabs& et, double inv_scale, const EncodeArgs& a, int ras_in_ct, double* y) {
+  if constexpr (LOGN <= 14)
+    hipLaunchKernelGGL(k_decode_readout<LOGN>, dim3(nct), dim3(NttShape<LOGN>::T), 0, L.stream, res, lv, ct, et, inv_scale,
+                       a, ras_in_ct, y);
 }
 
 #define DISPATCH_LOGN(L, FN, ...)                         \
@@ -249,9 +276,16 @@ hipError_t launch_encode_ct(const LaunchCtx& L, const EncodeArgs& a, const EncTa
   DISPATCH_LOGN(L, encode_ct_impl, L, a, et, count, msg);
   return hipGetLastError();
 }
-hipError_t launch_decode(const LaunchCtx& L, const double* res, int nct, int lv, const CrtTabs& ct, const EncTabs& et,
-                         double inv_scale, double* z) {
-  DISPATCH_LOGN(L, decode_impl, L, res, nct, lv, ct, et, inv_scale, z);
+hipError_t launch_decode15(const LaunchCtx& L, const double* res, int nct, int lv, const CrtTabs& ct, const EncTabs& et,
+                           double inv_scale, double* z) {
+  if (L.logN != 15) return hipErrorInvalidValue;
+  hipLaunchKernelGGL(k_decode15, dim3(nct), dim3(NttShape<15>::T), 0, L.stream, res, lv, ct, et, inv_scale, z);
+  return hipGetLastError();
+}
+hipError_t launch_decode_readout(const LaunchCtx& L, const double* res, int nct, int lv, const CrtTabs& ct,
+                                 const EncTabs& et, double inv_scale, const EncodeArgs& a, int ras_in_ct, double* y) {
+  if (L.logN > 14) return hipErrorInvalidValue;
+  DISPATCH_LOGN(L, decode_readout_impl, L, res, nct, lv, ct, et, inv_scale, a, ras_in_ct, y);
   return hipGetLastError();
 }
 hipError_t launch_encode_out(const LaunchCtx& L, const EncodeArgs& a, const double* v, int mode, int ras_in_ct,
@@ -269,7 +303,7 @@ hipError_t launch_out_add_pt(const LaunchCtx& L, const double* ct, const double*
   return hipGetLastError();
 }
 hipError_t launch_readout(const LaunchCtx& L, const double* z, const EncodeArgs& a, int ras_in_ct, int count, double* y) {
-  hipLaunchKernelGGL(k_readout, dim3((count + 255) / 256), dim3(256), 0, L.stream, z, a, ras_in_ct, y);
+  hipLaunchKernelGGL(k_readout, dim3((count + 255) / 256), dim3(256), 0, L.stream, z, a, ras_in_ct, count, y);
   return hipGetLastError();
 }
 
