@@ -167,6 +167,9 @@ void pvfl_plan_destroy(pvfl_plan* plan);
 size_t pvfl_bytes_ct_in(const pvfl_plan* plan);    /* all input ciphertexts */
 size_t pvfl_bytes_ct_out(const pvfl_plan* plan);   /* all output ciphertexts */
 size_t pvfl_bytes_pt(const pvfl_plan* plan);       /* all diagonal plaintexts */
+/* The workspace a product runs fastest with.  Plans that rotate single
+ * ciphertexts (per-rotation ModDown, giant steps) also take less, down to one
+ * rotation at a time: anything smaller is PVFL_E_SHAPE. */
 size_t pvfl_bytes_workspace(const pvfl_plan* plan);
 
 /* The hot path.
@@ -193,8 +196,8 @@ pvfl_status pvfl_matmul_ct_pt(const pvfl_plan* plan, const void* ct_dev, const v
  * streams, or host threads without ordering) race and must not be issued.
  * Plans: HYBRID, DIAG with lazy rotate-and-sum, CTMAT and COL.  Errors as
  * pvfl_matmul_ct_pt, plus PVFL_E_PLAN for ROW and in-ciphertext
- * rotate-and-sum plans and PVFL_E_SHAPE when the plan's workspace
- * (pvfl_bytes_workspace) exceeds the array, before anything is enqueued. */
+ * rotate-and-sum plans and PVFL_E_SHAPE when the plan's smallest workspace
+ * exceeds the array, before anything is enqueued. */
 pvfl_status pvfl_matmul_ct_pt_noalloc(const pvfl_plan* plan, const void* ct_dev, const void* pt_dev,
                                       const pvfl_rotkeys* keys, void* out_dev, void* stream);
 size_t pvfl_noalloc_max_bytes(void);

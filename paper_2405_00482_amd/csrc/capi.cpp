@@ -567,9 +567,20 @@ size_t rot_scratch_doubles(const pvfl_ctx* c, int lv) {
   const KsLevel& kl = c->ks_host[lv];
   return ((size_t)(lv + 1) + (size_t)kl.beta * kl.K + 2 * (size_t)c->alpha) * c->N;
 }
+// Whether n rotations side by side make their key products in a launch of
+// their own (2 K N doubles of scratch more for each) instead of inside the
+// transforms that use them.  Inside, a workgroup reads the 2 beta key and digit
+// limbs of its limb alone, at one CU's share of the bandwidth; that is hidden
+// only behind other workgroups.  While the ModDown's transforms leave CUs idle
+// (at most 256 workgroups) the launch is the shorter way: 15 giant steps at
+// 2^14, 4 + 1 primes 648 -> 588 us for the whole product, the row method's 12
+// rows at 2^13 521 -> 499 us, 186 workgroups 112.6 -> 112.1 us.  Beyond, its
+// memory traffic costs more: 63 rotations (756 workgroups) 554 -> 608 us.
+bool rot_inner_apart(int lv, int n) { return n * 2 * (lv + 1) <= 256; }
+size_t rot_inner_doubles(const pvfl_ctx* c, int lv) { return 2 * (size_t)c->ks_host[lv].K * c->N; }
 
 pvfl_status run_rotations(pvfl_ctx* c, const pvfl_rotkeys* keys, int lv, const RotJob* jobs, int n, bool pre, bool add,
-                          double* scratch, int at_once, const double* shared_digits, void* stream) {
+                          double* scratch, size_t scratch_n, int at_once, const double* shared_digits, void* stream) {
   const KsLevel& kl = c->ks_host[lv];
   const size_t N = c->N, DG = (size_t)kl.beta * kl.K * N;
   for (int k = 0; k < n; ++k)
@@ -589,6 +600,10 @@ pvfl_status run_rotations(pvfl_ctx* c, const pvfl_rotkeys* keys, int lv, const R
   r.digits = shared_digits ? const_cast<double*>(shared_digits) : scratch + (size_t)at_once * 2 * c->alpha * N;
   r.dig_stride = shared_digits ? 0 : DG;
   r.yup = shared_digits ? nullptr : r.digits + (size_t)at_once * DG;
+  // the key products apart, where the scratch has room for them
+  const size_t used = (size_t)at_once * (shared_digits ? 2 * (size_t)c->alpha * N : rot_scratch_doubles(c, lv));
+  const size_t apart = (size_t)at_once * rot_inner_doubles(c, lv);
+  r.inner = rot_inner_apart(lv, std::min(n, at_once)) && scratch_n >= used + apart ? scratch + used : nullptr;
   LaunchCtx L = launch_ctx(c, stream);
   for (int k0 = 0; k0 < n; k0 += at_once) {
     RotBatch b{};
@@ -611,7 +626,7 @@ extern "C" pvfl_status pvfl_rotate(pvfl_ctx* c, const pvfl_rotkeys* keys, int32_
   if (galois >= (uint32_t)(2 * N) || c->log5[galois] < 0) return fail(PVFL_E_INVALID, "Galois element not in <5>");
   const int rot = c->log5[galois];
   if (keys->slot_of_rot[rot] < 0) return fail(PVFL_E_NOKEY, "missing rotation key");
-  const size_t Q = (size_t)(level + 1) * N, per = rot_scratch_doubles(c, level);
+  const size_t Q = (size_t)(level + 1) * N, per = rot_scratch_doubles(c, level) + rot_inner_doubles(c, level);
   double* ws;
   pvfl_status st = ctx_scratch(c, (per + 2 * Q) * sizeof(double), &ws);
   if (st != PVFL_OK) return st;
@@ -622,7 +637,7 @@ extern "C" pvfl_status pvfl_rotate(pvfl_ctx* c, const pvfl_rotkeys* keys, int32_
     ct = ws + per;
   }
   const RotJob job{ct, out, rot};
-  return run_rotations(c, keys, level, &job, 1, hoisted == 0, false, ws, 1, nullptr, stream);
+  return run_rotations(c, keys, level, &job, 1, hoisted == 0, false, ws, per, 1, nullptr, stream);
 }
 
 extern "C" pvfl_status pvfl_rescale(pvfl_ctx* c, int32_t level, const void* ct, void* out, void* stream) {

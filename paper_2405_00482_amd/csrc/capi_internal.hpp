@@ -89,11 +89,9 @@ struct pvfl_plan {
   double pt_scale = 0;         // Delta_pt
   std::vector<pvfl::Term> terms;
   std::vector<uint32_t> galois;
-  // device tables
-  int* iota_dev = nullptr;     // [max(mprime, 1)] = 0..mprime-1
-  int* rot_dev = nullptr;      // BSGS: [mprime] baby rotation of diagonal i (i mod bsgs)
-  int chunk = 1, nchunk = 1;   // diagonal chunking of the fused kernel (BSGS: nchunk = giant steps x chunks per step)
-  int chunks_per_giant = 1;    // BSGS: chunks of one giant step's inner sum
+  // partial sums [2][K][N] the workspace has room for: one per column block and nchunk, one per giant step
+  int nchunk = 1, giants = 1;
+  int slices = 1;              // grid slices of the fused kernel (at most nchunk)
   // DIAG plan: in-ciphertext RaS rotations; ROW plan: per-row data
   std::vector<int> ras_rots;
   ~pvfl_plan();
@@ -133,6 +131,8 @@ pvfl_status noalloc_scratch_init(int device);  // plan.cpp
 pvfl_status ctx_rot_scratch(pvfl_ctx* c, size_t per, int want, void* stream, double** out, int* n);
 // doubles of scratch one rotation at level lv needs
 size_t rot_scratch_doubles(const pvfl_ctx* c, int lv);
+size_t rot_inner_doubles(const pvfl_ctx* c, int lv);
+bool rot_inner_apart(int lv, int n);
 struct RotJob {
   const double* ct;  // [2][lv+1][N]
   double* out;       // [2][lv+1][N], overlapping no input
@@ -142,7 +142,8 @@ struct RotJob {
 // side on scratch of at_once * rot_scratch_doubles.  pre: the automorphism
 // precedes the ModUp (O3), else the hoisted order (O4).  With shared_digits
 // (O4, every job rotates the one ciphertext whose ModUp they hold) a job
-// needs only 2 alpha N doubles of scratch.
+// needs only 2 alpha N doubles of scratch.  scratch_n: doubles of scratch in
+// all; rot_inner_doubles more for each job let the key products run apart.
 pvfl_status run_rotations(pvfl_ctx* c, const pvfl_rotkeys* keys, int lv, const RotJob* jobs, int n, bool pre, bool add,
-                          double* scratch, int at_once, const double* shared_digits, void* stream);
+                          double* scratch, size_t scratch_n, int at_once, const double* shared_digits, void* stream);
 }  // namespace pvfl

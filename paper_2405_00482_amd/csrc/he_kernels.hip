@@ -481,71 +481,24 @@ NTT_KERNEL(LOGN) void k_rescale(const double* __restrict__ in, size_t in_stride,
   }
 }
 
-// ---------------------------------------------------------------------------
-// The hot loop: fused hoisted rotations x plaintext diagonals, lazy ModDown.
-//   acc0 = sum_i pt_i * (P phi_i(c0) + sum_j phi_i(D_j) b_{i,j})
-//   acc1 = sum_i pt_i * (               sum_j phi_i(D_j) a_{i,j})
-// over Q_l u P; the i = 0 term is pt_0 * (P c0, P c1) on the Q limbs.
-// Thread = (limb r, coefficient t); blockIdx.z splits the diagonals into
-// chunks whose partial sums go to part[z][2][K][N].
-// ---------------------------------------------------------------------------
-__global__ __launch_bounds__(256) void k_diag_lazy(DiagArgs a) {
-  const int t = blockIdx.x * 256 + threadIdx.x;
-  const int r = blockIdx.y;
-  const int N = a.N, half = N >> 1, K = a.K;
-  const int pi = a.limb_prime[r];
-  const int klimb = a.key_limb[r];
-  const bool isq = r <= a.lv;
-  const ModQ m = a.mods[pi];
-  const int i0 = blockIdx.z * a.chunk;
-  const int i1 = min(i0 + a.chunk, a.mprime);
-  double acc0 = 0.0, acc1 = 0.0;
-  const size_t limbN = (size_t)r * N;
-  int cnt = 0;
-  for (int i = i0; i < i1; ++i) {
-    const double p = a.pt[(size_t)a.pt_index[i] * K * N + limbN + t];
-    if (a.rot[i] == 0) {
-      if (isq) {
-        acc0 += mulmod(p, a.pc[limbN + t], m);
-        acc1 += mulmod(p, a.pc[(size_t)(a.lv + 1) * N + limbN + t], m);
-      }
-    } else {
-      const int ts = orbit_shift(t, a.rot[i], half);
-      const double* key = a.keys + (size_t)a.slot_of_rot[a.rot[i]] * a.key_stride;
-      double u0 = 0.0, u1 = 0.0;
-      for (int j = 0; j < a.beta; ++j) {
-        const double d = a.digits[((size_t)j * K) * N + limbN + ts];
-        const double* kj = key + (size_t)j * 2 * a.key_limbs * N;
-        u0 += mulmod(d, kj[(size_t)klimb * N + t], m);
-        u1 += mulmod(d, kj[(size_t)(a.key_limbs + klimb) * N + t], m);
-      }
-      if (isq) u0 += a.pc[limbN + ts];
-      acc0 += mulmod(p, u0, m);
-      acc1 += mulmod(p, u1, m);
-    }
-    if (++cnt == 8) { acc0 = reduce(acc0, m); acc1 = reduce(acc1, m); cnt = 0; }
-  }
-  double* part = a.part + (size_t)blockIdx.z * 2 * K * N;
-  part[limbN + t] = reduce(acc0, m);
-  part[(size_t)K * N + limbN + t] = reduce(acc1, m);
-}
-
-// sum the chunk partials of every group y: part[y][nchunk][2][K][N] -> acc[y][2][K][N]
-__global__ __launch_bounds__(256) void k_sum_partials(const double* __restrict__ part, int nchunk, int K, int N,
+// sum n partials: part[n][2][K][N] -> acc[2][K][N]
+__global__ __launch_bounds__(256) void k_sum_partials(const double* __restrict__ part, int n, int K, int N,
                                                        LimbMap limb_prime, const ModQ* __restrict__ mods,
                                                        double* __restrict__ acc) {
   const size_t idx = (size_t)blockIdx.x * 256 + threadIdx.x;
   const size_t tot = (size_t)2 * K * N;
   if (idx >= tot) return;
-  part += (size_t)blockIdx.y * nchunk * tot;
-  acc += (size_t)blockIdx.y * tot;
   const int r = (int)((idx / N) % K);
   const ModQ m = mods[limb_prime.idx[r]];
   double v = 0.0;
-  for (int c = 0; c < nchunk; ++c) {
-    v += part[(size_t)c * tot + idx];
-    if ((c & 7) == 7) v = reduce(v, m);
+  int c = 0;
+  for (; c + 4 <= n; c += 4) {  // four loads in flight; |v| < 4.5 q between re-centrings
+    double t[4];
+#pragma unroll
+    for (int u = 0; u < 4; ++u) t[u] = part[(size_t)(c + u) * tot + idx];
+    v = reduce(v + t[0] + t[1] + t[2] + t[3], m);
   }
+  for (; c < n; ++c) v += part[(size_t)c * tot + idx];
   acc[idx] = reduce(v, m);
 }
 
@@ -767,18 +720,11 @@ hipError_t launch_rescale(const LaunchCtx& L, const double* in, int npoly, int l
 
 static inline unsigned blocks_for(size_t n) { return (unsigned)((n + 255) / 256); }
 
-hipError_t launch_diag_lazy(const LaunchCtx& L, const DiagArgs& a, int nchunk) {
-  const dim3 grid(a.N / 256, a.K, nchunk);
-  hipLaunchKernelGGL(k_diag_lazy, grid, dim3(256), 0, L.stream, a);
-  return hipGetLastError();
-}
-
-hipError_t launch_sum_partials(const LaunchCtx& L, const double* part, int nchunk, int K, int N, LimbMap limb_prime,
-                               double* acc, int ngroups) {
+hipError_t launch_sum_partials(const LaunchCtx& L, const double* part, int n, int K, int N, LimbMap limb_prime,
+                               double* acc) {
   const size_t tot = (size_t)2 * K * N;
-  if (ngroups < 1) return hipSuccess;
-  hipLaunchKernelGGL(k_sum_partials, dim3(blocks_for(tot), ngroups), dim3(256), 0, L.stream, part, nchunk, K, N,
-                     limb_prime, L.tb.mods, acc);
+  hipLaunchKernelGGL(k_sum_partials, dim3(blocks_for(tot)), dim3(256), 0, L.stream, part, n, K, N, limb_prime, L.tb.mods,
+                     acc);
   return hipGetLastError();
 }
 

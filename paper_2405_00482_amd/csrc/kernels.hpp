@@ -91,6 +91,7 @@ struct RotRun {
   double* digits;      // item k at digits + k * dig_stride, [beta][K][N]
   size_t dig_stride;
   double* ydown;       // [n][2][alpha][N]
+  double* inner;       // [n][2][K][N]: the key products in a launch of their own; null: inside the transforms
 };
 
 struct RescaleArgs {
@@ -100,19 +101,18 @@ struct RescaleArgs {
 };
 
 struct DiagArgs {
-  int N, K, lv, beta, mprime, chunk, key_limbs;
+  int N, K, lv, beta, mprime, chunk, key_limbs;  // chunk: diagonals per grid slice
+  int add;                 // 1: add to what `part` holds
   size_t key_stride;
   const ModQ* mods;
   int limb_prime[kMaxLimbs];
-  int key_limb[kMaxLimbs];
+  const double* pmod;      // P mod q_i, centred
   const double* pt;        // [n_pts][K][N]
-  const int* pt_index;     // [mprime]
-  const int* rot;          // [mprime] rotation amount of diagonal i (0: the unrotated P*c term)
   const int* slot_of_rot;  // [N/2] rotation amount -> key index
   const double* keys;
   const double* digits;    // [beta][K][N]
-  const double* pc;        // [2][lv+1][N]: P*c0, P*c1
-  double* part;            // [nchunk][2][K][N]
+  const double* ct;        // [2][lv+1][N]
+  double* part;            // [slices][2][K][N]
 };
 
 hipError_t launch_ntt(const LaunchCtx& L, NttOp op, const void* in, void* out, int nblocks, LimbMap map);
@@ -146,10 +146,13 @@ hipError_t launch_rotations(const LaunchCtx& L, const RotBatch& b, const RotRun&
 // out = (out_add ? out : 0) + sum_k ct_k pt_k (pt null: plain sum), ct_k at ct + k ct_stride, pt_k at pt + k pt_stride
 hipError_t launch_sum_cts(const LaunchCtx& L, const double* ct, size_t ct_stride, const double* pt, size_t pt_stride,
                           int n, int lv, int N, bool out_add, double* out);
-hipError_t launch_diag_lazy(const LaunchCtx& L, const DiagArgs& a, int nchunk);
-// part[y][nchunk][2][K][N] summed over the chunks into acc[y][2][K][N], y < ngroups
-hipError_t launch_sum_partials(const LaunchCtx& L, const double* part, int nchunk, int K, int N, LimbMap limb_prime,
-                               double* acc, int ngroups = 1);
+// one product's diagonals in `slices` slices of a.chunk
+hipError_t launch_diag_lazy(const LaunchCtx& L, const DiagArgs& a, int slices);
+// baby-step/giant-step inner sums of every giant step, a.part = [g][2][K][N]
+hipError_t launch_diag_bsgs(const LaunchCtx& L, const DiagArgs& a, int bs, int g);
+// part[n][2][K][N] summed into acc[2][K][N]
+hipError_t launch_sum_partials(const LaunchCtx& L, const double* part, int n, int K, int N, LimbMap limb_prime,
+                               double* acc);
 // Alg. 3: out[k] = sum_i ct[i] * pt[i][k]   (ct [nct][2][lv+1][N], pt [nct][nout][lv+1][N])
 hipError_t launch_ctmat(const LaunchCtx& L, const double* ct, const double* pt, int nct, int nout, int lv, int N,
                         double* out);

@@ -44,10 +44,7 @@ static int ilog2(int x) {
   return r;
 }
 
-pvfl_plan::~pvfl_plan() {
-  if (iota_dev) (void)hipFree(iota_dev);
-  if (rot_dev) (void)hipFree(rot_dev);
-}
+pvfl_plan::~pvfl_plan() {}
 
 static uint32_t galois_rotl(int i, int N) {
   const int half = N / 2;
@@ -228,28 +225,23 @@ extern "C" pvfl_status pvfl_plan_create(pvfl_ctx* c, const pvfl_plan_opts* o, pv
   p->galois.erase(std::unique(p->galois.begin(), p->galois.end()), p->galois.end());
   I.n_galois = (int)p->galois.size();
   I.pt_limbs = (lazy && (o->kind == PVFL_PLAN_HYBRID || o->kind == PVFL_PLAN_DIAG)) ? p->K : lv + 1;
-  // fused-kernel chunking: aim for >= 4096 workgroups per launch
+  // The workspace's room for partial sums: chunks of the diagonals that fill
+  // 4096 workgroups of 256 indices (giant steps: at least one per step).
   const int mprime = std::max(1, I.mprime);
-  const int per_chunk = (N / 256) * p->K;
-  int target = std::max(1, std::min(64, 4096 / std::max(1, per_chunk)));
-  p->chunk = std::max(1, (mprime + target - 1) / target);
-  p->nchunk = (mprime + p->chunk - 1) / p->chunk;
-  std::vector<int> iota(mprime);
-  for (int i = 0; i < mprime; ++i) iota[i] = i;
-  if (hipMalloc((void**)&p->iota_dev, sizeof(int) * mprime) != hipSuccess) return fail(PVFL_E_NOMEM, "plan tables");
-  HIP_TRY(hipMemcpy(p->iota_dev, iota.data(), sizeof(int) * mprime, hipMemcpyHostToDevice));
+  const int target = std::max(1, std::min(64, 4096 / std::max(1, (N / 256) * p->K)));
+  const int chunk = std::max(1, (mprime + target - 1) / target);
+  p->nchunk = (mprime + chunk - 1) / chunk;
   if (I.bsgs) {
-    // chunks never straddle a giant step; enough of them to fill the chip
-    const int g = mprime / I.bsgs;
+    p->giants = mprime / I.bsgs;
     int per = 1;
-    while (per < I.bsgs && (int64_t)g * per < target) per *= 2;
-    p->chunks_per_giant = per;
-    p->chunk = I.bsgs / per;
-    p->nchunk = g * per;
-    for (int i = 0; i < mprime; ++i) iota[i] = i % I.bsgs;
-    if (hipMalloc((void**)&p->rot_dev, sizeof(int) * mprime) != hipSuccess) return fail(PVFL_E_NOMEM, "plan tables");
-    HIP_TRY(hipMemcpy(p->rot_dev, iota.data(), sizeof(int) * mprime, hipMemcpyHostToDevice));
+    while (per < I.bsgs && (int64_t)p->giants * per < target) per *= 2;
+    p->nchunk = p->giants * per;
   }
+  // The fused kernel's 16 waves per 64 indices share the diagonals in LDS;
+  // slices of the diagonals only where that leaves less than 8192 waves (the
+  // chip's) and a wave would still have four diagonals.
+  const int64_t waves = (int64_t)(N / 64) * p->K * 16;
+  while (p->slices * 2 <= p->nchunk && waves * p->slices < 8192 && mprime >= 16 * 4 * 2 * p->slices) p->slices *= 2;
   *out = p.release();
   return PVFL_OK;
 }
@@ -290,7 +282,7 @@ static size_t ws_doubles(const pvfl_plan* p, int count = 1) {
     case PVFL_PLAN_DIAG:
       if (p->opts.lazy_moddown) {
         // every term (count of them) brings col_blocks input ciphertexts
-        const size_t CB = (size_t)count * p->info.col_blocks, g = p->info.bsgs ? p->nchunk / p->chunks_per_giant : 1;
+        const size_t CB = (size_t)count * p->info.col_blocks, g = p->giants;
         const size_t bsgs = p->info.bsgs ? g * 2 * Q + digits + 2 * Q + Q : 0;
         // + 4Q at the end: in-ciphertext RaS temporaries
         return CB * digits + Q + CB * 2 * Q + CB * p->nchunk * 2 * KN + g * 2 * KN + g * ydown + bsgs + 4 * Q;
@@ -320,14 +312,33 @@ static size_t eager_per(const pvfl_plan* p) {  // one rotation: its result and i
   const size_t N = p->ctx->N, own = p->opts.unhoisted ? rot_scratch_doubles(p->ctx, p->lv) : 2 * (size_t)p->ctx->alpha * N;
   return own + 2 * (size_t)(p->lv + 1) * N;
 }
+// what n rotations add when their key products run apart
+static size_t inner_room(const pvfl_plan* p, size_t n) {
+  return rot_inner_apart(p->lv, (int)n) ? n * rot_inner_doubles(p->ctx, p->lv) : 0;
+}
+// Giant steps: one rotation with its result, and the partial sums that its
+// rotations may overwrite.
+static size_t bsgs_per(const pvfl_plan* p) {
+  return rot_scratch_doubles(p->ctx, p->lv) + 2 * (size_t)(p->lv + 1) * p->ctx->N;
+}
+static size_t bsgs_sums(const pvfl_plan* p, int count) {
+  return ((size_t)count * p->info.col_blocks * p->nchunk + p->giants) * 2 * p->K * p->ctx->N;
+}
 static size_t ws_preferred(const pvfl_plan* p, int count) {
   const size_t need = std::max<size_t>(ws_doubles(p, count), 1);
+  // giant steps' rotations, where the room of the spent partial sums does not hold them all (bsgs_at_once)
+  if (p->info.bsgs) {
+    const size_t per = bsgs_per(p), n = std::min<size_t>((size_t)p->giants - 1, kRotBatchBytes / sizeof(double) / per);
+    const size_t room = n * per + inner_room(p, n);
+    return need + (bsgs_sums(p, count) < room ? room : 0);
+  }
   const bool eager = (p->opts.kind == PVFL_PLAN_HYBRID || p->opts.kind == PVFL_PLAN_DIAG) && !p->opts.lazy_moddown;
   if (!eager) return need;
   const size_t cap = kRotBatchBytes / sizeof(double), per = eager_per(p), fixed = eager_fixed(p);
   if (cap <= need) return need;
   const size_t n = std::min<size_t>({(size_t)std::max(1, p->info.mprime - 1), (size_t)kRotsPerLaunch, (cap - fixed) / per});
-  return std::max(need, fixed + n * per);
+  const size_t room = fixed + n * per, inner = inner_room(p, n);
+  return std::max(need, room + (room + inner <= cap ? inner : 0));
 }
 extern "C" size_t pvfl_bytes_workspace(const pvfl_plan* p) { return p ? sizeof(double) * ws_preferred(p, 1) : 0; }
 extern "C" size_t pvfl_bytes_workspace_sum(const pvfl_plan* p, int32_t count) {
@@ -360,30 +371,39 @@ static pvfl_status check_keys(const pvfl_plan* p, const pvfl_rotkeys* keys) {
 // `count` terms, each an input ciphertext set cts[k] and its plaintexts pts[k]
 // laid out by the plan, summed over Q u P before the ModDown (count > 1: Eq. 4)
 static pvfl_status run_diag_lazy(const pvfl_plan* p, int count, const double* const* cts, const double* const* ptss,
-                                 const pvfl_rotkeys* keys, double* out, double* ws, void* stream) {
+                                 const pvfl_rotkeys* keys, double* out, double* ws, size_t ws_bytes, void* stream) {
   pvfl_ctx* c = p->ctx;
   const int N = c->N, lv = p->lv, K = p->K;
-  const size_t rot_per = rot_scratch_doubles(c, lv) + 2 * (size_t)(lv + 1) * N;  // one giant rotation and its result
   const int CB1 = p->info.col_blocks, CB = count * CB1, RB = p->info.row_blocks;
-  const int bs = p->info.bsgs, g = bs ? p->nchunk / p->chunks_per_giant : 1;
+  const int bs = p->info.bsgs, g = p->giants;
   const size_t Q = (size_t)(lv + 1) * N, KN = (size_t)K * N, DG = (size_t)p->beta * KN;
   const KsLevel& kl = c->ks_host[lv];
   // workspace, in the order ws_doubles counts it
   // input x = k * CB1 + cb: column block cb of term k
-  auto ct_of = [&](int x) { return cts[x / CB1] + (size_t)(x % CB1) * 2 * (lv + 1) * N; };
+  double* const copies = ws + CB * DG + Q;              // [CB][2][lv+1][N]: inputs that the output overlaps
+  bool copied = false;
+  auto ct_of = [&](int x) -> const double* {
+    return copied ? copies + (size_t)x * 2 * Q : cts[x / CB1] + (size_t)(x % CB1) * 2 * Q;
+  };
   auto pt_of = [&](int b, int x) {
     return ptss[x / CB1] + (size_t)(b * CB1 + x % CB1) * std::max(1, p->info.mprime) * K * N;
   };
   double* digits = ws;                                  // [CB][beta][K][N]
   double* yup = digits + CB * DG;                       // [lv+1][N]
-  double* pc = yup + Q;                                 // [CB][2][lv+1][N]: P*c of every input
-  double* part = pc + CB * 2 * Q;                       // [CB][nchunk][2][K][N]
+  double* part = copies + CB * 2 * Q;                   // [CB][slices][2][K][N]
   double* acc = part + (size_t)CB * p->nchunk * 2 * KN; // [g][2][K][N]
   double* ydown = acc + (size_t)g * 2 * KN;             // [2g][alpha][N]
   double* cj = ydown + (size_t)2 * g * c->alpha * N;    // BSGS: [g][2][lv+1][N] giant-step inner sums
-  // BSGS: the giant rotations run side by side on the memory of the partial
-  // sums and the accumulators, which are spent by then
-  const int giants_at_once = bs ? std::min(g - 1, (int)((ydown - part) / rot_per)) : 0;
+  // BSGS: the giant rotations run side by side, on the memory of the partial
+  // sums and the accumulators, which are spent by then, or past the smallest
+  // workspace if there is more room; where neither holds one, one by one in the
+  // memory after cj.
+  double* rws = part;
+  size_t rws_n = bs ? bsgs_sums(p, count) : 0;
+  const size_t past = bs ? ws_bytes / sizeof(double) - ws_doubles(p, count) : 0;
+  if (past > rws_n) rws = ws + ws_doubles(p, count), rws_n = past;
+  const int at_once = bs ? (int)std::max<size_t>(1, std::min<size_t>(g - 1, rws_n / bsgs_per(p))) : 0;
+  if (bs && rws_n < bsgs_per(p)) rws = cj + (size_t)g * 2 * Q, rws_n = DG + 7 * Q;
   LaunchCtx L = launch_ctx(c, stream);
   const int mprime = p->info.mprime;
   if (mprime == 1 && c->alpha == 1) {
@@ -397,15 +417,17 @@ static pvfl_status run_diag_lazy(const pvfl_plan* p, int count, const double* co
     }
     return PVFL_OK;
   }
-  // one ModUp and one P*c per input ciphertext, shared by every row block
-  for (int cb = 0; cb < CB; ++cb) {
-    const double* ct = ct_of(cb);
-    if (mprime > 1) {
-      KernelTimer kt(c, stream, PVFL_TIMING_MODUP, 8.0 * (double)(Q + DG));
-      HIP_TRY(launch_modup(L, ct, 0, 1, lv, c->ks_dev + lv, kl.n_tasks, yup, digits + cb * DG, 0));
-      kt.stop();
-    }
-    HIP_TRY(launch_scale_by_p(L, ct, lv, N, c->pmod_dev, pc + cb * 2 * Q));
+  // the first row block's output is written before the next block reads the inputs
+  for (int x = 0; RB > 1 && !bs && x < CB; ++x)
+    if (ct_of(x) < out + (size_t)RB * 2 * Q && out < ct_of(x) + 2 * Q) copied = true;
+  for (int x = 0; copied && x < CB; ++x)
+    HIP_TRY(hipMemcpyAsync(copies + (size_t)x * 2 * Q, cts[x / CB1] + (size_t)(x % CB1) * 2 * Q, 2 * Q * sizeof(double),
+                           hipMemcpyDeviceToDevice, (hipStream_t)stream));
+  // one ModUp per input ciphertext, shared by every row block
+  for (int cb = 0; cb < CB && mprime > 1; ++cb) {
+    KernelTimer kt(c, stream, PVFL_TIMING_MODUP, 8.0 * (double)(Q + DG));
+    HIP_TRY(launch_modup(L, ct_of(cb), 0, 1, lv, c->ks_dev + lv, kl.n_tasks, yup, digits + cb * DG, 0));
+    kt.stop();
   }
   DiagArgs a{};
   a.N = N;
@@ -413,15 +435,12 @@ static pvfl_status run_diag_lazy(const pvfl_plan* p, int count, const double* co
   a.lv = lv;
   a.beta = p->beta;
   a.mprime = mprime;
-  a.chunk = p->chunk;
+  const int slices = bs ? 1 : p->slices;
+  a.chunk = (mprime + slices - 1) / slices;
+  a.pmod = c->pmod_dev;
   a.mods = c->tabs.mods;
   const LimbMap lp = qp_map(c, lv, true);
-  for (int r = 0; r < K; ++r) {
-    a.limb_prime[r] = lp.idx[r];
-    a.key_limb[r] = lp.idx[r];
-  }
-  a.pt_index = p->iota_dev;
-  a.rot = bs ? p->rot_dev : p->iota_dev;
+  for (int r = 0; r < K; ++r) a.limb_prime[r] = lp.idx[r];
   if (keys) {
     a.keys = keys->keys;
     a.key_limbs = keys->key_limbs;
@@ -429,52 +448,47 @@ static pvfl_status run_diag_lazy(const pvfl_plan* p, int count, const double* co
     a.slot_of_rot = keys->slot_of_rot_dev;
   }
   // algorithmic bytes of one fused launch: every key and plaintext limb once,
-  // digits and P*c once, partials written
+  // digits and the ciphertext once, sums written
   const int n_keys = bs ? bs - 1 : mprime - 1;
   const double diag_bytes = 8.0 * ((double)n_keys * 2 * p->beta * KN + (double)mprime * KN + (double)DG + 2.0 * Q +
-                                   (double)p->nchunk * 2 * KN);
+                                   (double)(bs ? g : slices) * 2 * KN);
   for (int b = 0; b < RB; ++b) {
     double* ob = out + (size_t)b * 2 * Q;
-    int z = 0;
     for (int cb = 0; cb < CB; ++cb) {
       a.digits = digits + cb * DG;
-      a.pc = pc + cb * 2 * Q;
+      a.ct = ct_of(cb);
       a.pt = pt_of(b, cb);
-      a.part = part + (size_t)z * 2 * KN;
+      // one slice: every input adds to the accumulator; more: each has its partial sums
+      a.add = !bs && slices == 1 && cb > 0 ? 1 : 0;
+      a.part = bs || slices == 1 ? acc : part + (size_t)cb * slices * 2 * KN;
       {
         KernelTimer kt(c, stream, PVFL_TIMING_DIAG, diag_bytes);
-        HIP_TRY(launch_diag_lazy(L, a, p->nchunk));
+        HIP_TRY(bs ? launch_diag_bsgs(L, a, bs, g) : launch_diag_lazy(L, a, slices));
         kt.stop();
       }
-      if (!bs) {
-        z += p->nchunk;
-        continue;
-      }
-      // every giant step's inner sum (its chunks added) down to Q at once, then
-      // rotated by j*bs and added
-      HIP_TRY(launch_sum_partials(L, a.part, p->chunks_per_giant, K, N, lp, acc, g));
+      if (!bs) continue;
+      // every giant step's inner sum down to Q at once, then rotated by j*bs and added
       {
         KernelTimer kt(c, stream, PVFL_TIMING_MODDOWN, 8.0 * (double)g * (2 * KN + 2 * Q));
         HIP_TRY(launch_moddown(L, acc, 2 * g, lv, c->alpha, c->ks_dev + lv, ydown, cj));
         kt.stop();
       }
       HIP_TRY(launch_sum_cts(L, cj, 0, nullptr, 0, 1, lv, N, cb > 0, ob));
-      // fewer than one there: the single giant rotation's own memory after cj
-      double* rws = giants_at_once > 0 ? part : cj + (size_t)g * 2 * Q;
-      const int at_once = std::max(1, giants_at_once);
-      double* rct = rws + (size_t)at_once * (rot_per - 2 * Q);
+      double* rct = rws;
+      double* scratch = rws + (size_t)at_once * 2 * Q;
       for (int j0 = 1; j0 < g; j0 += at_once) {
         const int cnt = std::min(at_once, g - j0);
         std::vector<RotJob> jobs(cnt);
         for (int u = 0; u < cnt; ++u)
           jobs[u] = RotJob{cj + (size_t)(j0 + u) * 2 * Q, rct + (size_t)u * 2 * Q, (j0 + u) * bs};
-        pvfl_status st = run_rotations(c, keys, lv, jobs.data(), cnt, false, false, rws, at_once, nullptr, stream);
+        pvfl_status st = run_rotations(c, keys, lv, jobs.data(), cnt, false, false, scratch,
+                                       rws_n - (size_t)at_once * 2 * Q, at_once, nullptr, stream);
         if (st != PVFL_OK) return st;
         HIP_TRY(launch_sum_cts(L, rct, 2 * Q, nullptr, 0, cnt, lv, N, true, ob));
       }
     }
     if (bs) continue;
-    HIP_TRY(launch_sum_partials(L, part, z, K, N, lp, acc));
+    if (slices > 1) HIP_TRY(launch_sum_partials(L, part, CB * slices, K, N, lp, acc));
     {
       KernelTimer kt(c, stream, PVFL_TIMING_MODDOWN, 8.0 * (double)(2 * KN + 2 * Q));
       HIP_TRY(launch_moddown(L, acc, 2, lv, c->alpha, c->ks_dev + lv, ydown, ob));
@@ -498,8 +512,9 @@ static pvfl_status run_diag_eager(const pvfl_plan* p, const double* ct_in, const
   const int at_once = (int)std::min<size_t>({(ws_bytes / sizeof(double) - fixed) / per, (size_t)kRotsPerLaunch,
                                              (size_t)std::max(1, mprime - 1)});
   double* digits = ws;                                  // hoisted: [beta][K][N], then ModUp's [lv+1][N]
-  double* scratch = ws + fixed;
-  double* rct = scratch + (size_t)at_once * (per - 2 * Q);  // [at_once][2][lv+1][N] rotated ciphertexts
+  double* rct = ws + fixed;                             // [at_once][2][lv+1][N] rotated ciphertexts
+  double* scratch = rct + (size_t)at_once * 2 * Q;
+  const size_t scratch_n = ws_bytes / sizeof(double) - fixed - (size_t)at_once * 2 * Q;
   LaunchCtx L = launch_ctx(c, stream);
   std::vector<RotJob> jobs(at_once);
   for (int b = 0; b < p->info.row_blocks; ++b) {
@@ -513,7 +528,8 @@ static pvfl_status run_diag_eager(const pvfl_plan* p, const double* ct_in, const
       for (int i0 = 1; i0 < mprime; i0 += at_once) {
         const int cnt = std::min(at_once, mprime - i0);
         for (int u = 0; u < cnt; ++u) jobs[u] = RotJob{ct, rct + (size_t)u * 2 * Q, i0 + u};
-        pvfl_status st = run_rotations(c, keys, lv, jobs.data(), cnt, o3, false, scratch, at_once, o3 ? nullptr : digits, stream);
+        pvfl_status st = run_rotations(c, keys, lv, jobs.data(), cnt, o3, false, scratch, scratch_n, at_once,
+                                       o3 ? nullptr : digits, stream);
         if (st != PVFL_OK) return st;
         HIP_TRY(launch_sum_cts(L, rct, 2 * Q, pt + (size_t)i0 * Q, Q, cnt, lv, N, true, acc));
       }
@@ -528,13 +544,14 @@ static pvfl_status run_ras_in_ct(const pvfl_plan* p, const pvfl_rotkeys* keys, d
   pvfl_ctx* c = p->ctx;
   const size_t Q = (size_t)(p->lv + 1) * c->N;
   double* ws;
-  pvfl_status st = ctx_scratch(c, rot_scratch_doubles(c, p->lv) * sizeof(double), &ws);
+  const size_t per = rot_scratch_doubles(c, p->lv) + rot_inner_doubles(c, p->lv);
+  pvfl_status st = ctx_scratch(c, per * sizeof(double), &ws);
   if (st != PVFL_OK) return st;
   double* src = ct;
   double* dst = tmp;
   for (int k : p->ras_rots) {
     const RotJob job{src, dst, k % (c->N / 2)};
-    if ((st = run_rotations(c, keys, p->lv, &job, 1, true, true, ws, 1, nullptr, stream)) != PVFL_OK) return st;
+    if ((st = run_rotations(c, keys, p->lv, &job, 1, true, true, ws, per, 1, nullptr, stream)) != PVFL_OK) return st;
     std::swap(src, dst);
   }
   if (src != ct) HIP_TRY(hipMemcpyAsync(ct, src, 2 * Q * sizeof(double), hipMemcpyDeviceToDevice, (hipStream_t)stream));
@@ -553,7 +570,8 @@ static pvfl_status run_row(const pvfl_plan* p, const double* ct, const double* p
   const size_t Q2 = (size_t)(lv + 1) * N, Q1 = (size_t)lv * N, Q0 = (size_t)(lv - 1) * N;
   // one row: t1 and its rotate-and-sum partner at lv - 1; the indicator's
   // product t0 and its placement at lv - 2; the rotations' scratch
-  const size_t bufs = 4 * Q1 + 4 * Q0, rot = rot_scratch_doubles(c, lv - 1);
+  const size_t bufs = 4 * Q1 + 4 * Q0, rot = rot_scratch_doubles(c, lv - 1) +
+                                           (rot_inner_apart(lv - 1, std::min(m, kRotsPerLaunch)) ? rot_inner_doubles(c, lv - 1) : 0);
   double* base;
   int rows;
   pvfl_status st = ctx_rot_scratch(c, bufs + rot, std::min(m, kRotsPerLaunch), stream, &base, &rows);
@@ -578,7 +596,7 @@ static pvfl_status run_row(const pvfl_plan* p, const double* ct, const double* p
     double* dst = tb;
     for (int k : p->ras_rots) {
       for (int u = 0; u < cnt; ++u) jobs[u] = RotJob{src + (size_t)u * 2 * Q1, dst + (size_t)u * 2 * Q1, k % half};
-      if ((st = run_rotations(c, keys, lv - 1, jobs.data(), cnt, true, true, scratch, rows, nullptr, stream)) != PVFL_OK)
+      if ((st = run_rotations(c, keys, lv - 1, jobs.data(), cnt, true, true, scratch, rows * rot, rows, nullptr, stream)) != PVFL_OK)
         return st;
       std::swap(src, dst);
     }
@@ -587,7 +605,7 @@ static pvfl_status run_row(const pvfl_plan* p, const double* ct, const double* p
     if (first) HIP_TRY(launch_sum_cts(L, t0, 0, nullptr, 0, 1, lv - 2, N, false, out));
     for (int u = first; u < cnt; ++u) jobs[u] = RotJob{t0 + (size_t)u * 2 * Q0, r0 + (size_t)u * 2 * Q0, (half - b - u) & (half - 1)};
     if (cnt > first) {
-      if ((st = run_rotations(c, keys, lv - 2, jobs.data() + first, cnt - first, true, false, scratch, rows, nullptr, stream)) !=
+      if ((st = run_rotations(c, keys, lv - 2, jobs.data() + first, cnt - first, true, false, scratch, rows * rot, rows, nullptr, stream)) !=
           PVFL_OK)
         return st;
       HIP_TRY(launch_sum_cts(L, r0 + (size_t)first * 2 * Q0, 2 * Q0, nullptr, 0, cnt - first, lv - 2, N, true, out));
@@ -613,7 +631,7 @@ extern "C" pvfl_status pvfl_matmul_ct_pt(const pvfl_plan* p, const void* ct_v, c
   switch (p->opts.kind) {
     case PVFL_PLAN_HYBRID:
     case PVFL_PLAN_DIAG: {
-      st = p->opts.lazy_moddown ? run_diag_lazy(p, 1, &ct, &pt, keys, out, ws, stream)
+      st = p->opts.lazy_moddown ? run_diag_lazy(p, 1, &ct, &pt, keys, out, ws, ws_bytes, stream)
                                 : run_diag_eager(p, ct, pt, keys, out, ws, ws_bytes, stream);
       if (st != PVFL_OK) return st;
       if (p->opts.kind == PVFL_PLAN_DIAG && !p->ras_rots.empty()) {
@@ -691,7 +709,7 @@ extern "C" pvfl_status pvfl_matmul_ct_pt_noalloc(const pvfl_plan* p, const void*
   switch (p->opts.kind) {
     case PVFL_PLAN_HYBRID:
     case PVFL_PLAN_DIAG:
-      st = p->opts.lazy_moddown ? run_diag_lazy(p, 1, &ct, &pt, keys, out, ws, stream)
+      st = p->opts.lazy_moddown ? run_diag_lazy(p, 1, &ct, &pt, keys, out, ws, kNoAllocBytes, stream)
                                 : run_diag_eager(p, ct, pt, keys, out, ws, kNoAllocBytes, stream);
       break;
     default: {
@@ -724,7 +742,7 @@ extern "C" pvfl_status pvfl_matmul_ct_pt_sum(const pvfl_plan* p, int32_t count, 
   if (st != PVFL_OK) return st;
   double* ws = nullptr;
   if ((st = get_ws(p, ws_v, ws_bytes, &ws, count)) != PVFL_OK) return st;
-  return run_diag_lazy(p, count, cts.data(), pts.data(), keys, (double*)out_v, ws, stream);
+  return run_diag_lazy(p, count, cts.data(), pts.data(), keys, (double*)out_v, ws, ws_bytes, stream);
 }
 
 // ---------------------------------------------------------------------------
@@ -776,7 +794,7 @@ extern "C" pvfl_status pvfl_ctmat_transpose(const pvfl_plan* p, const void* ct_i
   if (st != PVFL_OK) return st;
   if (ct_in == ct_out) return fail(PVFL_E_INVALID, "the conversion cannot run in place");
   pvfl_ctx* c = p->ctx;
-  const size_t Q = (size_t)(p->lv + 1) * c->N, per = rot_scratch_doubles(c, p->lv);
+  const size_t Q = (size_t)(p->lv + 1) * c->N;
   std::vector<RotJob> jobs;
   for (int i = 0; i < p->info.mprime; ++i) {
     int k, r;
@@ -792,10 +810,13 @@ extern "C" pvfl_status pvfl_ctmat_transpose(const pvfl_plan* p, const void* ct_i
   if (!keys) return fail(PVFL_E_NOKEY, "the conversion needs rotation keys");
   double* scratch;
   int at_once;
+  const bool apart = rot_inner_apart(p->lv, std::min((int)jobs.size(), kRotsPerLaunch));
+  const size_t per = rot_scratch_doubles(c, p->lv) + (apart ? rot_inner_doubles(c, p->lv) : 0);
   if ((st = ctx_rot_scratch(c, per, (int)jobs.size(), stream, &scratch, &at_once)) != PVFL_OK) return st;
   if (at_once == 0) {
     at_once = 1;
     if ((st = ctx_scratch(c, per * sizeof(double), &scratch)) != PVFL_OK) return st;
   }
-  return run_rotations(c, keys, p->lv, jobs.data(), (int)jobs.size(), true, false, scratch, at_once, nullptr, stream);
+  return run_rotations(c, keys, p->lv, jobs.data(), (int)jobs.size(), true, false, scratch, at_once * per, at_once,
+                       nullptr, stream);
 }

@@ -86,6 +86,43 @@ __device__ __forceinline__ void rot_inner(double (&u)[16], const RotDigits& d, i
   }
 }
 
+// The key products of every rotation and limb on their own, one thread per
+// index: u[item][x][r][N], x = 0 with P phi(c0) added, with add = 1 both with P
+// times the unrotated input.  See launch_rotations for when this is done.
+__global__ __launch_bounds__(256) void k_rot_inner(RotBatch b, int pre, int add, const KsLevel* __restrict__ kl,
+                                                   const double* __restrict__ digits, size_t dig_stride, int key_limbs,
+                                                   int N, const ModQ* __restrict__ mods, double* __restrict__ u) {
+  const int t = blockIdx.x * 256 + threadIdx.x, r = blockIdx.y, it = blockIdx.z;
+  const int lv = kl->lv, K = kl->K;
+  const bool isq = r <= lv;
+  const int pi = isq ? r : kl->n_q_total + r - lv - 1;
+  const ModQ m = mods[pi];
+  const int rot = b.it[it].rot;
+  const double* ct = b.it[it].ct;
+  const RotDigits d{digits + (size_t)it * dig_stride, ct + (size_t)(lv + 1) * N, K, lv, kl->alpha, N, rot, pre ? 0 : rot};
+  const double* key = b.it[it].key + (size_t)pi * N;
+  const size_t key_digit = (size_t)2 * key_limbs * N;
+  double u0 = 0.0, u1 = 0.0;
+  for (int j = 0; j < kl->beta; ++j) {
+    int sh;
+    const double* row = d.row(j, r, &sh);
+    const double x = gmem(row)[orbit_shift(t, sh, N >> 1)];
+    u0 += mulmod(x, gmem(key)[(size_t)j * key_digit + t], m);
+    u1 += mulmod(x, gmem(key)[(size_t)j * key_digit + (size_t)key_limbs * N + t], m);
+  }
+  if (isq) {
+    const double pmod = kl->p_mod[r];
+    u0 += mulmod(gmem(ct)[(size_t)r * N + orbit_shift(t, rot, N >> 1)], pmod, m);
+    if (add) {
+      u0 += mulmod(gmem(ct)[(size_t)r * N + t], pmod, m);
+      u1 += mulmod(gmem(ct)[(size_t)(lv + 1 + r) * N + t], pmod, m);
+    }
+  }
+  double* dst = u + ((size_t)it * 2 * K + r) * N + t;
+  *dst = reduce(u0, m);
+  dst[(size_t)K * N] = reduce(u1, m);
+}
+
 #define ROT_KERNEL(LOGN) __global__ __launch_bounds__(NttShape<LOGN>::T)
 
 // block (item, i): y[item][i] = [c1_i (Q_j/q_i)^-1]_{q_i}, canonical; pre = 1
@@ -131,7 +168,8 @@ ROT_KERNEL(LOGN) void k_rot_modup_conv(const double* __restrict__ y, const KsLev
 // ModDown's first step
 template <int LOGN>
 ROT_KERNEL(LOGN) void k_rot_down_p(RotBatch b, int pre, const KsLevel* __restrict__ kl, const double* __restrict__ digits,
-                                   size_t dig_stride, int key_limbs, double* __restrict__ y, DevTabs tb) {
+                                   size_t dig_stride, int key_limbs, const double* __restrict__ inner,
+                                   double* __restrict__ y, DevTabs tb) {
   constexpr int N = 1 << LOGN, T = NttShape<LOGN>::T;
   __shared__ double s[NttShape<LOGN>::LDS];
   const int alpha = kl->alpha, lv = kl->lv;
@@ -146,7 +184,10 @@ ROT_KERNEL(LOGN) void k_rot_down_p(RotBatch b, int pre, const KsLevel* __restric
   const size_t key_digit = (size_t)2 * key_limbs * N;
   double* dst = y + ((size_t)(2 * it + x) * alpha + k) * N;
   auto store = [&](int c, double v) { dst[c] = canon(mulmod(canon(v + h, m), ih, m), m); };
-  if constexpr (LOGN <= 14) {
+  if (inner) {
+    const auto* src = gmem(inner) + ((size_t)(2 * it + x) * kl->K + lv + 1 + k) * N;
+    ntt_inv_in<LOGN>(s, [&](int t) { return src[t]; }, tb.inv_tw + (size_t)pi * N, tb.perm, m, tb.ninv[pi], store);
+  } else if constexpr (LOGN <= 14) {
     double u[16], c[16];
     rot_inner<LOGN>(u, d, lv + 1 + k, key, key_digit, kl->beta, m);
     slots_to_lds<LOGN>(s, u, m);
@@ -166,7 +207,7 @@ ROT_KERNEL(LOGN) void k_rot_down_p(RotBatch b, int pre, const KsLevel* __restric
 template <int LOGN>
 ROT_KERNEL(LOGN) void k_rot_down_q(RotBatch b, int pre, int add, const KsLevel* __restrict__ kl,
                                    const double* __restrict__ digits, size_t dig_stride, int key_limbs,
-                                   const double* __restrict__ y, DevTabs tb) {
+                                   const double* __restrict__ inner, const double* __restrict__ y, DevTabs tb) {
   constexpr int N = 1 << LOGN, H = N / 2, T = NttShape<LOGN>::T;
   __shared__ double s[NttShape<LOGN>::LDS];
   const int alpha = kl->alpha, lv = kl->lv;
@@ -181,6 +222,7 @@ ROT_KERNEL(LOGN) void k_rot_down_q(RotBatch b, int pre, int add, const KsLevel* 
   const double* yx = y + (size_t)(2 * it + x) * alpha * N;
   const auto* c0 = gmem(ct) + (size_t)i * N;
   const auto* cx = gmem(ct) + (size_t)(x * (lv + 1) + i) * N;
+  const auto* in = gmem(inner) + ((size_t)(2 * it + x) * kl->K + i) * N;
   double* o = b.it[it].out + (size_t)(x * (lv + 1) + i) * N;
   auto conv = [&](int c) {
     double acc = -h;
@@ -189,13 +231,18 @@ ROT_KERNEL(LOGN) void k_rot_down_q(RotBatch b, int pre, int add, const KsLevel* 
   };
   if constexpr (LOGN <= 14) {
     double u[16];
-    rot_inner<LOGN>(u, d, i, key, key_digit, kl->beta, m);
-    if (x == 0) {
+    if (inner) {
+#pragma unroll
+      for (int w = 0; w < 16; ++w) u[w] = in[(int)opaque_tid() + (w >> 1) * T + (w & 1) * H];
+    } else {
+      rot_inner<LOGN>(u, d, i, key, key_digit, kl->beta, m);
+    }
+    if (!inner && x == 0) {
 #pragma unroll
       for (int w = 0; w < 16; ++w)
         u[w] += mulmod(c0[(((int)opaque_tid() + (w >> 1) * T + rot) & (H - 1)) + (w & 1) * H], pmod, m);
     }
-    if (add) {
+    if (!inner && add) {
 #pragma unroll
       for (int w = 0; w < 16; ++w) u[w] += mulmod(cx[(int)opaque_tid() + (w >> 1) * T + (w & 1) * H], pmod, m);
     }
@@ -210,9 +257,14 @@ ROT_KERNEL(LOGN) void k_rot_down_q(RotBatch b, int pre, int add, const KsLevel* 
       o[(int)opaque_tid() + (w >> 1) * T + (w & 1) * H] = reduce(mulmod(u[w] - v[w], pinv, m), m);
   } else {
     ntt_fwd_out<LOGN>(s, conv, tb.fwd_tw + (size_t)i * N, tb.perm, m, [&](int t, double v) {
-      double u = rot_inner_at(d, i, key, key_digit, kl->beta, t, m);
-      if (x == 0) u += mulmod(c0[orbit_shift(t, rot, H)], pmod, m);
-      if (add) u += mulmod(cx[t], pmod, m);
+      double u;
+      if (inner) {
+        u = in[t];
+      } else {
+        u = rot_inner_at(d, i, key, key_digit, kl->beta, t, m);
+        if (x == 0) u += mulmod(c0[orbit_shift(t, rot, H)], pmod, m);
+        if (add) u += mulmod(cx[t], pmod, m);
+      }
       o[t] = reduce(mulmod(reduce(u, m) - v, pinv, m), m);
     });
   }
@@ -268,10 +320,13 @@ static void rotations_impl(const LaunchCtx& L, const RotBatch& b, const RotRun& 
     hipLaunchKernelGGL(k_rot_modup_conv<LOGN>, dim3(b.n * r.n_tasks), block, 0, L.stream, r.yup, kl, r.digits,
                        r.dig_stride, L.tb);
   }
+  if (r.inner)
+    hipLaunchKernelGGL(k_rot_inner, dim3((1 << LOGN) / 256, r.lv + 1 + r.alpha, b.n), dim3(256), 0, L.stream, b, r.pre, r.add,
+                       kl, r.digits, r.dig_stride, r.key_limbs, 1 << LOGN, L.tb.mods, r.inner);
   hipLaunchKernelGGL(k_rot_down_p<LOGN>, dim3(b.n * 2 * r.alpha), block, 0, L.stream, b, r.pre, kl, r.digits,
-                     r.dig_stride, r.key_limbs, r.ydown, L.tb);
+                     r.dig_stride, r.key_limbs, r.inner, r.ydown, L.tb);
   hipLaunchKernelGGL(k_rot_down_q<LOGN>, dim3(b.n * 2 * (r.lv + 1)), block, 0, L.stream, b, r.pre, r.add, kl, r.digits,
-                     r.dig_stride, r.key_limbs, r.ydown, L.tb);
+                     r.dig_stride, r.key_limbs, r.inner, r.ydown, L.tb);
 }
 
 hipError_t launch_rotations(const LaunchCtx& L, const RotBatch& b, const RotRun& r) {
