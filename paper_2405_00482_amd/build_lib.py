@@ -12,7 +12,8 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 OUT = os.path.join(HERE, "libpvfl.so")
 PROBE_OUT = os.path.join(HERE, "libpvfl_probe.so")
-SOURCES = ["he_kernels.hip", "rot_kernels.hip", "diag_kernels.hip", "encode_kernels.hip", "batch.hip", "mlp.hip",
+SOURCES = ["he_kernels.hip", "rot_kernels.hip", "diag_kernels.hip", "encode_kernels.hip", "ring15_kernels.hip",
+           "batch.hip", "mlp.hip",
            "capi.cpp", "plan.cpp", "codec.cpp", "batch.cpp", "mlp_capi.cpp", "planner.cpp"]
 FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-ffp-contract=off",
          "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops", "-Wno-unused-result",

@@ -8,6 +8,7 @@
 #include "batch.hpp"
 #include "encode_dev.hpp"
 #include "he_dev.hpp"
+#include "ring15.hpp"
 
 namespace pvfl {
 
@@ -256,19 +257,8 @@ __global__ __launch_bounds__(NttShape<LOGN>::T) void k_encode_pt_batch(const Enc
 template <int LOGN>
 __global__ __launch_bounds__(NttShape<LOGN>::T) void k_encode_ct_batch(const EncodeArgs* __restrict__ args, EncTabs et,
                                                                        int64_t* __restrict__ msg) {
-  constexpr int N = 1 << LOGN, T = NttShape<LOGN>::T, PH = N / 2 / T;
   __shared__ double2 s2[NttShape<LOGN>::LDS / 2];
-  const int c = blockIdx.x;
-  double mreg[2 * PH];
-  const EncodeArgs a = args[c];
-  encode_to_regs<LOGN, true>(a, 0, s2, mreg, et, a.scale);
-  int64_t* dst = msg + (size_t)c * N;
-#pragma unroll
-  for (int u = 0; u < PH; ++u) {
-    const int kk = threadIdx.x + u * T;
-    dst[kk] = (int64_t)mreg[2 * u];
-    dst[kk + N / 2] = (int64_t)mreg[2 * u + 1];
-  }
+  encode_ct_body<LOGN>(args[blockIdx.x], 0, et, s2, msg + (size_t)blockIdx.x * (1 << LOGN));
 }
 
 // read-out of product p's decoded slots z[p][N/2] into its y (lazy RaS)
@@ -369,8 +359,11 @@ hipError_t launch_sum_partials_batch(const LaunchCtx& L, const double* part, con
 template <int LOGN>
 static void enc_pt_batch_impl(const LaunchCtx& L, const EncodeArgs* args, const int2* work, int nwork,
                               const BatchProd* prods, const EncTabs& et, LimbMap map) {
-  hipLaunchKernelGGL(k_encode_pt_batch<LOGN>, dim3(8 * ((nwork + 7) / 8)), dim3(NttShape<LOGN>::T), 0, L.stream, args,
-                     work, nwork, prods, et, map, L.tb);
+  if constexpr (LOGN == 15)
+    launch15_encode_pt_batch(L, args, work, nwork, prods, et, map);
+  else
+    hipLaunchKernelGGL(k_encode_pt_batch<LOGN>, dim3(8 * ((nwork + 7) / 8)), dim3(NttShape<LOGN>::T), 0, L.stream, args,
+                       work, nwork, prods, et, map, L.tb);
 }
 hipError_t launch_encode_pt_batch(const LaunchCtx& L, const EncodeArgs* args, const int2* work, int nwork,
                                   const BatchProd* prods, const EncTabs& et, LimbMap map) {
@@ -381,7 +374,10 @@ hipError_t launch_encode_pt_batch(const LaunchCtx& L, const EncodeArgs* args, co
 
 template <int LOGN>
 static void enc_ct_batch_impl(const LaunchCtx& L, const EncodeArgs* args, int count, const EncTabs& et, int64_t* msg) {
-  hipLaunchKernelGGL(k_encode_ct_batch<LOGN>, dim3(count), dim3(NttShape<LOGN>::T), 0, L.stream, args, et, msg);
+  if constexpr (LOGN == 15)
+    launch15_encode_ct(L, EncodeArgs{}, args, et, count, msg);
+  else
+    hipLaunchKernelGGL(k_encode_ct_batch<LOGN>, dim3(count), dim3(NttShape<LOGN>::T), 0, L.stream, args, et, msg);
 }
 hipError_t launch_encode_ct_batch(const LaunchCtx& L, const EncodeArgs* args, int count, const EncTabs& et, int64_t* msg) {
   DISPATCH_LOGN(L, enc_ct_batch_impl, L, args, count, et, msg);

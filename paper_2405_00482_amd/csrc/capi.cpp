@@ -261,29 +261,23 @@ extern "C" pvfl_status pvfl_context_create(const pvfl_params* prm, int device, p
       std::copy(iv.begin(), iv.end(), ir);
     }
   }
-  // orbit order t -> bit-reversed index
-  std::vector<uint32_t> perm(N);
   c->log5.assign(2 * N, -1);
   {
     u64 e = 1;
     for (int t = 0; t < N / 2; ++t) {
       c->log5[e] = t;
-      const u64 eneg = (2 * (u64)N - e) % (2 * N);
-      perm[t] = (uint32_t)bit_reverse((int)((e - 1) / 2), c->logN);
-      perm[t + N / 2] = (uint32_t)bit_reverse((int)((eneg - 1) / 2), c->logN);
       e = e * 5 % (2 * (u64)N);
     }
   }
   pvfl_status st;
-  void *d_mods, *d_fwd, *d_inv, *d_ninv, *d_two32, *d_perm;
+  void *d_mods, *d_fwd, *d_inv, *d_ninv, *d_two32;
   if ((st = dev_upload(c.get(), mods.data(), sizeof(ModQ) * nm, &d_mods)) != PVFL_OK) return st;
   if ((st = dev_upload(c.get(), fwd.data(), sizeof(double) * fwd.size(), &d_fwd)) != PVFL_OK) return st;
   if ((st = dev_upload(c.get(), inv.data(), sizeof(double) * inv.size(), &d_inv)) != PVFL_OK) return st;
   if ((st = dev_upload(c.get(), ninv.data(), sizeof(double) * nm, &d_ninv)) != PVFL_OK) return st;
   if ((st = dev_upload(c.get(), two32.data(), sizeof(double) * nm, &d_two32)) != PVFL_OK) return st;
-  if ((st = dev_upload(c.get(), perm.data(), sizeof(uint32_t) * N, &d_perm)) != PVFL_OK) return st;
   c->tabs = DevTabs{(const ModQ*)d_mods, (const double*)d_fwd, (const double*)d_inv, (const double*)d_ninv,
-                    (const double*)d_two32, (const uint32_t*)d_perm, c->logN};
+                    (const double*)d_two32, c->logN};
   c->mods_host = mods;
   // key-switching constants of every level
   c->ks_host.resize(c->n_q);

@@ -353,60 +353,70 @@ __device__ __forceinline__ void fft_split_regs(const double (&v)[8], double2* z,
   __syncthreads();
 }
 
-// slots -> FFT -> rounded coefficients in registers: mreg[2u] = m_k and
-// mreg[2u+1] = m_(k+N/2) for k = tid + u T, u < M/T.  gather(slot_of, v)
-// fills v[u] with the scaled value of slot slot_of(u) for every u of v.  At N = 2^15 the first DIF stage (pairs i, i + M/2, owned
-// by one thread) runs in registers and the two halves in LDS one after the
-// other; half h yields the coefficients with k = h mod 2.
+// slots -> FFT -> rounded coefficients in registers, N <= 2^14: mreg[2u] = m_k
+// and mreg[2u+1] = m_(k+N/2) for k = tid + u T, u < M/T.  gather(slot_of, v)
+// fills v[u] with the scaled value of slot slot_of(u) for every u of v.
 template <int LOGN, class Gather>
 __device__ __forceinline__ void encode_to_regs_v(Gather gather, double2* z, double* mreg, const EncTabs& et) {
   constexpr int N = 1 << LOGN, M = N / 2, T = NttShape<LOGN>::T;
   const int tid = opaque_tid();
-  if constexpr (LOGN <= 14) {
-    // The DFT input x[f] (slot value at f = f_j) is real: pack y[n] = x[2n] +
-    // i x[2n+1], transform M/2 points, and split (real-input FFT):
-    //   E[k] = (Y[k] + conj Y[M/2-k]) / 2,  O[k] = (Y[k] - conj Y[M/2-k]) / 2i,
-    //   X[k] = E[k] + W^k O[k],  X[k + M/2] = E[k] - W^k O[k],  W = exp(-2 pi i / M).
-    // The half transform runs on the first half of the threads with every
-    // other twiddle of the M-point table.
-    constexpr int HM = M / 2, QH = HM / T;  // QH = 4 complex inputs per thread
-    double v[2 * QH];
-    gather([&](int u) { return tid + u * T; }, v);
-    fft_split_regs<LOGN>(v, z, mreg, et);
-  } else {
-    constexpr int HM = M / 2, PH = M / T;
-    const double inv_m = 1.0 / (double)M;
-    double2 v0[HM / T];
+  // The DFT input x[f] (slot value at f = f_j) is real: pack y[n] = x[2n] +
+  // i x[2n+1], transform M/2 points, and split (real-input FFT):
+  //   E[k] = (Y[k] + conj Y[M/2-k]) / 2,  O[k] = (Y[k] - conj Y[M/2-k]) / 2i,
+  //   X[k] = E[k] + W^k O[k],  X[k + M/2] = E[k] - W^k O[k],  W = exp(-2 pi i / M).
+  // The half transform runs on the first half of the threads with every
+  // other twiddle of the M-point table.
+  constexpr int HM = M / 2, QH = HM / T;  // QH = 4 complex inputs per thread
+  double v[2 * QH];
+  gather([&](int u) { return tid + u * T; }, v);
+  fft_split_regs<LOGN>(v, z, mreg, et);
+}
+
+// The same at N = 2^15, coefficient tid + w T handed to put(w, m) as it is
+// made.  The first DIF stage (pairs i, i + M/2, owned by one thread) runs in
+// registers and the two halves in LDS one after the other; half h yields the
+// coefficients with k = h mod 2.  A thread's 32 coefficients do not stay in
+// registers: beside the transform's own values they would spill.  All of a thread's slots are gathered at once.
+template <class Gather, class Put>
+__device__ __forceinline__ void encode15(Gather gather, double2* z, const EncTabs& et, Put put) {
+  constexpr int LOGN = 15, N = 1 << LOGN, M = N / 2, T = NttShape<LOGN>::T, HM = M / 2, PH = M / T, U = HM / T;
+  const int tid = opaque_tid();
+  const double inv_m = 1.0 / (double)M;
+  double2 v0[U];
+  {
+    int slot[2 * U];
 #pragma unroll
-    for (int u = 0; u < HM / T; ++u) {
+    for (int q = 0; q < 2 * U; ++q) slot[q] = (int)et.f2slot[tid + (q >> 1) * T + (q & 1) * HM];
+    double ab[2 * U];
+    gather([&](int q) { return slot[q]; }, ab);
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
       const int i = tid + u * T;
-      double ab[2];
-      gather([&](int j) { return (int)et.f2slot[i + j * HM]; }, ab);
-      const double a0 = ab[0], b0 = ab[1];
+      const double a0 = ab[2 * u], b0 = ab[2 * u + 1];
       z[cpad(i)] = make_double2(a0 + b0, 0.0);
       v0[u] = cmul(make_double2(a0 - b0, 0.0), et.fft_tw[i]);
     }
+  }
 #pragma unroll 1
-    for (int h = 0; h < 2; ++h) {
-      if (h) {
-        __syncthreads();  // half 0's read-out is done
+  for (int h = 0; h < 2; ++h) {
+    if (h) {
+      __syncthreads();  // half 0's read-out is done
 #pragma unroll
-        for (int u = 0; u < HM / T; ++u) z[cpad(tid + u * T)] = v0[u];
-      }
-      __syncthreads();
-      fft_dif_half15(z, et.fft_tw, false);
-      if ((tid & 1) == h) {  // k = tid + u T has the parity of tid
-#pragma unroll
-        for (int u = 0; u < PH; ++u) {
-          const int kk = tid + u * T;
-          const double2 w = cmul(z[cpad(brev(kk, LOGN - 1) - h * HM)], cconj(et.twist[kk]));
-          mreg[2 * u] = round_half_away(w.x * inv_m);
-          mreg[2 * u + 1] = round_half_away(w.y * inv_m);
-        }
-      }
+      for (int u = 0; u < U; ++u) z[cpad(tid + u * T)] = v0[u];
     }
     __syncthreads();
+    fft_dif_half15(z, et.fft_tw, false);
+    if ((tid & 1) == h) {  // k = tid + u T has the parity of tid
+#pragma unroll 4
+      for (int u = 0; u < PH; ++u) {
+        const int kk = tid + u * T;
+        const double2 w = cmul(z[cpad(brev(kk, LOGN - 1) - h * HM)], cconj(et.twist[kk]));
+        put(u, round_half_away(w.x * inv_m));
+        put(u + PH, round_half_away(w.y * inv_m));
+      }
+    }
   }
+  __syncthreads();
 }
 
 template <int LOGN, bool CT>
@@ -415,43 +425,143 @@ __device__ __forceinline__ void encode_to_regs(const EncodeArgs& a, int k, doubl
   encode_to_regs_v<LOGN>([&](auto slot_of, auto& v) { gather_slots<CT>(a, k, scale, slot_of, v); }, z, mreg, et);
 }
 
+// Message of input ciphertext c as int64 coefficients.
+template <int LOGN>
+__device__ __forceinline__ void encode_ct_body(const EncodeArgs& a, int c, const EncTabs& et, double2* s2,
+                                               int64_t* __restrict__ dst) {
+  constexpr int N = 1 << LOGN, T = NttShape<LOGN>::T, PH = N / 2 / T;
+  if constexpr (LOGN <= 14) {
+    double mreg[2 * PH];
+    encode_to_regs<LOGN, true>(a, c, s2, mreg, et, a.scale);
+#pragma unroll
+    for (int u = 0; u < PH; ++u) {
+      const int kk = threadIdx.x + u * T;
+      dst[kk] = (int64_t)mreg[2 * u];
+      dst[kk + N / 2] = (int64_t)mreg[2 * u + 1];
+    }
+  } else {
+    encode15([&](auto slot_of, auto& v) { gather_slots<true>(a, c, a.scale, slot_of, v); }, s2, et,
+             [&](int w, double m) { dst[threadIdx.x + w * T] = (int64_t)m; });
+  }
+}
+
+// Encodes the slots that gather() yields and transforms every limb of `map`,
+// to out[limb][N]; first(c, l) turns the integer coefficients into limb l's
+// input (|x| < 2^51).  s2: LDS of NttShape<LOGN>::LDS doubles.
+template <int LOGN, class Gather, class First, class Store>
+__device__ __forceinline__ void encode_limbs(Gather gather, const EncTabs& et, const LimbMap& map, const DevTabs& tb,
+                                             double2* s2, double* __restrict__ out, First first, Store store) {
+  constexpr int N = 1 << LOGN, T = NttShape<LOGN>::T, PH = N / 2 / T, PER = NttShape<LOGN>::PER;
+  double* s = (double*)s2;
+  if constexpr (LOGN <= 14) {
+    double mreg[2 * PH];
+    encode_to_regs_v<LOGN>(gather, s2, mreg, et);
+    // coefficient tid + w T: w < PH -> m_k (real part), w >= PH -> m_(k+N/2) (imaginary part)
+    for (int l = 0; l < map.n; ++l) {
+      const int pi = map.idx[l];
+      double c[PER];
+#pragma unroll
+      for (int w = 0; w < PER; ++w) c[w] = first(w < PH ? mreg[2 * w] : mreg[2 * (w - PH) + 1], l);
+      double* dst = out + (size_t)l * N;
+      ntt_fwd_regs_out<LOGN>(s, c, tb.fwd_tw + (size_t)pi * N, tb.mods[pi],
+                             [&](int t, double v) { store(dst + t, v); });
+    }
+  } else {
+    // the integer coefficients wait in the last limb's place, where each thread
+    // reads back only what it wrote; that limb is transformed last, and its
+    // first barrier stands between the reads and the output's writes
+    double* park = out + (size_t)(map.n - 1) * N;
+    encode15(gather, s2, et, [&](int w, double m) { park[opaque_tid() + w * T] = m; });
+    for (int l = 0; l < map.n; ++l) {
+      const int pi = map.idx[l];
+      double c[PER];
+#pragma unroll
+      for (int w = 0; w < PER; ++w) c[w] = first(park[opaque_tid() + w * T], l);
+      double* dst = out + (size_t)l * N;
+      ntt_fwd_regs_out<LOGN>(s, c, tb.fwd_tw + (size_t)pi * N, tb.mods[pi],
+                             [&](int t, double v) { store(dst + t, v); });
+    }
+  }
+}
 
 // Plaintext k of a plan: pack, encode, then every limb of `map` reduced and
-// transformed; written to out_pt[limb][N].  s2: LDS of NttShape<LOGN>::LDS doubles.
+// transformed; written to out_pt[limb][N].  |m| < 2^51, which the transform
+// reduces on entry.
 template <int LOGN>
 __device__ __forceinline__ void encode_pt_body(const EncodeArgs& a, int k, const EncTabs& et, const LimbMap& map,
                                                const DevTabs& tb, double2* s2, double* __restrict__ out_pt) {
-  constexpr int N = 1 << LOGN, T = NttShape<LOGN>::T, PH = N / 2 / T, PER = NttShape<LOGN>::PER;
-  double* s = (double*)s2;
-  double mreg[2 * PH];
+  auto same = [](double m, int) { return m; };
+  // the plaintext buffer is device memory: global stores (unlike flat stores
+  // they do not count against the LDS wait counter of the gather before
+  // them), nontemporal because nothing in this kernel reads them again --
+  // they would only push the twiddle tables and X out of L2
+  auto stream = [](double* p, double v) {
+    __builtin_nontemporal_store(v, (__attribute__((address_space(1))) double*)p);
+  };
   if (a.kind == 2 && k == a.m) {
     // ROW indicator plaintext: 1 in slot 0 at scale q_(l-1)
     const double ind = a.ind_scale;
-    encode_to_regs_v<LOGN>(
+    encode_limbs<LOGN>(
         [&](auto slot_of, auto& v) {
 #pragma unroll
           for (int u = 0; u < (int)(sizeof(v) / sizeof(v[0])); ++u) v[u] = slot_of(u) == 0 ? ind : 0.0;
         },
-        s2, mreg, et);
+        et, map, tb, s2, out_pt, same, stream);
   } else {
-    encode_to_regs<LOGN, false>(a, k, s2, mreg, et, a.scale);
+    encode_limbs<LOGN>([&](auto slot_of, auto& v) { gather_slots<false>(a, k, a.scale, slot_of, v); }, et, map, tb, s2,
+                       out_pt, same, stream);
   }
-  // coefficient tid + w T: w < PH -> m_k (real part), w >= PH -> m_(k+N/2) (imaginary part);
-  // |m| < 2^51, which the transform reduces on entry
-  for (int l = 0; l < map.n; ++l) {
-    const int pi = map.idx[l];
-    const ModQ m = tb.mods[pi];
-    double c[PER];
+}
+
+// Value of slot s of output ciphertext b for a cleartext added to the plan's
+// result (mode 0: the m outputs spread by the cleartext inverse RaS of Sec.
+// 5.2, each split into equal parts over the slots its row's lazy RaS adds;
+// mode 1: slot values [ct_out][N/2] as given).  The parts are powers-of-two
+// fractions of v, so the split is exact.
+__device__ __forceinline__ double out_slot_value(const EncodeArgs& a, const double* __restrict__ v, int mode,
+                                                 int ras_in_ct, int b, int s) {
+  if (mode == 1) return v[(size_t)b * a.slots + s];
+  switch (a.kind) {
+    case 0: {  // HYBRID: slot g bn + j adds into row g m' + (j mod m') of block b
+      const int g = s >> a.lbn, j = s & (a.bn - 1);
+      const int row = b * a.bm + (g << a.lmp) + (j & (a.mprime - 1));
+      return row < a.m ? ldexp(v[row], a.lmp - a.lbn) : 0.0;
+    }
+    case 1: {  // DIAG over max(m,n) slots
+      if (a.bm >= a.bn || ras_in_ct) return s < a.m ? v[s] : 0.0;
+      const int r = s & (a.bm - 1);
+      return (s < a.bn && r < a.m) ? ldexp(v[r], __builtin_ctz(a.bm) - a.lbn) : 0.0;
+    }
+    case 4: {  // COL: slot s of output ciphertext b is row b bm + s
+      const int row = b * a.bm + s;
+      return (s < a.bm && row < a.m) ? v[row] : 0.0;
+    }
+    case 3: {  // CTMAT: output ciphertext b, column block blk = s / width
+      const int blk = s >> a.lw, j = s & (a.width - 1), col = b * a.pack + blk;
+      if (blk >= a.pack || col >= a.n_out) return 0.0;
+      if (a.bm >= a.bn) return j < a.m ? v[(size_t)j * a.n_out + col] : 0.0;
+      const int r = j & (a.bm - 1);
+      return (j < a.bn && r < a.m) ? ldexp(v[(size_t)r * a.n_out + col], __builtin_ctz(a.bm) - a.lbn) : 0.0;
+    }
+  }
+  return 0.0;
+}
+
+// Output ciphertext b's cleartext at scale a.scale, rounded, then every limb's
+// residues times fac[l] (2^e mod q) and transformed, to out[limb][N].
+template <int LOGN>
+__device__ __forceinline__ void encode_out_body(const EncodeArgs& a, const double* __restrict__ v, int mode,
+                                                int ras_in_ct, int b, const OutFactors& fac, const EncTabs& et,
+                                                const LimbMap& map, const DevTabs& tb, double2* s2,
+                                                double* __restrict__ out) {
+  encode_limbs<LOGN>(
+      [&](auto slot_of, auto& val) {
 #pragma unroll
-    for (int w = 0; w < PER; ++w) c[w] = w < PH ? mreg[2 * w] : mreg[2 * (w - PH) + 1];
-    // the plaintext buffer is device memory: global stores (unlike flat stores
-    // they do not count against the LDS wait counter of the gather before
-    // them), nontemporal because nothing in this kernel reads them again --
-    // they would only push the twiddle tables and X out of L2
-    auto* dst = (__attribute__((address_space(1))) double*)(out_pt + (size_t)l * N);
-    ntt_fwd_regs_out<LOGN>(s, c, tb.fwd_tw + (size_t)pi * N, tb.perm, m,
-                           [&](int t, double v) { __builtin_nontemporal_store(v, dst + t); });
-  }
+        for (int u = 0; u < (int)(sizeof(val) / sizeof(val[0])); ++u)
+          val[u] = out_slot_value(a, v, mode, ras_in_ct, b, slot_of(u)) * a.scale;
+      },
+      et, map, tb, s2, out, [&](double m, int l) { return mulmod(m, fac.f[l], tb.mods[map.idx[l]]); },
+      [](double* p, double x) { *p = x; });
 }
 
 }  // namespace pvfl

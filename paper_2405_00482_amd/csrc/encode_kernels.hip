@@ -13,6 +13,7 @@
 #include <stdint.h>
 
 #include "encode_dev.hpp"
+#include "ring15.hpp"
 
 namespace pvfl {
 
@@ -28,18 +29,8 @@ __global__ __launch_bounds__(NttShape<LOGN>::T) void k_encode_pt(EncodeArgs a, E
 // Input ciphertext messages: one workgroup per ciphertext, int64 coefficients
 template <int LOGN>
 __global__ __launch_bounds__(NttShape<LOGN>::T) void k_encode_ct_msg(EncodeArgs a, EncTabs et, int64_t* __restrict__ msg) {
-  constexpr int N = 1 << LOGN, T = NttShape<LOGN>::T, PH = N / 2 / T;
   __shared__ double2 s2[NttShape<LOGN>::LDS / 2];
-  const int c = blockIdx.x;
-  double mreg[2 * PH];
-  encode_to_regs<LOGN, true>(a, c, s2, mreg, et, a.scale);
-  int64_t* dst = msg + (size_t)c * N;
-#pragma unroll
-  for (int u = 0; u < PH; ++u) {
-    const int kk = threadIdx.x + u * T;
-    dst[kk] = (int64_t)mreg[2 * u];
-    dst[kk + N / 2] = (int64_t)mreg[2 * u + 1];
-  }
+  encode_ct_body<LOGN>(a, (int)blockIdx.x, et, s2, msg + (size_t)blockIdx.x * (1 << LOGN));
 }
 
 // Output idx of a plan from its decoded slots slot(c, j) (output ciphertext
@@ -107,107 +98,13 @@ __global__ __launch_bounds__(NttShape<LOGN>::T) void k_decode_readout(const doub
   }
 }
 
-// Decode alone at N = 2^15: slots z[c][j] = Re(.)/scale.  The first DIF stage
-// (pairs k, k + M/2) runs in registers, then the two halves in LDS.
-__global__ __launch_bounds__(NttShape<15>::T) void k_decode15(const double* __restrict__ res, int lv, CrtTabs ct,
-                                                              EncTabs et, double inv_scale, double* __restrict__ z) {
-  constexpr int LOGN = 15, N = 1 << LOGN, M = N / 2, T = NttShape<LOGN>::T, HM = M / 2;
-  __shared__ double2 w[NttShape<LOGN>::LDS / 2];
-  const int c = blockIdx.x;
-  const double* base = res + (size_t)c * (lv + 1) * N;
-  const int nl = lv + 1;
-  double* zc = z + (size_t)c * M;
-  double2 v0[HM / T];
-  with_limbs(nl, [&](auto nl_c) {
-    constexpr int NL = decltype(nl_c)::value;
-    // twisted w_k = (m_k + i m_(k+N/2)) zeta^k
-    auto twisted = [&](int k) {
-      return cmul(make_double2(crt_lift<NL>(base, k, N, ct, nl), crt_lift<NL>(base, k + M, N, ct, nl)), et.twist[k]);
-    };
-#pragma unroll
-    for (int u = 0; u < HM / T; ++u) {
-      const int k = threadIdx.x + u * T;
-      const double2 a0 = twisted(k), b0 = twisted(k + HM);
-      w[cpad(k)] = make_double2(a0.x + b0.x, a0.y + b0.y);
-      v0[u] = cmul(make_double2(a0.x - b0.x, a0.y - b0.y), cconj(et.fft_tw[k]));
-    }
-  });
-#pragma unroll 1
-  for (int h = 0; h < 2; ++h) {
-    if (h) {
-      __syncthreads();  // half 0's read-out is done
-#pragma unroll
-      for (int u = 0; u < HM / T; ++u) w[cpad(threadIdx.x + u * T)] = v0[u];
-    }
-    __syncthreads();
-    fft_dif_half15(w, et.fft_tw, true);
-    for (int j = threadIdx.x; j < M; j += T) {
-      const int r = brev(et.slot2f[j], LOGN - 1);
-      if ((r >> (LOGN - 2)) == h) zc[j] = w[cpad(r - h * HM)].x * inv_scale;
-    }
-  }
-}
-
-// Value of slot s of output ciphertext b for a cleartext added to the plan's
-// result (mode 0: the m outputs spread by the cleartext inverse RaS of Sec.
-// 5.2, each split into equal parts over the slots its row's lazy RaS adds;
-// mode 1: slot values [ct_out][N/2] as given).  The parts are powers-of-two
-// fractions of v, so the split is exact.
-__device__ __forceinline__ double out_slot_value(const EncodeArgs& a, const double* __restrict__ v, int mode,
-                                                 int ras_in_ct, int b, int s) {
-  if (mode == 1) return v[(size_t)b * a.slots + s];
-  switch (a.kind) {
-    case 0: {  // HYBRID: slot g bn + j adds into row g m' + (j mod m') of block b
-      const int g = s >> a.lbn, j = s & (a.bn - 1);
-      const int row = b * a.bm + (g << a.lmp) + (j & (a.mprime - 1));
-      return row < a.m ? ldexp(v[row], a.lmp - a.lbn) : 0.0;
-    }
-    case 1: {  // DIAG over max(m,n) slots
-      if (a.bm >= a.bn || ras_in_ct) return s < a.m ? v[s] : 0.0;
-      const int r = s & (a.bm - 1);
-      return (s < a.bn && r < a.m) ? ldexp(v[r], __builtin_ctz(a.bm) - a.lbn) : 0.0;
-    }
-    case 4: {  // COL: slot s of output ciphertext b is row b bm + s
-      const int row = b * a.bm + s;
-      return (s < a.bm && row < a.m) ? v[row] : 0.0;
-    }
-    case 3: {  // CTMAT: output ciphertext b, column block blk = s / width
-      const int blk = s >> a.lw, j = s & (a.width - 1), col = b * a.pack + blk;
-      if (blk >= a.pack || col >= a.n_out) return 0.0;
-      if (a.bm >= a.bn) return j < a.m ? v[(size_t)j * a.n_out + col] : 0.0;
-      const int r = j & (a.bm - 1);
-      return (j < a.bn && r < a.m) ? ldexp(v[(size_t)r * a.n_out + col], __builtin_ctz(a.bm) - a.lbn) : 0.0;
-    }
-  }
-  return 0.0;
-}
-
-// One workgroup per output ciphertext: the cleartext at scale a.scale,
-// rounded, then every limb's residues times fac[l] (2^e mod q) and transformed.
 template <int LOGN>
 __global__ __launch_bounds__(NttShape<LOGN>::T) void k_encode_out(EncodeArgs a, const double* __restrict__ v, int mode,
                                                                   int ras_in_ct, OutFactors fac, EncTabs et, LimbMap map,
                                                                   DevTabs tb, double* __restrict__ out) {
-  constexpr int N = 1 << LOGN, T = NttShape<LOGN>::T, PH = N / 2 / T, PER = NttShape<LOGN>::PER;
   __shared__ double2 s2[NttShape<LOGN>::LDS / 2];
-  const int b = blockIdx.x;
-  double mreg[2 * PH];
-  encode_to_regs_v<LOGN>(
-      [&](auto slot_of, auto& val) {
-#pragma unroll
-        for (int u = 0; u < (int)(sizeof(val) / sizeof(val[0])); ++u)
-          val[u] = out_slot_value(a, v, mode, ras_in_ct, b, slot_of(u)) * a.scale;
-      },
-      s2, mreg, et);
-  double* s = (double*)s2;
-  for (int l = 0; l < map.n; ++l) {
-    const ModQ m = tb.mods[map.idx[l]];
-    double c[PER];
-#pragma unroll
-    for (int w = 0; w < PER; ++w) c[w] = mulmod(w < PH ? mreg[2 * w] : mreg[2 * (w - PH) + 1], fac.f[l], m);
-    double* dst = out + ((size_t)b * map.n + l) * N;
-    ntt_fwd_regs_out<LOGN>(s, c, tb.fwd_tw + (size_t)map.idx[l] * N, tb.perm, m, [&](int t, double x) { dst[t] = x; });
-  }
+  encode_out_body<LOGN>(a, v, mode, ras_in_ct, (int)blockIdx.x, fac, et, map, tb, s2,
+                        out + (size_t)blockIdx.x * map.n * (1 << LOGN));
 }
 
 // out c0 = ct c0 + sign * pt, c1 copied, on nct ciphertexts of lv+1 limbs
@@ -237,17 +134,26 @@ __global__ __launch_bounds__(256) void k_readout(const double* __restrict__ z, E
 // ---------------------------------------------------------------------------
 template <int LOGN>
 static void encode_pt_impl(const LaunchCtx& L, const EncodeArgs& a, const EncTabs& et, LimbMap map, int count, double* out) {
-  hipLaunchKernelGGL(k_encode_pt<LOGN>, dim3(count), dim3(NttShape<LOGN>::T), 0, L.stream, a, et, map, L.tb, out);
+  if constexpr (LOGN == 15)
+    launch15_encode_pt(L, a, et, map, count, out);
+  else
+    hipLaunchKernelGGL(k_encode_pt<LOGN>, dim3(count), dim3(NttShape<LOGN>::T), 0, L.stream, a, et, map, L.tb, out);
 }
 template <int LOGN>
 static void encode_out_impl(const LaunchCtx& L, const EncodeArgs& a, const double* v, int mode, int ras_in_ct,
                             const OutFactors& fac, const EncTabs& et, LimbMap map, int count, double* out) {
-  hipLaunchKernelGGL(k_encode_out<LOGN>, dim3(count), dim3(NttShape<LOGN>::T), 0, L.stream, a, v, mode, ras_in_ct, fac,
-                     et, map, L.tb, out);
+  if constexpr (LOGN == 15)
+    launch15_encode_out(L, a, v, mode, ras_in_ct, fac, et, map, count, out);
+  else
+    hipLaunchKernelGGL(k_encode_out<LOGN>, dim3(count), dim3(NttShape<LOGN>::T), 0, L.stream, a, v, mode, ras_in_ct, fac,
+                       et, map, L.tb, out);
 }
 template <int LOGN>
 static void encode_ct_impl(const LaunchCtx& L, const EncodeArgs& a, const EncTabs& et, int count, int64_t* msg) {
-  hipLaunchKernelGGL(k_encode_ct_msg<LOGN>, dim3(count), dim3(NttShape<LOGN>::T), 0, L.stream, a, et, msg);
+  if constexpr (LOGN == 15)
+    launch15_encode_ct(L, a, nullptr, et, count, msg);
+  else
+    hipLaunchKernelGGL(k_encode_ct_msg<LOGN>, dim3(count), dim3(NttShape<LOGN>::T), 0, L.stream, a, et, msg);
 }
 template <int LOGN>
 static void decode_readout_impl(const LaunchCtx& L, const double* res, int nct, int lv, const CrtTabs& ct,
@@ -274,12 +180,6 @@ hipError_t launch_encode_pt(const LaunchCtx& L, const EncodeArgs& a, const EncTa
 }
 hipError_t launch_encode_ct(const LaunchCtx& L, const EncodeArgs& a, const EncTabs& et, int count, int64_t* msg) {
   DISPATCH_LOGN(L, encode_ct_impl, L, a, et, count, msg);
-  return hipGetLastError();
-}
-hipError_t launch_decode15(const LaunchCtx& L, const double* res, int nct, int lv, const CrtTabs& ct, const EncTabs& et,
-                           double inv_scale, double* z) {
-  if (L.logN != 15) return hipErrorInvalidValue;
-  hipLaunchKernelGGL(k_decode15, dim3(nct), dim3(NttShape<15>::T), 0, L.stream, res, lv, ct, et, inv_scale, z);
   return hipGetLastError();
 }
 hipError_t launch_decode_readout(const LaunchCtx& L, const double* res, int nct, int lv, const CrtTabs& ct,

@@ -30,7 +30,7 @@ NTT_KERNEL(LOGN) void k_ntt_fwd(const double* __restrict__ in, double* __restric
   const ModQ m = tb.mods[pi];
   const double* src = in + (size_t)b * N;
   double* dst = out + (size_t)b * N;
-  ntt_fwd_out<LOGN>(s, [&](int j) { return src[j]; }, tb.fwd_tw + (size_t)pi * N, tb.perm, m,
+  ntt_fwd_out<LOGN>(s, [&](int j) { return src[j]; }, tb.fwd_tw + (size_t)pi * N, m,
                     [&](int t, double v) { dst[t] = v; });
 }
 
@@ -42,7 +42,7 @@ NTT_KERNEL(LOGN) void k_ntt_inv(const double* __restrict__ in, double* __restric
   const ModQ m = tb.mods[pi];
   const double* src = in + (size_t)b * N;
   double* dst = out + (size_t)b * N;
-  ntt_inv_in<LOGN>(s, [&](int t) { return src[t]; }, tb.inv_tw + (size_t)pi * N, tb.perm, m, tb.ninv[pi],
+  ntt_inv_in<LOGN>(s, [&](int t) { return src[t]; }, tb.inv_tw + (size_t)pi * N, m, tb.ninv[pi],
                    [&](int j, double v) { dst[j] = v; });
 }
 
@@ -57,7 +57,7 @@ NTT_KERNEL(LOGN) void k_import_i64(const int64_t* __restrict__ in, double* __res
   const double t32 = tb.two32[pi];
   const int64_t* src = in + (size_t)c * N;
   double* dst = out + (size_t)b * N;
-  ntt_fwd_out<LOGN>(s, [&](int j) { return i64_to_res(src[j], m, t32); }, tb.fwd_tw + (size_t)pi * N, tb.perm, m,
+  ntt_fwd_out<LOGN>(s, [&](int j) { return i64_to_res(src[j], m, t32); }, tb.fwd_tw + (size_t)pi * N, m,
                     [&](int t, double v) { dst[t] = v; });
 }
 
@@ -90,7 +90,7 @@ NTT_KERNEL(LOGN) void k_import_i64_poly(const int64_t* __restrict__ in, double* 
     for (int w = 0; w < 16; ++w) x[w] = reduce(mulmod(reduce(hi[w], m), t32, m) + lo[w], m);  // as i64_to_res
     double* dst = out + ((size_t)c * map.n + l) * N;
     // nothing in this kernel reads the output again: stream it past L2
-    ntt_fwd_regs_out<LOGN>(s, x, tb.fwd_tw + (size_t)pi * N, tb.perm, m,
+    ntt_fwd_regs_out<LOGN>(s, x, tb.fwd_tw + (size_t)pi * N, m,
                            [&](int t, double y) { __builtin_nontemporal_store(y, dst + t); });
   }
 }
@@ -104,7 +104,7 @@ NTT_KERNEL(LOGN) void k_export_u64(const double* __restrict__ in, uint64_t* __re
   const ModQ m = tb.mods[pi];
   const double* src = in + (size_t)b * N;
   uint64_t* dst = out + (size_t)b * N;
-  ntt_inv_in<LOGN>(s, [&](int t) { return src[t]; }, tb.inv_tw + (size_t)pi * N, tb.perm, m, tb.ninv[pi],
+  ntt_inv_in<LOGN>(s, [&](int t) { return src[t]; }, tb.inv_tw + (size_t)pi * N, m, tb.ninv[pi],
                    [&](int j, double v) { dst[j] = f64_to_u64(canon(v, m)); });
 }
 
@@ -169,7 +169,7 @@ NTT_KERNEL(LOGN) void k_keygen(uint64_t seed, double* __restrict__ sk, DevTabs t
   const ModQ m = tb.mods[pi];
   double* dst = sk + (size_t)pi * N;
   ntt_fwd_out<LOGN>(s, [&](int j) { return (double)sample_ternary(seed, kStreamSecret, (uint64_t)j); },
-                    tb.fwd_tw + (size_t)pi * N, tb.perm, m, [&](int t, double v) { dst[t] = v; });
+                    tb.fwd_tw + (size_t)pi * N, m, [&](int t, double v) { dst[t] = v; });
 }
 
 // secret-key encryption of integer coefficients m (c1 = a, c0 = -a s + m + e)
@@ -190,13 +190,13 @@ NTT_KERNEL(LOGN) void k_encrypt(const int64_t* __restrict__ msg, const double* _
   double* c1 = ct + (size_t)(lv + 1 + i) * N;
   // a, sampled in the coefficient domain
   ntt_fwd_out<LOGN>(s, [&](int j) { return sample_uniform_res(seed, kStreamEncA | (uint64_t)i, j, qi); },
-                    tb.fwd_tw + (size_t)i * N, tb.perm, m, [&](int t, double v) { c1[t] = v; });
+                    tb.fwd_tw + (size_t)i * N, m, [&](int t, double v) { c1[t] = v; });
   const double t32 = tb.two32[i];
   const double* sk_i = sk + (size_t)i * N;
   // c0 = m + e - a s; slot t of a is read back from what this thread wrote above
   ntt_fwd_out<LOGN>(s, [&](int j) {
       return reduce(i64_to_res(mc[j], m, t32) + (double)sample_cbd21(seed, kStreamEncE, (uint64_t)j), m);
-    }, tb.fwd_tw + (size_t)i * N, tb.perm, m,
+    }, tb.fwd_tw + (size_t)i * N, m,
     [&](int t, double v) { c0[t] = reduce(v - mulmod(c1[t], sk_i[t], m), m); });
 }
 
@@ -212,11 +212,11 @@ NTT_KERNEL(LOGN) void k_pk_gen(const double* __restrict__ sk, uint64_t seed, int
   double* b = pk + (size_t)i * N;
   double* a = pk + (size_t)(nl + i) * N;
   ntt_fwd_out<LOGN>(s, [&](int j) { return sample_uniform_res(seed, kStreamPkA | (uint64_t)i, j, qi); },
-                    tb.fwd_tw + (size_t)i * N, tb.perm, m, [&](int t, double v) { a[t] = v; });
+                    tb.fwd_tw + (size_t)i * N, m, [&](int t, double v) { a[t] = v; });
   const double* sk_i = sk + (size_t)i * N;
   // slot t of a is read back from what this thread wrote above
   ntt_fwd_out<LOGN>(s, [&](int j) { return (double)sample_cbd21(seed, kStreamPkE, (uint64_t)j); },
-                    tb.fwd_tw + (size_t)i * N, tb.perm, m,
+                    tb.fwd_tw + (size_t)i * N, m,
                     [&](int t, double v) { b[t] = reduce(v - mulmod(a[t], sk_i[t], m), m); });
 }
 
@@ -239,14 +239,14 @@ NTT_KERNEL(LOGN) void k_encrypt_pk(const int64_t* __restrict__ msg, const double
   // v in the evaluation domain, parked in c1; every later read of slot t is by
   // the thread that wrote it
   ntt_fwd_out<LOGN>(s, [&](int j) { return (double)sample_ternary(seed, kStreamPkV, (uint64_t)j); },
-                    tb.fwd_tw + (size_t)i * N, tb.perm, m, [&](int t, double v) { c1[t] = v; });
+                    tb.fwd_tw + (size_t)i * N, m, [&](int t, double v) { c1[t] = v; });
   const double t32 = tb.two32[i];
   ntt_fwd_out<LOGN>(s, [&](int j) {
       return reduce(i64_to_res(mc[j], m, t32) + (double)sample_cbd21(seed, kStreamPkE0, (uint64_t)j), m);
-    }, tb.fwd_tw + (size_t)i * N, tb.perm, m,
+    }, tb.fwd_tw + (size_t)i * N, m,
     [&](int t, double v) { c0[t] = reduce(v + mulmod(c1[t], b[t], m), m); });
   ntt_fwd_out<LOGN>(s, [&](int j) { return (double)sample_cbd21(seed, kStreamPkE1, (uint64_t)j); },
-                    tb.fwd_tw + (size_t)i * N, tb.perm, m,
+                    tb.fwd_tw + (size_t)i * N, m,
                     [&](int t, double v) { c1[t] = reduce(v + mulmod(c1[t], a[t], m), m); });
 }
 
@@ -262,7 +262,7 @@ NTT_KERNEL(LOGN) void k_decrypt_u64(const double* __restrict__ ct, const double*
   const double* c1 = ct + (size_t)(lv + 1 + i) * N;
   const double* sk_i = sk + (size_t)i * N;
   uint64_t* dst = out + (size_t)i * N;
-  ntt_inv_in<LOGN>(s, [&](int t) { return c0[t] + mulmod(c1[t], sk_i[t], m); }, tb.inv_tw + (size_t)i * N, tb.perm,
+  ntt_inv_in<LOGN>(s, [&](int t) { return c0[t] + mulmod(c1[t], sk_i[t], m); }, tb.inv_tw + (size_t)i * N,
                    m, tb.ninv[i], [&](int j, double v) { dst[j] = f64_to_u64(canon(v, m)); });
 }
 
@@ -280,7 +280,7 @@ NTT_KERNEL(LOGN) void k_decrypt_f64(const double* __restrict__ ct, const double*
   const double* c1 = base + (size_t)(lv + 1 + i) * N;
   const double* sk_i = sk + (size_t)i * N;
   double* dst = out + ((size_t)c * (lv + 1) + i) * N;
-  ntt_inv_in<LOGN>(s, [&](int t) { return c0[t] + mulmod(c1[t], sk_i[t], m); }, tb.inv_tw + (size_t)i * N, tb.perm,
+  ntt_inv_in<LOGN>(s, [&](int t) { return c0[t] + mulmod(c1[t], sk_i[t], m); }, tb.inv_tw + (size_t)i * N,
                    m, tb.ninv[i], [&](int j, double v) { dst[j] = canon(v, m); });
 }
 
@@ -305,14 +305,14 @@ NTT_KERNEL(LOGN) void k_rotkey_gen(const double* __restrict__ sk, RotKeyList lis
   double* kb = keys + ((((size_t)kk * ka.beta + j) * 2 + 0) * nlimb + r) * N;
   double* kaout = keys + ((((size_t)kk * ka.beta + j) * 2 + 1) * nlimb + r) * N;
   ntt_fwd_out<LOGN>(s, [&](int k) { return sample_uniform_res(seed, sa, k, (uint64_t)m.q); },
-                    tb.fwd_tw + (size_t)r * N, tb.perm, m, [&](int t, double v) { kaout[t] = v; });
+                    tb.fwd_tw + (size_t)r * N, m, [&](int t, double v) { kaout[t] = v; });
   const double* sk_r = sk + (size_t)r * N;
   const bool in_digit = (r < ka.n_q) && (r / ka.alpha == j);
   const double pmod = ka.P_mod[r];
   const int half = N / 2;
   // b = e - a s (+ P phi_g(s) on the digit's own limbs); a read back from this thread's writes
   ntt_fwd_out<LOGN>(s, [&](int k) { return (double)sample_cbd21(seed, se, (uint64_t)k); }, tb.fwd_tw + (size_t)r * N,
-                    tb.perm, m, [&](int t, double e) {
+                    m, [&](int t, double e) {
                       double v = e - mulmod(kaout[t], sk_r[t], m);
                       if (in_digit) v += mulmod(pmod, sk_r[orbit_shift(t, rot, half)], m);
                       kb[t] = reduce(v, m);
@@ -337,7 +337,7 @@ NTT_KERNEL(LOGN) void k_modup_intt(const double* __restrict__ ct, const double* 
   const double* c1 = (ct_tab ? ct_tab[c] : ct + (size_t)c * ct_stride) + (size_t)(lv + 1 + i) * N;
   const double ih = kl->up_inv_hat[i];
   double* dst = y + ((size_t)c * (lv + 1) + i) * N;
-  ntt_inv_in<LOGN>(s, [&](int t) { return c1[t]; }, tb.inv_tw + (size_t)i * N, tb.perm, m, tb.ninv[i],
+  ntt_inv_in<LOGN>(s, [&](int t) { return c1[t]; }, tb.inv_tw + (size_t)i * N, m, tb.ninv[i],
                    [&](int j, double v) { dst[j] = canon(mulmod(canon(v, m), ih, m), m); });
 }
 
@@ -366,7 +366,7 @@ NTT_KERNEL(LOGN) void k_modup_conv(const double* __restrict__ y, const double* _
       double acc = 0.0;
       for (int u = 0; u < nsrc; ++u) acc += mulmod(yc[(size_t)(src0 + u) * N + j], task.hat[u], m);
       return reduce(acc, m);
-    }, tb.fwd_tw + (size_t)pi * N, tb.perm, m, [&](int t, double v) { dst[t] = v; });
+    }, tb.fwd_tw + (size_t)pi * N, m, [&](int t, double v) { dst[t] = v; });
 }
 
 // ---------------------------------------------------------------------------
@@ -389,7 +389,7 @@ NTT_KERNEL(LOGN) void k_moddown_p(const double* __restrict__ u, const KsLevel* _
   const double h = kl->down_half[lv + 1 + k];
   const double ih = kl->down_inv_hat[k];
   double* dst = y + ((size_t)x * alpha + k) * N;
-  ntt_inv_in<LOGN>(s, [&](int t) { return src[t]; }, tb.inv_tw + (size_t)pi * N, tb.perm, m, tb.ninv[pi],
+  ntt_inv_in<LOGN>(s, [&](int t) { return src[t]; }, tb.inv_tw + (size_t)pi * N, m, tb.ninv[pi],
                    [&](int c, double v) { dst[c] = canon(mulmod(canon(v + h, m), ih, m), m); });
 }
 
@@ -425,7 +425,7 @@ NTT_KERNEL(LOGN) void k_moddown_q(const double* __restrict__ u, const double* __
     for (int w = 0; w < 16; ++w)
       oi[(int)opaque_tid() + (w >> 1) * T + (w & 1) * (N / 2)] = reduce(mulmod(uv[w] - v[w], pinv, m), m);
   } else {
-    ntt_fwd_out<LOGN>(s, conv, tb.fwd_tw + (size_t)i * N, tb.perm, m,
+    ntt_fwd_out<LOGN>(s, conv, tb.fwd_tw + (size_t)i * N, m,
                       [&](int t, double v) { oi[t] = reduce(mulmod(ui[t] - v, pinv, m), m); });
   }
 }
@@ -449,10 +449,10 @@ NTT_KERNEL(LOGN) void k_rescale(const double* __restrict__ in, size_t in_stride,
   const double* plast = pp + (size_t)lv * N;
   double c[PER];
   if (pp)
-    ntt_inv_in_regs<LOGN>(s, [&](int t) { return mulmod(last[t], plast[t], ml); }, tb.inv_tw + (size_t)lv * N, tb.perm,
+    ntt_inv_in_regs<LOGN>(s, [&](int t) { return mulmod(last[t], plast[t], ml); }, tb.inv_tw + (size_t)lv * N,
                           ml, tb.ninv[lv], c);
   else
-    ntt_inv_in_regs<LOGN>(s, [&](int t) { return last[t]; }, tb.inv_tw + (size_t)lv * N, tb.perm, ml, tb.ninv[lv], c);
+    ntt_inv_in_regs<LOGN>(s, [&](int t) { return last[t]; }, tb.inv_tw + (size_t)lv * N, ml, tb.ninv[lv], c);
   const double hl = ra.half_mod_last, hi = ra.half_mod[i];
   // [c + h]_{q_l} lifted to q_i, minus h mod q_i
 #pragma unroll
@@ -474,7 +474,7 @@ NTT_KERNEL(LOGN) void k_rescale(const double* __restrict__ in, size_t in_stride,
     for (int w = 0; w < 16; ++w)
       oi[(int)opaque_tid() + (w >> 1) * T + (w & 1) * (N / 2)] = reduce(mulmod(u[w] - v[w], inv, m), m);
   } else {
-    ntt_fwd_regs_out<LOGN>(s, c, tb.fwd_tw + (size_t)i * N, tb.perm, m, [&](int t, double v) {
+    ntt_fwd_regs_out<LOGN>(s, c, tb.fwd_tw + (size_t)i * N, m, [&](int t, double v) {
       const double u = pp ? mulmod(ui[t], pi[t], m) : ui[t];
       oi[t] = reduce(mulmod(u - v, inv, m), m);
     });

@@ -18,7 +18,7 @@
 // and ntt_inv_regs).  The LDS array is padded by one double every 16 (lds_pad)
 // so that the strided set loads of every pass are close to bank-conflict
 // free.  The orbit-order permutation is computed from powers of 5 (OrbitWalk)
-// rather than read from a table, up to N = 2^14.
+// rather than read from a table.
 //
 // Value ranges (q < 2^48): inputs may be any integers with |x| < 2^51.  A
 // twiddle mulmod of |a| <= 2^51 by a centred twiddle returns |r| <= 0.875 q
@@ -40,7 +40,6 @@ struct DevTabs {
   const double* inv_tw;    // [n_mod][N]  psi^-brv(k), centred
   const double* ninv;      // [n_mod]     N^-1 mod q, centred
   const double* two32;     // [n_mod]     2^32 mod q, centred
-  const uint32_t* perm;    // [N]         orbit index t -> bit-reversed index
   int logN;
 };
 
@@ -345,26 +344,27 @@ __device__ __forceinline__ void ntt_inv(double* s, Store store, const double* __
 }
 
 
-// Orbit order <-> bit-reversed index, computed instead of read from the
-// table (2^12 <= N <= 2^14).  Slot t < N/2 holds the exponent e = 5^t mod 2N,
-// at bit-reversed index brv((e - 1) / 2); slot t + N/2 holds -e, at the
-// complement (N - 1) - brv((e - 1) / 2).  A thread's slots t = tid + w N/16
-// have e = 5^tid (5^(N/16))^w: as 2N is a power of two every product is
-// exact in 32 bits and the reduction is a mask.
+// Orbit order <-> bit-reversed index, computed instead of read from a table.
+// Slot t < N/2 holds the exponent e = 5^t mod 2N, at bit-reversed index
+// brv((e - 1) / 2); slot t + N/2 holds -e, at the complement (N - 1) -
+// brv((e - 1) / 2).  A thread's slots t = tid + w T (T threads) have e =
+// 5^tid (5^T)^w: as 2N is a power of two every product is exact in 32 bits
+// and the reduction is a mask.
 template <int LOGN>
-constexpr uint32_t pow5_step() {  // 5^(N/16) mod 2N
+constexpr uint32_t pow5_step() {  // 5^T mod 2N
   uint32_t r = 1;
-  for (int i = 0; i < (1 << LOGN) / 16; ++i) r = (r * 5u) & ((2u << LOGN) - 1u);
+  for (int i = 0; i < NttShape<LOGN>::T; ++i) r = (r * 5u) & ((2u << LOGN) - 1u);
   return r;
 }
+constexpr int ilog2_c(int x) { return x <= 1 ? 0 : 1 + ilog2_c(x / 2); }
 struct OrbitWalk {
-  uint32_t e;  // 5^(tid + w N/16) mod 2N for the thread's current w
+  uint32_t e;  // 5^(tid + w T) mod 2N for the thread's current w
   template <int LOGN>
-  __device__ __forceinline__ static OrbitWalk start() {  // 5^tid mod 2N, tid < N/16
+  __device__ __forceinline__ static OrbitWalk start() {  // 5^tid mod 2N, tid < T
     const uint32_t mask = (2u << LOGN) - 1u, tid = opaque_tid();
     uint32_t r = 1, b = 5;
 #pragma unroll
-    for (int k = 0; k < LOGN - 4; ++k) {
+    for (int k = 0; k < ilog2_c(NttShape<LOGN>::T); ++k) {
       if ((tid >> k) & 1u) r = (r * b) & mask;
       b = (b * b) & mask;
     }
@@ -420,8 +420,7 @@ __device__ __forceinline__ void slots_from_lds(const double* s, double (&v)[16])
 // ---------------------------------------------------------------------------
 template <int LOGN, class Out>
 __device__ __forceinline__ void ntt_fwd_regs_out(double* s, const double (&c)[NttShape<LOGN>::PER],
-                                                 const double* __restrict__ tw, const uint32_t* __restrict__ perm,
-                                                 ModQ m, Out out) {
+                                                 const double* __restrict__ tw, ModQ m, Out out) {
   constexpr int N = 1 << LOGN, T = NttShape<LOGN>::T;
   if constexpr (LOGN <= 14) {
     ntt_fwd_regs<LOGN>(s, c, tw, m);
@@ -459,7 +458,21 @@ __device__ __forceinline__ void ntt_fwd_regs_out(double* s, const double (&c)[Nt
         x[w] = h ? U - V : U + V;
       }
       ntt_fwd_regs<14>(s, x, tw + h * H, m);
-      for (int t = h * (N / 2) + (int)opaque_tid(); t < (h + 1) * (N / 2); t += T) out(t, s[lds_pad(perm[t] - h * H)]);
+      // slot t of half 0 sits at an index below H, slot t + N/2 at its
+      // complement: the same walk for both halves, four slots at a time
+      OrbitWalk ow = OrbitWalk::start<LOGN>();
+#pragma unroll 1
+      for (int w = 0; w < 16; w += 4) {
+        double v[4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+          const int j = ow.brv_index<LOGN>();
+          v[u] = s[lds_pad(h ? H - 1 - j : j)];
+          ow.next<LOGN>();
+        }
+#pragma unroll
+        for (int u = 0; u < 4; ++u) out(h * (N / 2) + (int)opaque_tid() + (w + u) * T, v[u]);
+      }
     }
   }
 }
@@ -467,12 +480,12 @@ __device__ __forceinline__ void ntt_fwd_regs_out(double* s, const double (&c)[Nt
 // forward transform of the coefficients load(j), handing slot t to out(t, v)
 template <int LOGN, class Load, class Out>
 __device__ __forceinline__ void ntt_fwd_out(double* s, Load load, const double* __restrict__ tw,
-                                            const uint32_t* __restrict__ perm, ModQ m, Out out) {
+                                            ModQ m, Out out) {
   constexpr int T = NttShape<LOGN>::T, PER = NttShape<LOGN>::PER;
   double c[PER];
 #pragma unroll
   for (int w = 0; w < PER; ++w) c[w] = load((int)opaque_tid() + w * T);
-  ntt_fwd_regs_out<LOGN>(s, c, tw, perm, m, out);
+  ntt_fwd_regs_out<LOGN>(s, c, tw, m, out);
 }
 
 // Inverse transform of the orbit-order values in(t) (|x| < 2^51); c[w] gets
@@ -480,7 +493,7 @@ __device__ __forceinline__ void ntt_fwd_out(double* s, Load load, const double* 
 // threads on return: barrier before writing `s` again.
 template <int LOGN, class In>
 __device__ __forceinline__ void ntt_inv_in_regs(double* s, In in, const double* __restrict__ itw,
-                                                const uint32_t* __restrict__ perm, ModQ m, double ninv,
+                                                ModQ m, double ninv,
                                                 double (&c)[NttShape<LOGN>::PER]) {
   constexpr int N = 1 << LOGN, T = NttShape<LOGN>::T;
   if constexpr (LOGN <= 14) {
@@ -497,11 +510,26 @@ __device__ __forceinline__ void ntt_inv_in_regs(double* s, In in, const double* 
   } else {
     constexpr int H = 1 << 14;
     double c0[16], c1[16];
-    for (int t = opaque_tid(); t < N / 2; t += T) s[lds_pad(perm[t])] = reduce(in(t), m);
+    auto fill = [&](int h) {
+      OrbitWalk ow = OrbitWalk::start<LOGN>();
+#pragma unroll 1
+      for (int w = 0; w < 16; w += 8) {  // eight slots' loads in flight
+        double v[8];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) v[u] = in(h * (N / 2) + (int)opaque_tid() + (w + u) * T);
+#pragma unroll
+        for (int u = 0; u < 8; ++u) {
+          const int j = ow.brv_index<LOGN>();
+          s[lds_pad(h ? H - 1 - j : j)] = reduce(v[u], m);
+          ow.next<LOGN>();
+        }
+      }
+    };
+    fill(0);
     __syncthreads();
     ntt_inv_regs<14>(s, c0, itw, m, ninv);
     __syncthreads();
-    for (int t = N / 2 + (int)opaque_tid(); t < N; t += T) s[lds_pad(perm[t] - H)] = reduce(in(t), m);
+    fill(1);
     __syncthreads();
     ntt_inv_regs<14>(s, c1, itw + H, m, ninv);
     const double iw0 = itw[0];
@@ -516,10 +544,10 @@ __device__ __forceinline__ void ntt_inv_in_regs(double* s, In in, const double* 
 // inverse transform of in(t), handing coefficient j to store(j, v)
 template <int LOGN, class In, class Store>
 __device__ __forceinline__ void ntt_inv_in(double* s, In in, const double* __restrict__ itw,
-                                           const uint32_t* __restrict__ perm, ModQ m, double ninv, Store store) {
+                                           ModQ m, double ninv, Store store) {
   constexpr int T = NttShape<LOGN>::T, PER = NttShape<LOGN>::PER;
   double c[PER];
-  ntt_inv_in_regs<LOGN>(s, in, itw, perm, m, ninv, c);
+  ntt_inv_in_regs<LOGN>(s, in, itw, m, ninv, c);
 #pragma unroll
   for (int w = 0; w < PER; ++w) store((int)opaque_tid() + w * T, c[w]);
 }

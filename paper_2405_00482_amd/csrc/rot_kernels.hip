@@ -139,7 +139,7 @@ ROT_KERNEL(LOGN) void k_rot_modup_intt(RotBatch b, int pre, const KsLevel* __res
   const int rot = pre ? b.it[it].rot : 0;
   const double ih = kl->up_inv_hat[i];
   double* dst = y + ((size_t)it * (lv + 1) + i) * N;
-  ntt_inv_in<LOGN>(s, [&](int t) { return c1[orbit_shift(t, rot, N / 2)]; }, tb.inv_tw + (size_t)i * N, tb.perm, m,
+  ntt_inv_in<LOGN>(s, [&](int t) { return c1[orbit_shift(t, rot, N / 2)]; }, tb.inv_tw + (size_t)i * N, m,
                    tb.ninv[i], [&](int j, double v) { dst[j] = canon(mulmod(canon(v, m), ih, m), m); });
 }
 
@@ -161,7 +161,7 @@ ROT_KERNEL(LOGN) void k_rot_modup_conv(const double* __restrict__ y, const KsLev
       double acc = 0.0;
       for (int u = 0; u < nsrc; ++u) acc += mulmod(yc[(size_t)u * N + j], task->hat[u], m);
       return reduce(acc, m);
-    }, tb.fwd_tw + (size_t)pi * N, tb.perm, m, [&](int t, double v) { dst[t] = v; });
+    }, tb.fwd_tw + (size_t)pi * N, m, [&](int t, double v) { dst[t] = v; });
 }
 
 // block (item, half x, special limb k): the key product on limb p_k, then
@@ -186,7 +186,7 @@ ROT_KERNEL(LOGN) void k_rot_down_p(RotBatch b, int pre, const KsLevel* __restric
   auto store = [&](int c, double v) { dst[c] = canon(mulmod(canon(v + h, m), ih, m), m); };
   if (inner) {
     const auto* src = gmem(inner) + ((size_t)(2 * it + x) * kl->K + lv + 1 + k) * N;
-    ntt_inv_in<LOGN>(s, [&](int t) { return src[t]; }, tb.inv_tw + (size_t)pi * N, tb.perm, m, tb.ninv[pi], store);
+    ntt_inv_in<LOGN>(s, [&](int t) { return src[t]; }, tb.inv_tw + (size_t)pi * N, m, tb.ninv[pi], store);
   } else if constexpr (LOGN <= 14) {
     double u[16], c[16];
     rot_inner<LOGN>(u, d, lv + 1 + k, key, key_digit, kl->beta, m);
@@ -197,7 +197,7 @@ ROT_KERNEL(LOGN) void k_rot_down_p(RotBatch b, int pre, const KsLevel* __restric
     for (int w = 0; w < 16; ++w) store((int)opaque_tid() + w * T, c[w]);
   } else {
     ntt_inv_in<LOGN>(s, [&](int t) { return rot_inner_at(d, lv + 1 + k, key, key_digit, kl->beta, t, m); },
-                     tb.inv_tw + (size_t)pi * N, tb.perm, m, tb.ninv[pi], store);
+                     tb.inv_tw + (size_t)pi * N, m, tb.ninv[pi], store);
   }
 }
 
@@ -256,7 +256,7 @@ ROT_KERNEL(LOGN) void k_rot_down_q(RotBatch b, int pre, int add, const KsLevel* 
     for (int w = 0; w < 16; ++w)
       o[(int)opaque_tid() + (w >> 1) * T + (w & 1) * H] = reduce(mulmod(u[w] - v[w], pinv, m), m);
   } else {
-    ntt_fwd_out<LOGN>(s, conv, tb.fwd_tw + (size_t)i * N, tb.perm, m, [&](int t, double v) {
+    ntt_fwd_out<LOGN>(s, conv, tb.fwd_tw + (size_t)i * N, m, [&](int t, double v) {
       double u;
       if (inner) {
         u = in[t];
