@@ -197,6 +197,67 @@ __global__ __launch_bounds__(512) void k_diag_bsgs(DiagArgs a, int bs, int g) {
   }
 }
 
+// Alg. 3 ciphertext-matrix product (and the column-order one): out_k = sum_i
+// ct_i pt_{i,k}, i < nct, k < nout.  A workgroup holds the sums of OUTS outputs
+// at 64 indices of one limb and its waves share the ciphertexts, so that a
+// ciphertext is read once per OUTS outputs; sums are exact (fp64_mod.hpp):
+// eight products of residues below q stay below 8 B^2 < 0.43 * 2^(2b + 5).
+// Bound by memory, each plaintext limb read once.  64 ciphertexts, 8 outputs,
+// 6 limbs at N = 2^14 (0.50 GB, 83 us at the read rate): one output per thread
+// 126 us, this 82.
+template <int OUTS>
+__global__ __launch_bounds__(512) void k_ctmat(const double* __restrict__ ct, const double* __restrict__ pt, int nct,
+                                               int nout, int lv, int N, const ModQ* __restrict__ mods,
+                                               double* __restrict__ out) {
+  __shared__ double red[2 * OUTS][8][64];
+  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6, nw = blockDim.x >> 6;
+  const int r = blockIdx.y, k0 = blockIdx.z * OUTS, nk = min(OUTS, nout - k0);
+  const ModQ m = mods[r];
+  const size_t Q = (size_t)(lv + 1) * N, off = (size_t)r * N + blockIdx.x * 64 + lane;
+  const double c = acc_offset(m.q, 5);
+  double hi0[OUTS], lo0[OUTS], hi1[OUTS], lo1[OUTS];
+#pragma unroll
+  for (int u = 0; u < OUTS; ++u) {
+    hi0[u] = hi1[u] = c;
+    lo0[u] = lo1[u] = 0.0;
+  }
+  int cnt = 0;
+  for (int i = w; i < nct; i += nw) {
+    const auto* pi = gmem(pt) + ((size_t)i * nout + k0) * Q + off;
+    const auto* ci = gmem(ct) + (size_t)i * 2 * Q + off;
+    double p[OUTS];
+#pragma unroll
+    for (int u = 0; u < OUTS; ++u)  // past the last output: the first one's again, never stored
+      p[u] = __builtin_nontemporal_load(pi + (size_t)(u < nk ? u : 0) * Q);
+    const double x0 = ci[0], x1 = ci[Q];
+#pragma unroll
+    for (int u = 0; u < OUTS; ++u) {
+      acc_mac(x0, p[u], hi0[u], lo0[u]);
+      acc_mac(x1, p[u], hi1[u], lo1[u]);
+    }
+    if (++cnt == 8) {
+#pragma unroll
+      for (int u = 0; u < OUTS; ++u) {
+        lo0[u] = reduce(acc_fold(hi0[u], lo0[u], m), m);
+        lo1[u] = reduce(acc_fold(hi1[u], lo1[u], m), m);
+        hi0[u] = hi1[u] = c;
+      }
+      cnt = 0;
+    }
+  }
+#pragma unroll
+  for (int u = 0; u < OUTS; ++u) {
+    red[2 * u][w][lane] = reduce(acc_fold(hi0[u], lo0[u], m), m);
+    red[2 * u + 1][w][lane] = reduce(acc_fold(hi1[u], lo1[u], m), m);
+  }
+  __syncthreads();
+  for (int h = w; h < 2 * nk; h += nw) {
+    double v = 0.0;
+    for (int k = 0; k < nw; ++k) v += red[h][k][lane];
+    out[(size_t)(2 * k0 + h) * Q + off] = reduce(v, m);
+  }
+}
+
 // ---------------------------------------------------------------------------
 #define DISPATCH_BETA(KERNEL, BETA_RT, GRID, BLOCK, ...)                                              \
   switch (BETA_RT) {                                                                                  \
@@ -223,6 +284,19 @@ hipError_t launch_diag_lazy(const LaunchCtx& L, const DiagArgs& a, int slices) {
 hipError_t launch_diag_bsgs(const LaunchCtx& L, const DiagArgs& a, int bs, int g) {
   const dim3 grid(a.N / 64, a.K, (g + kGiants - 1) / kGiants), block(64 * waves_for(bs, 8));
   DISPATCH_BETA(k_diag_bsgs, a.beta, grid, block, a, bs, g);
+  return hipGetLastError();
+}
+
+hipError_t launch_ctmat(const LaunchCtx& L, const double* ct, const double* pt, int nct, int nout, int lv, int N,
+                        double* out) {
+  const int outs = nout >= 5 ? 8 : nout >= 3 ? 4 : nout;
+  const dim3 grid(N / 64, lv + 1, (nout + outs - 1) / outs), block(64 * waves_for(nct, 8));
+  switch (outs) {
+    case 1: hipLaunchKernelGGL(k_ctmat<1>, grid, block, 0, L.stream, ct, pt, nct, nout, lv, N, L.tb.mods, out); break;
+    case 2: hipLaunchKernelGGL(k_ctmat<2>, grid, block, 0, L.stream, ct, pt, nct, nout, lv, N, L.tb.mods, out); break;
+    case 4: hipLaunchKernelGGL(k_ctmat<4>, grid, block, 0, L.stream, ct, pt, nct, nout, lv, N, L.tb.mods, out); break;
+    default: hipLaunchKernelGGL(k_ctmat<8>, grid, block, 0, L.stream, ct, pt, nct, nout, lv, N, L.tb.mods, out); break;
+  }
   return hipGetLastError();
 }
 

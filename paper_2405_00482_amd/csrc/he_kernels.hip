@@ -538,26 +538,6 @@ __global__ __launch_bounds__(256) void k_ct_add(const double* __restrict__ a, co
   out[idx] = reduce(a[idx] + b[idx], mods[i]);
 }
 
-// Alg. 3 ciphertext-matrix product: thread = (coefficient t, limb r, output k)
-__global__ __launch_bounds__(256) void k_ctmat(const double* __restrict__ ct, const double* __restrict__ pt, int nct,
-                                               int nout, int lv, int N, const ModQ* __restrict__ mods,
-                                               double* __restrict__ out) {
-  const int t = blockIdx.x * 256 + threadIdx.x;
-  const int r = blockIdx.y, k = blockIdx.z;
-  const ModQ m = mods[r];
-  const size_t Q = (size_t)(lv + 1) * N;
-  const size_t off = (size_t)r * N + t;
-  double a0 = 0.0, a1 = 0.0;
-  for (int i = 0; i < nct; ++i) {
-    const double p = pt[((size_t)i * nout + k) * Q + off];
-    a0 += mulmod(ct[(size_t)i * 2 * Q + off], p, m);
-    a1 += mulmod(ct[(size_t)i * 2 * Q + Q + off], p, m);
-    if ((i & 7) == 7) { a0 = reduce(a0, m); a1 = reduce(a1, m); }
-  }
-  out[(size_t)k * 2 * Q + off] = reduce(a0, m);
-  out[(size_t)k * 2 * Q + Q + off] = reduce(a1, m);
-}
-
 // ---------------------------------------------------------------------------
 // host-side launchers
 // ---------------------------------------------------------------------------
@@ -725,13 +705,6 @@ hipError_t launch_sum_partials(const LaunchCtx& L, const double* part, int n, in
   const size_t tot = (size_t)2 * K * N;
   hipLaunchKernelGGL(k_sum_partials, dim3(blocks_for(tot)), dim3(256), 0, L.stream, part, n, K, N, limb_prime, L.tb.mods,
                      acc);
-  return hipGetLastError();
-}
-
-hipError_t launch_ctmat(const LaunchCtx& L, const double* ct, const double* pt, int nct, int nout, int lv, int N,
-                        double* out) {
-  hipLaunchKernelGGL(k_ctmat, dim3(N / 256, lv + 1, nout), dim3(256), 0, L.stream, ct, pt, nct, nout, lv, N, L.tb.mods,
-                     out);
   return hipGetLastError();
 }
 
