@@ -251,7 +251,7 @@ __global__ __launch_bounds__(NttShape<LOGN>::T) void k_encode_pt_batch(const Enc
   const int2 wk = work[vt];
   const EncodeArgs a = args[wk.x];
   double* out = prods[wk.x].pt_out + (size_t)wk.y * map.n * (1 << LOGN);
-  encode_pt_body<LOGN>(a, wk.y, et, map, tb, s2, out);
+  encode_pt_body<LOGN>(a, wk.y, et, map, LimbRange{0, map.n}, tb, s2, out);
 }
 
 template <int LOGN>

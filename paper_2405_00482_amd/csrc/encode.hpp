@@ -36,6 +36,25 @@ struct OutFactors {
   double f[kMaxLimbs];
 };
 
+// Workgroups that share one plaintext's nl limbs, each repeating its FFT (worth
+// 1.5 limbs' transforms): the number for which `count` plaintexts take the
+// least time on 256 CUs holding 4, 2 or 1 workgroups at N = 2^12, 2^13, 2^14+.
+// With more than a few rounds of workgroups it is one.  64 plaintexts of 4
+// limbs at 2^13: 38 -> 23 us; 128 of 6 limbs at 2^14: 87 -> 62 us; one
+// cleartext of 3 limbs at 2^13: 29 -> 16 us.
+inline int encode_parts(int logN, int count, int nl) {
+  const long slots = 256L * (logN <= 12 ? 4 : logN == 13 ? 2 : 1);
+  int best = 1;
+  double least = 0.0;
+  for (int p = 1; p <= nl; ++p) {
+    const double t = (double)(((long)count * p + slots - 1) / slots) * (1.5 + (nl + p - 1) / p);
+    if (p == 1 || t < least) {
+      best = p;
+      least = t;
+    }
+  }
+  return best;
+}
 hipError_t launch_encode_pt(const LaunchCtx& L, const EncodeArgs& a, const EncTabs& et, LimbMap map, int count,
                             double* out);
 // cleartext at the plan's output scale (pvfl_encode_out): out[count][map.n][N]

@@ -445,19 +445,30 @@ __device__ __forceinline__ void encode_ct_body(const EncodeArgs& a, int c, const
   }
 }
 
-// Encodes the slots that gather() yields and transforms every limb of `map`,
-// to out[limb][N]; first(c, l) turns the integer coefficients into limb l's
+// Part of a plaintext's limbs [l0, l1) that one workgroup makes.
+struct LimbRange {
+  int l0, l1;
+};
+// part `p` of `parts` of n limbs
+__device__ __forceinline__ LimbRange limb_part(int n, int p, int parts) {
+  const int per = (n + parts - 1) / parts;
+  return LimbRange{min(n, p * per), min(n, (p + 1) * per)};
+}
+
+// Encodes the slots that gather() yields and transforms the limbs `lr` of
+// `map`, to out[limb][N]; first(c, l) turns the integer coefficients into limb l's
 // input (|x| < 2^51).  s2: LDS of NttShape<LOGN>::LDS doubles.
 template <int LOGN, class Gather, class First, class Store>
-__device__ __forceinline__ void encode_limbs(Gather gather, const EncTabs& et, const LimbMap& map, const DevTabs& tb,
-                                             double2* s2, double* __restrict__ out, First first, Store store) {
+__device__ __forceinline__ void encode_limbs(Gather gather, const EncTabs& et, const LimbMap& map, LimbRange lr,
+                                             const DevTabs& tb, double2* s2, double* __restrict__ out, First first,
+                                             Store store) {
   constexpr int N = 1 << LOGN, T = NttShape<LOGN>::T, PH = N / 2 / T, PER = NttShape<LOGN>::PER;
   double* s = (double*)s2;
   if constexpr (LOGN <= 14) {
     double mreg[2 * PH];
     encode_to_regs_v<LOGN>(gather, s2, mreg, et);
     // coefficient tid + w T: w < PH -> m_k (real part), w >= PH -> m_(k+N/2) (imaginary part)
-    for (int l = 0; l < map.n; ++l) {
+    for (int l = lr.l0; l < lr.l1; ++l) {
       const int pi = map.idx[l];
       double c[PER];
 #pragma unroll
@@ -470,9 +481,9 @@ __device__ __forceinline__ void encode_limbs(Gather gather, const EncTabs& et, c
     // the integer coefficients wait in the last limb's place, where each thread
     // reads back only what it wrote; that limb is transformed last, and its
     // first barrier stands between the reads and the output's writes
-    double* park = out + (size_t)(map.n - 1) * N;
+    double* park = out + (size_t)(lr.l1 - 1) * N;
     encode15(gather, s2, et, [&](int w, double m) { park[opaque_tid() + w * T] = m; });
-    for (int l = 0; l < map.n; ++l) {
+    for (int l = lr.l0; l < lr.l1; ++l) {
       const int pi = map.idx[l];
       double c[PER];
 #pragma unroll
@@ -484,12 +495,12 @@ __device__ __forceinline__ void encode_limbs(Gather gather, const EncTabs& et, c
   }
 }
 
-// Plaintext k of a plan: pack, encode, then every limb of `map` reduced and
+// Plaintext k of a plan: pack, encode, then the limbs `lr` of `map` reduced and
 // transformed; written to out_pt[limb][N].  |m| < 2^51, which the transform
 // reduces on entry.
 template <int LOGN>
 __device__ __forceinline__ void encode_pt_body(const EncodeArgs& a, int k, const EncTabs& et, const LimbMap& map,
-                                               const DevTabs& tb, double2* s2, double* __restrict__ out_pt) {
+                                               LimbRange lr, const DevTabs& tb, double2* s2, double* __restrict__ out_pt) {
   auto same = [](double m, int) { return m; };
   // the plaintext buffer is device memory: global stores (unlike flat stores
   // they do not count against the LDS wait counter of the gather before
@@ -506,10 +517,10 @@ __device__ __forceinline__ void encode_pt_body(const EncodeArgs& a, int k, const
 #pragma unroll
           for (int u = 0; u < (int)(sizeof(v) / sizeof(v[0])); ++u) v[u] = slot_of(u) == 0 ? ind : 0.0;
         },
-        et, map, tb, s2, out_pt, same, stream);
+        et, map, lr, tb, s2, out_pt, same, stream);
   } else {
-    encode_limbs<LOGN>([&](auto slot_of, auto& v) { gather_slots<false>(a, k, a.scale, slot_of, v); }, et, map, tb, s2,
-                       out_pt, same, stream);
+    encode_limbs<LOGN>([&](auto slot_of, auto& v) { gather_slots<false>(a, k, a.scale, slot_of, v); }, et, map, lr,
+                       tb, s2, out_pt, same, stream);
   }
 }
 
@@ -552,7 +563,7 @@ __device__ __forceinline__ double out_slot_value(const EncodeArgs& a, const doub
 template <int LOGN>
 __device__ __forceinline__ void encode_out_body(const EncodeArgs& a, const double* __restrict__ v, int mode,
                                                 int ras_in_ct, int b, const OutFactors& fac, const EncTabs& et,
-                                                const LimbMap& map, const DevTabs& tb, double2* s2,
+                                                const LimbMap& map, LimbRange lr, const DevTabs& tb, double2* s2,
                                                 double* __restrict__ out) {
   encode_limbs<LOGN>(
       [&](auto slot_of, auto& val) {
@@ -560,7 +571,7 @@ __device__ __forceinline__ void encode_out_body(const EncodeArgs& a, const doubl
         for (int u = 0; u < (int)(sizeof(val) / sizeof(val[0])); ++u)
           val[u] = out_slot_value(a, v, mode, ras_in_ct, b, slot_of(u)) * a.scale;
       },
-      et, map, tb, s2, out, [&](double m, int l) { return mulmod(m, fac.f[l], tb.mods[map.idx[l]]); },
+      et, map, lr, tb, s2, out, [&](double m, int l) { return mulmod(m, fac.f[l], tb.mods[map.idx[l]]); },
       [](double* p, double x) { *p = x; });
 }
 

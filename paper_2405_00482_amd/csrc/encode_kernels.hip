@@ -17,13 +17,16 @@
 
 namespace pvfl {
 
-// One workgroup per plaintext: pack, encode, then every limb reduced and
-// transformed.  out[k][limb][N].
+// `parts` workgroups per plaintext (encode_parts): pack, encode, then each its
+// share of the limbs reduced and transformed.  out[k][limb][N].
 template <int LOGN>
-__global__ __launch_bounds__(NttShape<LOGN>::T) void k_encode_pt(EncodeArgs a, EncTabs et, LimbMap map, DevTabs tb,
-                                                                 double* __restrict__ out) {
+__global__ __launch_bounds__(NttShape<LOGN>::T) void k_encode_pt(EncodeArgs a, EncTabs et, LimbMap map, int parts,
+                                                                 DevTabs tb, double* __restrict__ out) {
   __shared__ double2 s2[NttShape<LOGN>::LDS / 2];
-  encode_pt_body<LOGN>(a, (int)blockIdx.x, et, map, tb, s2, out + (size_t)blockIdx.x * map.n * (1 << LOGN));
+  const int k = blockIdx.x / parts;
+  const LimbRange lr = limb_part(map.n, blockIdx.x % parts, parts);
+  if (lr.l0 >= lr.l1) return;
+  encode_pt_body<LOGN>(a, k, et, map, lr, tb, s2, out + (size_t)k * map.n * (1 << LOGN));
 }
 
 // Input ciphertext messages: one workgroup per ciphertext, int64 coefficients
@@ -101,10 +104,12 @@ __global__ __launch_bounds__(NttShape<LOGN>::T) void k_decode_readout(const doub
 template <int LOGN>
 __global__ __launch_bounds__(NttShape<LOGN>::T) void k_encode_out(EncodeArgs a, const double* __restrict__ v, int mode,
                                                                   int ras_in_ct, OutFactors fac, EncTabs et, LimbMap map,
-                                                                  DevTabs tb, double* __restrict__ out) {
+                                                                  int parts, DevTabs tb, double* __restrict__ out) {
   __shared__ double2 s2[NttShape<LOGN>::LDS / 2];
-  encode_out_body<LOGN>(a, v, mode, ras_in_ct, (int)blockIdx.x, fac, et, map, tb, s2,
-                        out + (size_t)blockIdx.x * map.n * (1 << LOGN));
+  const int b = blockIdx.x / parts;
+  const LimbRange lr = limb_part(map.n, blockIdx.x % parts, parts);
+  if (lr.l0 >= lr.l1) return;
+  encode_out_body<LOGN>(a, v, mode, ras_in_ct, b, fac, et, map, lr, tb, s2, out + (size_t)b * map.n * (1 << LOGN));
 }
 
 // out c0 = ct c0 + sign * pt, c1 copied, on nct ciphertexts of lv+1 limbs
@@ -134,19 +139,22 @@ __global__ __launch_bounds__(256) void k_readout(const double* __restrict__ z, E
 // ---------------------------------------------------------------------------
 template <int LOGN>
 static void encode_pt_impl(const LaunchCtx& L, const EncodeArgs& a, const EncTabs& et, LimbMap map, int count, double* out) {
+  const int parts = encode_parts(LOGN, count, map.n);
   if constexpr (LOGN == 15)
-    launch15_encode_pt(L, a, et, map, count, out);
+    launch15_encode_pt(L, a, et, map, count, parts, out);
   else
-    hipLaunchKernelGGL(k_encode_pt<LOGN>, dim3(count), dim3(NttShape<LOGN>::T), 0, L.stream, a, et, map, L.tb, out);
+    hipLaunchKernelGGL(k_encode_pt<LOGN>, dim3(count * parts), dim3(NttShape<LOGN>::T), 0, L.stream, a, et, map, parts,
+                       L.tb, out);
 }
 template <int LOGN>
 static void encode_out_impl(const LaunchCtx& L, const EncodeArgs& a, const double* v, int mode, int ras_in_ct,
                             const OutFactors& fac, const EncTabs& et, LimbMap map, int count, double* out) {
+  const int parts = encode_parts(LOGN, count, map.n);
   if constexpr (LOGN == 15)
-    launch15_encode_out(L, a, v, mode, ras_in_ct, fac, et, map, count, out);
+    launch15_encode_out(L, a, v, mode, ras_in_ct, fac, et, map, count, parts, out);
   else
-    hipLaunchKernelGGL(k_encode_out<LOGN>, dim3(count), dim3(NttShape<LOGN>::T), 0, L.stream, a, v, mode, ras_in_ct, fac,
-                       et, map, L.tb, out);
+    hipLaunchKernelGGL(k_encode_out<LOGN>, dim3(count * parts), dim3(NttShape<LOGN>::T), 0, L.stream, a, v, mode, ras_in_ct,
+                       fac, et, map, parts, L.tb, out);
 }
 template <int LOGN>
 static void encode_ct_impl(const LaunchCtx& L, const EncodeArgs& a, const EncTabs& et, int count, int64_t* msg) {
