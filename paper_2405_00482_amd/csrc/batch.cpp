@@ -400,7 +400,7 @@ static pvfl_status batch_modup(pvfl_batch* b, void* stream) {
   LaunchCtx L = launch_ctx(c, stream);
   {
     KernelTimer kt(c, stream, PVFL_TIMING_MODUP, 8.0 * (double)b->count * (Q + (size_t)b->beta * KN));
-    HIP_TRY(launch_modup(L, nullptr, 0, b->count, lv, c->ks_dev + lv, kl.n_tasks, b->yup, b->digits,
+    HIP_TRY(launch_modup(L, nullptr, 0, b->count, lv, c->alpha, c->ks_dev + lv, kl.n_tasks, b->yup, b->digits,
                          (size_t)b->beta * KN, b->ct_tab));
     kt.stop();
   }

@@ -47,4 +47,43 @@ __device__ __forceinline__ int orbit_shift(int t, int rot, int half) {
   return (t & half) | ((t + rot) & (half - 1));
 }
 
+// Key switching with one special prime, both transforms of a step in one
+// workgroup (N <= 2^14).
+// ModUp: coefficients x of limb task.src0 (slots in(t)) converted to the
+// target limb's prime.  Barrier before writing LDS again (the transforms do).
+template <int LOGN, class In>
+__device__ __forceinline__ void modup_source(double* s, In in, const KsTask& task, const KsLevel* __restrict__ kl,
+                                             const DevTabs& tb, double (&x)[16]) {
+  constexpr int N = 1 << LOGN;
+  const int si = task.src0;
+  const ModQ ms = tb.mods[si], m = tb.mods[task.prime];
+  const double ih = kl->up_inv_hat[si], hat = task.hat[0];
+  ntt_inv_in_regs<LOGN>(s, in, tb.inv_tw + (size_t)si * N, ms, tb.ninv[si], x);
+#pragma unroll
+  for (int w = 0; w < 16; ++w) x[w] = reduce(mulmod(canon(mulmod(canon(x[w], ms), ih, ms), ms), hat, m), m);
+}
+// ModDown of ciphertext limb i: the special limb's slots in(t), the limb's own
+// slots u (as slots_from_lds orders them), results to out(t, v).
+template <int LOGN, class In, class Out>
+__device__ __forceinline__ void moddown_limb(double* s, In in, const double (&u)[16], int i,
+                                             const KsLevel* __restrict__ kl, const DevTabs& tb, Out out) {
+  constexpr int N = 1 << LOGN, T = NttShape<LOGN>::T;
+  const int lv = kl->lv, pi = kl->n_q_total;
+  const ModQ mp = tb.mods[pi], m = tb.mods[i];
+  const double hp = kl->down_half[lv + 1], ih = kl->down_inv_hat[0];
+  const double h = kl->down_half[i], hat = kl->down_hat[i], pinv = kl->down_pinv[i];
+  double c[16], v[16];
+  ntt_inv_in_regs<LOGN>(s, in, tb.inv_tw + (size_t)pi * N, mp, tb.ninv[pi], c);
+#pragma unroll
+  for (int w = 0; w < 16; ++w) {
+    const double y = canon(mulmod(canon(c[w] + hp, mp), ih, mp), mp);
+    c[w] = reduce(mulmod(y, hat, m) - h, m);
+  }
+  ntt_fwd_regs<LOGN>(s, c, tb.fwd_tw + (size_t)i * N, m);
+  slots_from_lds<LOGN>(s, v);
+#pragma unroll
+  for (int w = 0; w < 16; ++w)
+    out((int)opaque_tid() + (w >> 1) * T + (w & 1) * (N / 2), reduce(mulmod(u[w] - v[w], pinv, m), m));
+}
+
 }  // namespace pvfl

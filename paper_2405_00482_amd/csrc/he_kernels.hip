@@ -369,6 +369,32 @@ NTT_KERNEL(LOGN) void k_modup_conv(const double* __restrict__ y, const double* _
     }, tb.fwd_tw + (size_t)pi * N, m, [&](int t, double v) { dst[t] = v; });
 }
 
+// Both steps in one launch for alpha = 1 (a digit is one limb): every target
+// limb's workgroup makes the source limb's inverse transform again.  Where the
+// transforms leave CUs idle the repeated work costs nothing and one launch with
+// its memory round trip is saved (see fuse_transforms).
+template <int LOGN>
+NTT_KERNEL(LOGN) void k_modup_one(const double* __restrict__ ct, const double* const* __restrict__ ct_tab,
+                                   size_t ct_stride, const KsLevel* __restrict__ kl, double* __restrict__ digits,
+                                   size_t dig_stride, DevTabs tb) {
+  static_assert(LOGN <= 14, "one LDS-resident limb");
+  constexpr int N = 1 << LOGN, T = NttShape<LOGN>::T;
+  NTT_LDS(LOGN);
+  const int nt = kl->n_tasks;
+  const KsTask& task = kl->up_task[blockIdx.x % nt];
+  const int c = blockIdx.x / nt, lv = kl->lv, pi = task.prime;
+  const double* c1 = (ct_tab ? ct_tab[c] : ct + (size_t)c * ct_stride) + (size_t)(lv + 1) * N;
+  double* dst = digits + (size_t)c * dig_stride + ((size_t)task.digit * kl->K + task.limb) * N;
+  const double* src = c1 + (size_t)task.src0 * N;
+  if (task.nsrc == 0) {  // limb of the digit itself: residues kept as they are
+    for (int t = threadIdx.x; t < N; t += T) dst[t] = src[t];
+    return;
+  }
+  double x[16];
+  modup_source<LOGN>(s, [&](int t) { return src[t]; }, task, kl, tb, x);
+  ntt_fwd_regs_out<LOGN>(s, x, tb.fwd_tw + (size_t)pi * N, tb.mods[pi], [&](int t, double v) { dst[t] = v; });
+}
+
 // ---------------------------------------------------------------------------
 // ModDown Q_l u P -> Q_l with coefficient-wise rounding, on `npoly` polys
 // stored [npoly][K][N] (evaluation domain); output [npoly][l+1][N].
@@ -428,6 +454,24 @@ NTT_KERNEL(LOGN) void k_moddown_q(const double* __restrict__ u, const double* __
     ntt_fwd_out<LOGN>(s, conv, tb.fwd_tw + (size_t)i * N, m,
                       [&](int t, double v) { oi[t] = reduce(mulmod(ui[t] - v, pinv, m), m); });
   }
+}
+
+// Both steps in one launch for alpha = 1, as k_modup_one
+template <int LOGN>
+NTT_KERNEL(LOGN) void k_moddown_one(const double* __restrict__ u, const KsLevel* __restrict__ kl, double* __restrict__ out,
+                                     double* const* __restrict__ out_tab, DevTabs tb) {
+  static_assert(LOGN <= 14, "one LDS-resident limb");
+  constexpr int N = 1 << LOGN, T = NttShape<LOGN>::T;
+  NTT_LDS(LOGN);
+  const int K = kl->K, lv = kl->lv;
+  const int i = blockIdx.x % (lv + 1), x = blockIdx.x / (lv + 1);
+  const double* up = u + ((size_t)x * K + lv + 1) * N;
+  const double* ui = u + ((size_t)x * K + i) * N;
+  double* oi = out_tab ? out_tab[x >> 1] + ((size_t)(x & 1) * (lv + 1) + i) * N : out + ((size_t)x * (lv + 1) + i) * N;
+  double uv[16];
+#pragma unroll
+  for (int w = 0; w < 16; ++w) uv[w] = ui[(int)opaque_tid() + (w >> 1) * T + (w & 1) * (N / 2)];
+  moddown_limb<LOGN>(s, [&](int t) { return up[t]; }, uv, i, kl, tb, [&](int t, double v) { oi[t] = v; });
 }
 
 // Rescale by q_lv (drop the last limb, coefficient-wise rounding) on polys
@@ -659,22 +703,36 @@ hipError_t launch_rotkey_gen(const LaunchCtx& L, const double* sk, const RotKeyL
 
 template <int LOGN>
 static void modup_impl(const LaunchCtx& L, const double* ct, const double* const* ct_tab, size_t ct_stride, int nct,
-                       int lv, const KsLevel* kl_dev, int n_tasks, double* y, double* digits, size_t dig_stride) {
+                       int lv, int alpha, const KsLevel* kl_dev, int n_tasks, double* y, double* digits, size_t dig_stride) {
+  if constexpr (LOGN <= 14) {
+    if (fuse_transforms(alpha, nct * n_tasks)) {
+      hipLaunchKernelGGL(k_modup_one<LOGN>, dim3(nct * n_tasks), dim3(NttShape<LOGN>::T), 0, L.stream, ct, ct_tab, ct_stride,
+                         kl_dev, digits, dig_stride, L.tb);
+      return;
+    }
+  }
   hipLaunchKernelGGL(k_modup_intt<LOGN>, dim3(nct * (lv + 1)), dim3(NttShape<LOGN>::T), 0, L.stream, ct, ct_tab, ct_stride,
                      lv, kl_dev, y, L.tb);
   hipLaunchKernelGGL(k_modup_conv<LOGN>, dim3(nct * n_tasks), dim3(NttShape<LOGN>::T), 0, L.stream, y, ct, ct_tab,
                      ct_stride, kl_dev, digits, dig_stride, L.tb);
 }
-hipError_t launch_modup(const LaunchCtx& L, const double* ct, size_t ct_stride, int nct, int lv, const KsLevel* kl_dev,
-                        int n_tasks, double* y, double* digits, size_t dig_stride, const double* const* ct_tab) {
+hipError_t launch_modup(const LaunchCtx& L, const double* ct, size_t ct_stride, int nct, int lv, int alpha,
+                        const KsLevel* kl_dev, int n_tasks, double* y, double* digits, size_t dig_stride, const double* const* ct_tab) {
   if (nct <= 0) return hipSuccess;
-  DISPATCH_LOGN(L, modup_impl, L, ct, ct_tab, ct_stride, nct, lv, kl_dev, n_tasks, y, digits, dig_stride);
+  DISPATCH_LOGN(L, modup_impl, L, ct, ct_tab, ct_stride, nct, lv, alpha, kl_dev, n_tasks, y, digits, dig_stride);
   return hipGetLastError();
 }
 
 template <int LOGN>
 static void moddown_impl(const LaunchCtx& L, const double* u, int npoly, int lv, int alpha, const KsLevel* kl_dev,
                          double* y, double* out, double* const* out_tab) {
+  if constexpr (LOGN <= 14) {
+    if (fuse_transforms(alpha, npoly * (lv + 1))) {
+      hipLaunchKernelGGL(k_moddown_one<LOGN>, dim3(npoly * (lv + 1)), dim3(NttShape<LOGN>::T), 0, L.stream, u, kl_dev, out,
+                         out_tab, L.tb);
+      return;
+    }
+  }
   hipLaunchKernelGGL(k_moddown_p<LOGN>, dim3(npoly * alpha), dim3(NttShape<LOGN>::T), 0, L.stream, u, kl_dev, y, L.tb);
   hipLaunchKernelGGL(k_moddown_q<LOGN>, dim3(npoly * (lv + 1)), dim3(NttShape<LOGN>::T), 0, L.stream, u, y, kl_dev, out,
                      out_tab, L.tb);

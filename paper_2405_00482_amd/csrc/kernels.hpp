@@ -115,6 +115,15 @@ struct DiagArgs {
   double* part;            // [slices][2][K][N]
 };
 
+// Whether a key-switching step with `alpha` special primes and `blocks` target
+// limbs makes both of its transforms in one launch, each target repeating the
+// transform of its source limb: while one round of workgroups, one per CU,
+// holds the targets.  Two launches and one, us: ModUp of one ciphertext at
+// 2^12 / 2^13 / 2^14 15 -> 11, 29 -> 20, 54 -> 36, ModDown 17 -> 11, 31 -> 20,
+// 47 -> 38; beyond the line, 300 targets at 2^14 62 -> 70, 372 at 2^13 level
+// (one call 104).  With alpha > 1 a target would repeat alpha transforms.
+inline bool fuse_transforms(int alpha, int blocks) { return alpha == 1 && blocks <= 256; }
+
 hipError_t launch_ntt(const LaunchCtx& L, NttOp op, const void* in, void* out, int nblocks, LimbMap map);
 hipError_t launch_keygen(const LaunchCtx& L, uint64_t seed, double* sk, int n_mod);
 // nct ciphertexts [nct][2][lv+1][N] from messages [nct][N]; ciphertext c uses seed + c
@@ -132,8 +141,8 @@ hipError_t launch_rotkey_gen(const LaunchCtx& L, const double* sk, const RotKeyL
                              const RotKeyArgs& ka, double* keys);
 // ModUp of the c1 halves of nct ciphertexts (ct + c*ct_stride); y holds
 // [nct][lv+1][N] coefficient scratch; digits of ciphertext c at digits + c*dig_stride
-hipError_t launch_modup(const LaunchCtx& L, const double* ct, size_t ct_stride, int nct, int lv, const KsLevel* kl_dev,
-                        int n_tasks, double* y, double* digits, size_t dig_stride,
+hipError_t launch_modup(const LaunchCtx& L, const double* ct, size_t ct_stride, int nct, int lv, int alpha,
+                        const KsLevel* kl_dev, int n_tasks, double* y, double* digits, size_t dig_stride,
                         const double* const* ct_tab = nullptr);
 // out_tab (optional): output of poly x at out_tab[x/2] + (x%2)*(lv+1)*N
 hipError_t launch_moddown(const LaunchCtx& L, const double* u, int npoly, int lv, int alpha, const KsLevel* kl_dev,

@@ -426,7 +426,7 @@ static pvfl_status run_diag_lazy(const pvfl_plan* p, int count, const double* co
   // one ModUp per input ciphertext, shared by every row block
   for (int cb = 0; cb < CB && mprime > 1; ++cb) {
     KernelTimer kt(c, stream, PVFL_TIMING_MODUP, 8.0 * (double)(Q + DG));
-    HIP_TRY(launch_modup(L, ct_of(cb), 0, 1, lv, c->ks_dev + lv, kl.n_tasks, yup, digits + cb * DG, 0));
+    HIP_TRY(launch_modup(L, ct_of(cb), 0, 1, lv, c->alpha, c->ks_dev + lv, kl.n_tasks, yup, digits + cb * DG, 0));
     kt.stop();
   }
   DiagArgs a{};
@@ -523,7 +523,7 @@ static pvfl_status run_diag_eager(const pvfl_plan* p, const double* ct_in, const
       const double* ct = ct_in + (size_t)cb * 2 * Q;
       const double* pt = pts + (size_t)(b * p->info.col_blocks + cb) * mprime * Q;
       if (mprime > 1 && !o3)
-        HIP_TRY(launch_modup(L, ct, 0, 1, lv, c->ks_dev + lv, kl.n_tasks, digits + (size_t)p->beta * p->K * N, digits, 0));
+        HIP_TRY(launch_modup(L, ct, 0, 1, lv, c->alpha, c->ks_dev + lv, kl.n_tasks, digits + (size_t)p->beta * p->K * N, digits, 0));
       HIP_TRY(launch_sum_cts(L, ct, 0, pt, 0, 1, lv, N, cb > 0, acc));
       for (int i0 = 1; i0 < mprime; i0 += at_once) {
         const int cnt = std::min(at_once, mprime - i0);

@@ -164,6 +164,41 @@ ROT_KERNEL(LOGN) void k_rot_modup_conv(const double* __restrict__ y, const KsLev
     }, tb.fwd_tw + (size_t)pi * N, m, [&](int t, double v) { dst[t] = v; });
 }
 
+// block (item, task), alpha = 1: both ModUp transforms (k_modup_one)
+template <int LOGN>
+ROT_KERNEL(LOGN) void k_rot_modup_one(RotBatch b, int pre, const KsLevel* __restrict__ kl, double* __restrict__ digits,
+                                      size_t dig_stride, DevTabs tb) {
+  constexpr int N = 1 << LOGN;
+  __shared__ double s[NttShape<LOGN>::LDS];
+  const int nt = kl->n_tasks, it = blockIdx.x / nt;
+  const KsTask& task = kl->up_task[blockIdx.x % nt];
+  if (task.nsrc == 0) return;  // the digit's own limb: read from c1
+  const int pi = task.prime, rot = pre ? b.it[it].rot : 0;
+  const auto* src = gmem(b.it[it].ct) + (size_t)(kl->lv + 1 + task.src0) * N;
+  double* dst = digits + (size_t)it * dig_stride + ((size_t)task.digit * kl->K + task.limb) * N;
+  double x[16];
+  modup_source<LOGN>(s, [&](int t) { return src[orbit_shift(t, rot, N / 2)]; }, task, kl, tb, x);
+  ntt_fwd_regs_out<LOGN>(s, x, tb.fwd_tw + (size_t)pi * N, tb.mods[pi], [&](int t, double v) { dst[t] = v; });
+}
+
+// block (item, half x, limb i), alpha = 1, key products made apart: both
+// ModDown transforms
+template <int LOGN>
+ROT_KERNEL(LOGN) void k_rot_down_one(RotBatch b, const KsLevel* __restrict__ kl, const double* __restrict__ inner,
+                                     DevTabs tb) {
+  constexpr int N = 1 << LOGN, T = NttShape<LOGN>::T;
+  __shared__ double s[NttShape<LOGN>::LDS];
+  const int lv = kl->lv;
+  const int i = blockIdx.x % (lv + 1), x = (blockIdx.x / (lv + 1)) & 1, it = blockIdx.x / (2 * (lv + 1));
+  const auto* u = gmem(inner) + (size_t)(2 * it + x) * kl->K * N;
+  double* o = b.it[it].out + (size_t)(x * (lv + 1) + i) * N;
+  double uv[16];
+#pragma unroll
+  for (int w = 0; w < 16; ++w) uv[w] = u[(size_t)i * N + (int)opaque_tid() + (w >> 1) * T + (w & 1) * (N / 2)];
+  moddown_limb<LOGN>(s, [&](int t) { return u[(size_t)(lv + 1) * N + t]; }, uv, i, kl, tb,
+                     [&](int t, double v) { o[t] = v; });
+}
+
 // block (item, half x, special limb k): the key product on limb p_k, then
 // ModDown's first step
 template <int LOGN>
@@ -315,7 +350,14 @@ template <int LOGN>
 static void rotations_impl(const LaunchCtx& L, const RotBatch& b, const RotRun& r) {
   const dim3 block(NttShape<LOGN>::T);
   const KsLevel* kl = r.kl_dev;
-  if (!r.shared_digits) {
+  const bool one = LOGN <= 14 && fuse_transforms(r.alpha, b.n * r.n_tasks);
+  const bool down_one = LOGN <= 14 && r.inner && fuse_transforms(r.alpha, b.n * 2 * (r.lv + 1));
+  if constexpr (LOGN <= 14) {
+    if (!r.shared_digits && one)
+      hipLaunchKernelGGL(k_rot_modup_one<LOGN>, dim3(b.n * r.n_tasks), block, 0, L.stream, b, r.pre, kl, r.digits,
+                         r.dig_stride, L.tb);
+  }
+  if (!r.shared_digits && !one) {
     hipLaunchKernelGGL(k_rot_modup_intt<LOGN>, dim3(b.n * (r.lv + 1)), block, 0, L.stream, b, r.pre, kl, r.yup, L.tb);
     hipLaunchKernelGGL(k_rot_modup_conv<LOGN>, dim3(b.n * r.n_tasks), block, 0, L.stream, r.yup, kl, r.digits,
                        r.dig_stride, L.tb);
@@ -323,6 +365,12 @@ static void rotations_impl(const LaunchCtx& L, const RotBatch& b, const RotRun& 
   if (r.inner)
     hipLaunchKernelGGL(k_rot_inner, dim3((1 << LOGN) / 256, r.lv + 1 + r.alpha, b.n), dim3(256), 0, L.stream, b, r.pre, r.add,
                        kl, r.digits, r.dig_stride, r.key_limbs, 1 << LOGN, L.tb.mods, r.inner);
+  if constexpr (LOGN <= 14) {
+    if (down_one) {
+      hipLaunchKernelGGL(k_rot_down_one<LOGN>, dim3(b.n * 2 * (r.lv + 1)), block, 0, L.stream, b, kl, r.inner, L.tb);
+      return;
+    }
+  }
   hipLaunchKernelGGL(k_rot_down_p<LOGN>, dim3(b.n * 2 * r.alpha), block, 0, L.stream, b, r.pre, kl, r.digits,
                      r.dig_stride, r.key_limbs, r.inner, r.ydown, L.tb);
   hipLaunchKernelGGL(k_rot_down_q<LOGN>, dim3(b.n * 2 * (r.lv + 1)), block, 0, L.stream, b, r.pre, r.add, kl, r.digits,
