@@ -25,7 +25,7 @@
 // (its quotient estimate is within 0.875 of the true quotient), so a forward
 // butterfly grows values by at most 0.875 q.  Re-centring (to |x| <= q/2) at
 // least every 9 stages keeps every butterfly input below q/2 + 8 * 0.875 q =
-// 7.5 q < 2^51.  The inverse re-centres its sums every second stage.
+// 7.5 q < 2^51.  The inverse re-centres after every pass (gs_pass_regs).
 // Outputs are centred.
 #pragma once
 #include "fp64_mod.hpp"
@@ -248,11 +248,15 @@ __device__ __forceinline__ void ntt_fwd(double* s, Load load, const double* __re
 // S Gentleman-Sande stages lg1, lg1-1, ..., lg1-S+1 (span doubling each
 // stage); sets {base + u * 2^ls}, 2^ls = span of the first stage.  The set is
 // one group of stage lg1-S+1; at stage lg1-st it spans 2^(S-1-st) groups with
-// contiguous twiddles.  Sums are re-centred every second stage, differences
-// go through mulmod; everything is re-centred at the end.
+// contiguous twiddles.  From centred inputs the sums double at every stage, so
+// that the differences of the fourth stage are below 8q < 2^51, which mulmod
+// takes: no reduction inside a pass of S <= 4 stages.  `scale`, if not null,
+// multiplies the pass's results (the sums of its last stage directly, the
+// differences through their twiddle).
 template <int LOGN, int S>
 __device__ __forceinline__ void gs_pass_regs(double (&x)[16], int lg1, const int (&base)[16 >> S],
-                                             const double* __restrict__ itw, ModQ m) {
+                                             const double* __restrict__ itw, ModQ m, const double* scale = nullptr) {
+  static_assert(S <= 4, "the growth of the sums");
   constexpr int SET = 1 << S;
 #pragma unroll
   for (int q = 0; q < (16 >> S); ++q) {
@@ -265,14 +269,14 @@ __device__ __forceinline__ void gs_pass_regs(double (&x)[16], int lg1, const int
       const double* tws = itw + (1 << lg) + gbase;
 #pragma unroll
       for (int k = 0; k < (SET >> (st + 1)); ++k) w[k] = tws[k];
+      const bool scaled = scale && st == S - 1;
+      if (scaled) w[0] = reduce(mulmod(w[0], *scale, m), m);
 #pragma unroll
       for (int u = 0; u < SET; ++u) {
         if (u & half) continue;
         const double U = x[q * SET + u];
         const double V = x[q * SET + u + half];
-        double sum = U + V;
-        if (st & 1) sum = reduce(sum, m);
-        x[q * SET + u] = sum;
+        x[q * SET + u] = scaled ? mulmod(U + V, *scale, m) : U + V;
         x[q * SET + u + half] = mulmod(U - V, w[u >> (st + 1)], m);
       }
     }
@@ -327,9 +331,9 @@ __device__ __forceinline__ void ntt_inv_regs(double* s, double (&c)[16], const d
   {  // spans N/16 .. N/2 on the thread's coefficients tid + u N/16
     const int base[1] = {tid};
     lds_load_c<4, LOGN - 4>(s, x, base);
-    gs_pass_regs<LOGN, 4>(x, 3, base, itw, m);
+    gs_pass_regs<LOGN, 4>(x, 3, base, itw, m, &ninv);
 #pragma unroll
-    for (int u = 0; u < 16; ++u) c[u] = reduce(mulmod(x[u], ninv, m), m);
+    for (int u = 0; u < 16; ++u) c[u] = x[u];
   }
 }
 
