@@ -46,15 +46,6 @@ __host__ __device__ constexpr int stage_row(int ch) {
   return 256 + (CHX ? CHX : ch);
 }
 
-// A row address that is the same for the whole workgroup, kept in scalar
-// registers: the loads take it as their base and share one 32-bit thread
-// offset, instead of a 64-bit vector addition per row.
-__device__ __forceinline__ const __attribute__((address_space(1))) double* scalar_base(const double* p) {
-  uint64_t x = (uint64_t)p;
-  asm("" : "+s"(x));
-  return (const __attribute__((address_space(1))) double*)x;
-}
-
 template <int PG, int BETA, int CHX>
 __global__ __launch_bounds__(256) void k_diag_batch(BatchDiagArgs a) {
   extern __shared__ double stage[];  // [PG][BETA + 1][win]
@@ -240,7 +231,7 @@ __global__ __launch_bounds__(256) void k_sum_partials_batch(const double* __rest
 // range of the (product, diagonal) list so that neighbouring diagonals of one
 // product, which read neighbouring columns of X, share its L2.
 template <int LOGN>
-__global__ __launch_bounds__(NttShape<LOGN>::T) void k_encode_pt_batch(const EncodeArgs* __restrict__ args,
+LIMBS_KERNEL(LOGN) void k_encode_pt_batch(const EncodeArgs* __restrict__ args,
                                                                        const int2* __restrict__ work, int nwork,
                                                                        const BatchProd* __restrict__ prods, EncTabs et,
                                                                        LimbMap map, DevTabs tb) {

@@ -467,6 +467,7 @@ __device__ __forceinline__ void encode_limbs(Gather gather, const EncTabs& et, c
   if constexpr (LOGN <= 14) {
     double mreg[2 * PH];
     encode_to_regs_v<LOGN>(gather, s2, mreg, et);
+    const OrbitIndex<LOGN> oi = OrbitIndex<LOGN>::make();
     // coefficient tid + w T: w < PH -> m_k (real part), w >= PH -> m_(k+N/2) (imaginary part)
     for (int l = lr.l0; l < lr.l1; ++l) {
       const int pi = map.idx[l];
@@ -475,7 +476,7 @@ __device__ __forceinline__ void encode_limbs(Gather gather, const EncTabs& et, c
       for (int w = 0; w < PER; ++w) c[w] = first(w < PH ? mreg[2 * w] : mreg[2 * (w - PH) + 1], l);
       double* dst = out + (size_t)l * N;
       ntt_fwd_regs_out<LOGN>(s, c, tb.fwd_tw + (size_t)pi * N, tb.mods[pi],
-                             [&](int t, double v) { store(dst + t, v); });
+                             [&](unsigned b, unsigned t, double v) { store(scalar_base(dst + b) + t, v); }, oi.opaque());
     }
   } else {
     // the integer coefficients wait in the last limb's place, where each thread
@@ -506,7 +507,7 @@ __device__ __forceinline__ void encode_pt_body(const EncodeArgs& a, int k, const
   // they do not count against the LDS wait counter of the gather before
   // them), nontemporal because nothing in this kernel reads them again --
   // they would only push the twiddle tables and X out of L2
-  auto stream = [](double* p, double v) {
+  auto stream = [](auto* p, double v) {
     __builtin_nontemporal_store(v, (__attribute__((address_space(1))) double*)p);
   };
   if (a.kind == 2 && k == a.m) {
@@ -572,7 +573,7 @@ __device__ __forceinline__ void encode_out_body(const EncodeArgs& a, const doubl
           val[u] = out_slot_value(a, v, mode, ras_in_ct, b, slot_of(u)) * a.scale;
       },
       et, map, lr, tb, s2, out, [&](double m, int l) { return mulmod(m, fac.f[l], tb.mods[map.idx[l]]); },
-      [](double* p, double x) { *p = x; });
+      [](auto* p, double x) { *p = x; });
 }
 
 }  // namespace pvfl

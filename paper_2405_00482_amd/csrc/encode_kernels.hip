@@ -20,7 +20,7 @@ namespace pvfl {
 // `parts` workgroups per plaintext (encode_parts): pack, encode, then each its
 // share of the limbs reduced and transformed.  out[k][limb][N].
 template <int LOGN>
-__global__ __launch_bounds__(NttShape<LOGN>::T) void k_encode_pt(EncodeArgs a, EncTabs et, LimbMap map, int parts,
+LIMBS_KERNEL(LOGN) void k_encode_pt(EncodeArgs a, EncTabs et, LimbMap map, int parts,
                                                                  DevTabs tb, double* __restrict__ out) {
   __shared__ double2 s2[NttShape<LOGN>::LDS / 2];
   const int k = blockIdx.x / parts;
@@ -102,7 +102,7 @@ __global__ __launch_bounds__(NttShape<LOGN>::T) void k_decode_readout(const doub
 }
 
 template <int LOGN>
-__global__ __launch_bounds__(NttShape<LOGN>::T) void k_encode_out(EncodeArgs a, const double* __restrict__ v, int mode,
+LIMBS_KERNEL(LOGN) void k_encode_out(EncodeArgs a, const double* __restrict__ v, int mode,
                                                                   int ras_in_ct, OutFactors fac, EncTabs et, LimbMap map,
                                                                   int parts, DevTabs tb, double* __restrict__ out) {
   __shared__ double2 s2[NttShape<LOGN>::LDS / 2];

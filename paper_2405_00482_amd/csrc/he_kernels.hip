@@ -66,32 +66,40 @@ NTT_KERNEL(LOGN) void k_import_i64(const int64_t* __restrict__ in, double* __res
 // transformed in turn, so the row's memory latency is paid once per
 // polynomial instead of once per limb.
 template <int LOGN>
-NTT_KERNEL(LOGN) void k_import_i64_poly(const int64_t* __restrict__ in, double* __restrict__ out, LimbMap map,
+LIMBS_KERNEL(LOGN) void k_import_i64_poly(const int64_t* __restrict__ in, double* __restrict__ out, LimbMap map,
                                         DevTabs tb) {
   static_assert(LOGN <= 14, "one LDS-resident limb");
   constexpr int N = 1 << LOGN, T = NttShape<LOGN>::T;
   NTT_LDS(LOGN);
   const int c = blockIdx.x;
   const int64_t* src = in + (size_t)c * N;
-  // v = hi 2^32 + lo, both parts exact in binary64, split once for all limbs
-  double hi[16], lo[16];
+  // v = hi 2^32 + lo, both parts exact in binary64
+  const unsigned tid = opaque_tid();
+  int hi[16];
+  unsigned lo[16];
 #pragma unroll
   for (int w = 0; w < 16; ++w) {
-    const int64_t v = src[opaque_tid() + w * T];
-    hi[w] = (double)(v >> 32);
-    lo[w] = (double)(uint32_t)(v & 0xffffffffll);
+    const int64_t v = scalar_base(src + w * T)[tid];
+    hi[w] = (int)(v >> 32);
+    lo[w] = (unsigned)v;
   }
+  const OrbitIndex<LOGN> oi = OrbitIndex<LOGN>::make();
   for (int l = 0; l < map.n; ++l) {
     const int pi = map.idx[l];
     const ModQ m = tb.mods[pi];
     const double t32 = tb.two32[pi];
     double x[16];
+    // |hi| <= 2^31 and |t32| <= q/2 as mulmod needs, q + 2^32 < 2^51 as the transform
 #pragma unroll
-    for (int w = 0; w < 16; ++w) x[w] = reduce(mulmod(reduce(hi[w], m), t32, m) + lo[w], m);  // as i64_to_res
+    for (int w = 0; w < 16; ++w) {
+      asm volatile("" : "+v"(hi[w]), "+v"(lo[w]));  // converted for every limb: half the registers
+      x[w] = mulmod((double)hi[w], t32, m) + (double)lo[w];
+    }
     double* dst = out + ((size_t)c * map.n + l) * N;
     // nothing in this kernel reads the output again: stream it past L2
     ntt_fwd_regs_out<LOGN>(s, x, tb.fwd_tw + (size_t)pi * N, m,
-                           [&](int t, double y) { __builtin_nontemporal_store(y, dst + t); });
+                           [&](unsigned b, unsigned t, double y) { __builtin_nontemporal_store(y, scalar_base(dst + b) + t); },
+                           oi.opaque());
   }
 }
 
@@ -112,39 +120,32 @@ NTT_KERNEL(LOGN) void k_export_u64(const double* __restrict__ in, uint64_t* __re
 // transformed, the next limb's values are already being loaded into
 // registers (its slots go to LDS only after this limb's transform is done).
 template <int LOGN>
-NTT_KERNEL(LOGN) void k_export_u64_poly(const double* __restrict__ in, uint64_t* __restrict__ out, LimbMap map,
+LIMBS_KERNEL(LOGN) void k_export_u64_poly(const double* __restrict__ in, uint64_t* __restrict__ out, LimbMap map,
                                         DevTabs tb) {
   static_assert(LOGN <= 14, "one LDS-resident limb");
   constexpr int N = 1 << LOGN, T = NttShape<LOGN>::T;
   NTT_LDS(LOGN);
   const int c = blockIdx.x;
   const double* src = in + (size_t)c * map.n * N;
+  const unsigned tid = opaque_tid();
   // v[2w], v[2w+1]: orbit slots t = tid + w T and t + N/2 of the current limb
   double v[16];
 #pragma unroll
   for (int w = 0; w < 8; ++w) {
-    v[2 * w] = src[opaque_tid() + w * T];
-    v[2 * w + 1] = src[opaque_tid() + w * T + N / 2];
+    v[2 * w] = scalar_base(src + w * T)[tid];
+    v[2 * w + 1] = scalar_base(src + w * T + N / 2)[tid];
   }
+  const OrbitIndex<LOGN> oi = OrbitIndex<LOGN>::make();
   for (int l = 0; l < map.n; ++l) {
     const int pi = map.idx[l];
     const ModQ m = tb.mods[pi];
-    {
-      OrbitWalk ow = OrbitWalk::start<LOGN>();
-#pragma unroll
-      for (int w = 0; w < 8; ++w) {
-        const int j = ow.brv_index<LOGN>();
-        s[lds_pad(j)] = reduce(v[2 * w], m);
-        s[lds_pad(j ^ (N - 1))] = reduce(v[2 * w + 1], m);
-        ow.next<LOGN>();
-      }
-    }
+    slots_to_lds<LOGN>(s, v, m, oi.opaque());
     if (l + 1 < map.n) {
       const double* nsrc = src + (size_t)(l + 1) * N;
 #pragma unroll
       for (int w = 0; w < 8; ++w) {
-        v[2 * w] = nsrc[opaque_tid() + w * T];
-        v[2 * w + 1] = nsrc[opaque_tid() + w * T + N / 2];
+        v[2 * w] = scalar_base(nsrc + w * T)[tid];
+        v[2 * w + 1] = scalar_base(nsrc + w * T + N / 2)[tid];
       }
     }
     __syncthreads();
@@ -152,7 +153,8 @@ NTT_KERNEL(LOGN) void k_export_u64_poly(const double* __restrict__ in, uint64_t*
     ntt_inv_regs<LOGN>(s, cf, tb.inv_tw + (size_t)pi * N, m, tb.ninv[pi]);
     uint64_t* dst = out + ((size_t)c * map.n + l) * N;
 #pragma unroll
-    for (int w = 0; w < 16; ++w) __builtin_nontemporal_store(f64_to_u64(canon(cf[w], m)), dst + opaque_tid() + w * T);
+    for (int w = 0; w < 16; ++w)
+      __builtin_nontemporal_store(f64_to_u64(cf[w] < 0.0 ? cf[w] + m.q : cf[w]), scalar_base(dst + w * T) + tid);
     __syncthreads();  // other threads may still read this limb from LDS
   }
 }
