@@ -14,8 +14,12 @@ namespace pvfl {
 // Word idx of stream `stream` under key `seed`: counter = (idx>>1, stream),
 // key = seed, word (0,1) for even idx and (2,3) for odd idx, low word first.
 // ---------------------------------------------------------------------------
-__device__ __forceinline__ uint64_t philox_word(uint64_t seed, uint64_t stream, uint64_t idx) {
-  uint32_t c0 = (uint32_t)(idx >> 1), c1 = (uint32_t)(idx >> 33);
+// words 2 `pair` and 2 `pair` + 1
+struct PhiloxPair {
+  uint64_t w0, w1;
+};
+__device__ __forceinline__ PhiloxPair philox_pair(uint64_t seed, uint64_t stream, uint64_t pair) {
+  uint32_t c0 = (uint32_t)pair, c1 = (uint32_t)(pair >> 32);
   uint32_t c2 = (uint32_t)stream, c3 = (uint32_t)(stream >> 32);
   uint32_t k0 = (uint32_t)seed, k1 = (uint32_t)(seed >> 32);
 #pragma unroll
@@ -26,21 +30,51 @@ __device__ __forceinline__ uint64_t philox_word(uint64_t seed, uint64_t stream, 
     const uint32_t n0 = hi1 ^ c1 ^ k0, n2 = hi0 ^ c3 ^ k1;
     c0 = n0; c1 = lo1; c2 = n2; c3 = lo0;
   }
-  return (idx & 1) ? ((uint64_t)c2 | ((uint64_t)c3 << 32)) : ((uint64_t)c0 | ((uint64_t)c1 << 32));
+  return PhiloxPair{(uint64_t)c0 | ((uint64_t)c1 << 32), (uint64_t)c2 | ((uint64_t)c3 << 32)};
+}
+__device__ __forceinline__ uint64_t philox_word(uint64_t seed, uint64_t stream, uint64_t idx) {
+  const PhiloxPair p = philox_pair(seed, stream, idx >> 1);
+  return (idx & 1) ? p.w1 : p.w0;
 }
 
 // floor(u * q / 2^64) for q < 2^49: the high 64 bits of a 64x64 product.
 __device__ __forceinline__ uint64_t mul_hi64(uint64_t a, uint64_t b) { return __umul64hi(a, b); }
 
+__device__ __forceinline__ double uniform_res(uint64_t word, uint64_t q) { return u64_to_f64(mul_hi64(word, q)); }
+__device__ __forceinline__ int ternary(uint64_t word) { return (int)mul_hi64(word, 3ull) - 1; }
+__device__ __forceinline__ int cbd21(uint64_t word) {
+  return __popcll(word & 0x1FFFFFull) - __popcll((word >> 21) & 0x1FFFFFull);
+}
 __device__ __forceinline__ double sample_uniform_res(uint64_t seed, uint64_t stream, uint64_t idx, uint64_t q) {
-  return u64_to_f64(mul_hi64(philox_word(seed, stream, idx), q));
+  return uniform_res(philox_word(seed, stream, idx), q);
 }
 __device__ __forceinline__ int sample_ternary(uint64_t seed, uint64_t stream, uint64_t idx) {
-  return (int)mul_hi64(philox_word(seed, stream, idx), 3ull) - 1;
+  return ternary(philox_word(seed, stream, idx));
 }
 __device__ __forceinline__ int sample_cbd21(uint64_t seed, uint64_t stream, uint64_t idx) {
-  const uint64_t u = philox_word(seed, stream, idx);
-  return __popcll(u & 0x1FFFFFull) - __popcll((u >> 21) & 0x1FFFFFull);
+  return cbd21(philox_word(seed, stream, idx));
+}
+
+// c[w] = f(word j, j) for a thread's coefficients j = tid + w T.  A generator
+// call yields the words of two neighbouring coefficients, which two
+// neighbouring lanes own: each lane calls it for every other w and hands the
+// partner its word (quad permutation), half the calls of one per coefficient.
+template <int LOGN, class F>
+__device__ __forceinline__ void sample_coeffs(uint64_t seed, uint64_t stream, double (&c)[NttShape<LOGN>::PER], F f) {
+  constexpr int T = NttShape<LOGN>::T, PER = NttShape<LOGN>::PER;
+  const int tid = opaque_tid(), odd = tid & 1;
+  auto swap = [](uint64_t x) {
+    const int lo = __builtin_amdgcn_mov_dpp((int)(uint32_t)x, 0xB1, 0xf, 0xf, true);
+    const int hi = __builtin_amdgcn_mov_dpp((int)(uint32_t)(x >> 32), 0xB1, 0xf, 0xf, true);
+    return (uint64_t)(uint32_t)lo | ((uint64_t)(uint32_t)hi << 32);
+  };
+#pragma unroll
+  for (int w = 0; w < PER; w += 2) {
+    const PhiloxPair p = philox_pair(seed, stream, (uint64_t)((tid >> 1) + (w + odd) * (T / 2)));
+    const uint64_t got = swap(odd ? p.w0 : p.w1);
+    c[w] = f(odd ? got : p.w0, tid + w * T);
+    c[w + 1] = f(odd ? p.w1 : got, tid + (w + 1) * T);
+  }
 }
 
 __device__ __forceinline__ int orbit_shift(int t, int rot, int half) {

@@ -174,32 +174,77 @@ NTT_KERNEL(LOGN) void k_keygen(uint64_t seed, double* __restrict__ sk, DevTabs t
                     tb.fwd_tw + (size_t)pi * N, m, [&](int t, double v) { dst[t] = v; });
 }
 
-// secret-key encryption of integer coefficients m (c1 = a, c0 = -a s + m + e)
-// at level lv.  Block (c, i): ciphertext c, limb i; ciphertext c uses
-// msg[c] and seed + c.
+// Secret-key encryption of integer coefficients m (c1 = a, c0 = -a s + m + e)
+// at level lv; ciphertext c uses msg[c] and seed + c.  The two transforms:
+// a, uniform in the coefficient domain, and m + e.
+template <int LOGN, class Out>
+__device__ __forceinline__ void encrypt_a(double* s, uint64_t seed, int i, const DevTabs& tb, Out out) {
+  constexpr int N = 1 << LOGN;
+  const ModQ m = tb.mods[i];
+  const uint64_t qi = (uint64_t)m.q;
+  double c[NttShape<LOGN>::PER];
+  sample_coeffs<LOGN>(seed, kStreamEncA | (uint64_t)i, c, [&](uint64_t u, int) { return uniform_res(u, qi); });
+  ntt_fwd_regs_out<LOGN>(s, c, tb.fwd_tw + (size_t)i * N, m, out);
+}
+template <int LOGN, class Out>
+__device__ __forceinline__ void encrypt_message(double* s, const int64_t* __restrict__ msg, uint64_t seed, uint64_t stream,
+                                                int i, const DevTabs& tb, Out out) {
+  constexpr int N = 1 << LOGN;
+  const ModQ m = tb.mods[i];
+  const double t32 = tb.two32[i];
+  double c[NttShape<LOGN>::PER];
+  sample_coeffs<LOGN>(seed, stream, c,
+                      [&](uint64_t u, int j) { return reduce(i64_to_res(msg[j], m, t32) + (double)cbd21(u), m); });
+  ntt_fwd_regs_out<LOGN>(s, c, tb.fwd_tw + (size_t)i * N, m, out);
+}
+
+// block (c, i): ciphertext c, limb i
 template <int LOGN>
 NTT_KERNEL(LOGN) void k_encrypt(const int64_t* __restrict__ msg, const double* __restrict__ sk, uint64_t seed0,
                                  int lv, double* __restrict__ ct_all, double* const* __restrict__ ct_tab, DevTabs tb) {
   constexpr int N = 1 << LOGN;
   NTT_LDS(LOGN);
   const int i = blockIdx.x % (lv + 1), c = blockIdx.x / (lv + 1);
-  const uint64_t seed = seed0 + (uint64_t)c;
-  const int64_t* mc = msg + (size_t)c * N;
   double* ct = ct_tab ? ct_tab[c] : ct_all + (size_t)c * 2 * (lv + 1) * N;
   const ModQ m = tb.mods[i];
-  const uint64_t qi = (uint64_t)m.q;
   double* c0 = ct + (size_t)i * N;
   double* c1 = ct + (size_t)(lv + 1 + i) * N;
-  // a, sampled in the coefficient domain
-  ntt_fwd_out<LOGN>(s, [&](int j) { return sample_uniform_res(seed, kStreamEncA | (uint64_t)i, j, qi); },
-                    tb.fwd_tw + (size_t)i * N, m, [&](int t, double v) { c1[t] = v; });
-  const double t32 = tb.two32[i];
+  encrypt_a<LOGN>(s, seed0 + (uint64_t)c, i, tb, [&](int t, double v) { c1[t] = v; });
   const double* sk_i = sk + (size_t)i * N;
-  // c0 = m + e - a s; slot t of a is read back from what this thread wrote above
-  ntt_fwd_out<LOGN>(s, [&](int j) {
-      return reduce(i64_to_res(mc[j], m, t32) + (double)sample_cbd21(seed, kStreamEncE, (uint64_t)j), m);
-    }, tb.fwd_tw + (size_t)i * N, m,
-    [&](int t, double v) { c0[t] = reduce(v - mulmod(c1[t], sk_i[t], m), m); });
+  // slot t of a is read back from what this thread wrote above
+  encrypt_message<LOGN>(s, msg + (size_t)c * N, seed0 + (uint64_t)c, kStreamEncE, i, tb,
+                        [&](int t, double v) { c0[t] = reduce(v - mulmod(c1[t], sk_i[t], m), m); });
+}
+
+// Few ciphertexts: block (c, i, h) makes one of the two transforms, into the
+// half h of the ciphertext, and k_encrypt_join subtracts a s.  The sampling
+// and the transform of a limb on one CU are the whole time, so the two halves
+// side by side take half of it.  One ciphertext at 2^12 / 2^14 / 2^15: 19 ->
+// 9 + 2, 54 -> 23 + 3, 127 -> 53 + 15 us (of it 4 / 9 / 10 through
+// sample_coeffs).
+template <int LOGN>
+NTT_KERNEL(LOGN) void k_encrypt_half(const int64_t* __restrict__ msg, uint64_t seed0, int lv, double* __restrict__ ct_all,
+                                     double* const* __restrict__ ct_tab, DevTabs tb) {
+  constexpr int N = 1 << LOGN;
+  NTT_LDS(LOGN);
+  const int h = blockIdx.x & 1, b = blockIdx.x >> 1, i = b % (lv + 1), c = b / (lv + 1);
+  double* ct = ct_tab ? ct_tab[c] : ct_all + (size_t)c * 2 * (lv + 1) * N;
+  double* o = ct + (size_t)(h * (lv + 1) + i) * N;
+  if (h)
+    encrypt_a<LOGN>(s, seed0 + (uint64_t)c, i, tb, [&](int t, double v) { o[t] = v; });
+  else
+    encrypt_message<LOGN>(s, msg + (size_t)c * N, seed0 + (uint64_t)c, kStreamEncE, i, tb,
+                          [&](int t, double v) { o[t] = v; });
+}
+// grid (N / 256, limbs, ciphertexts)
+__global__ __launch_bounds__(256) void k_encrypt_join(const double* __restrict__ sk, int lv, int N,
+                                                      double* __restrict__ ct_all, double* const* __restrict__ ct_tab,
+                                                      const ModQ* __restrict__ mods) {
+  const int i = blockIdx.y, c = blockIdx.z;
+  const size_t t = (size_t)i * N + blockIdx.x * 256 + threadIdx.x;
+  double* ct = ct_tab ? ct_tab[c] : ct_all + (size_t)c * 2 * (lv + 1) * N;
+  const ModQ m = mods[i];
+  ct[t] = reduce(ct[t] - mulmod(ct[(size_t)(lv + 1) * N + t], sk[t], m), m);
 }
 
 // public key: block i (limb i < nl): a uniform, b = -a s + e (Sec. 2.2, the
@@ -223,33 +268,38 @@ NTT_KERNEL(LOGN) void k_pk_gen(const double* __restrict__ sk, uint64_t seed, int
 }
 
 // public-key encryption of integer coefficients m at level lv: v ternary,
-// c0 = v b + m + e0, c1 = v a + e1.  Block (c, i): ciphertext c (seed + c), limb i.
-template <int LOGN>
+// c0 = v b + m + e0, c1 = v a + e1; ciphertext c uses seed + c.  Block (c, i):
+// ciphertext c, limb i, three transforms.  Few ciphertexts (SPLIT): block
+// (c, i, h) makes half h of the ciphertext and transforms v for itself, two
+// transforms in a row instead of three: one ciphertext at 2^13 45 -> 26 us.
+template <int LOGN, bool SPLIT>
 NTT_KERNEL(LOGN) void k_encrypt_pk(const int64_t* __restrict__ msg, const double* __restrict__ pk, int pk_nl,
                                     uint64_t seed0, int lv, double* __restrict__ ct_all, DevTabs tb) {
   constexpr int N = 1 << LOGN;
   NTT_LDS(LOGN);
-  const int i = blockIdx.x % (lv + 1), c = blockIdx.x / (lv + 1);
+  const int b = SPLIT ? blockIdx.x >> 1 : blockIdx.x, i = b % (lv + 1), c = b / (lv + 1);
+  const bool h0 = !SPLIT || !(blockIdx.x & 1), h1 = !SPLIT || (blockIdx.x & 1);
   const uint64_t seed = seed0 + (uint64_t)c;
-  const int64_t* mc = msg + (size_t)c * N;
   double* ct = ct_all + (size_t)c * 2 * (lv + 1) * N;
   const ModQ m = tb.mods[i];
+  const double* tw = tb.fwd_tw + (size_t)i * N;
   double* c0 = ct + (size_t)i * N;
   double* c1 = ct + (size_t)(lv + 1 + i) * N;
-  const double* b = pk + (size_t)i * N;
-  const double* a = pk + (size_t)(pk_nl + i) * N;
-  // v in the evaluation domain, parked in c1; every later read of slot t is by
-  // the thread that wrote it
-  ntt_fwd_out<LOGN>(s, [&](int j) { return (double)sample_ternary(seed, kStreamPkV, (uint64_t)j); },
-                    tb.fwd_tw + (size_t)i * N, m, [&](int t, double v) { c1[t] = v; });
-  const double t32 = tb.two32[i];
-  ntt_fwd_out<LOGN>(s, [&](int j) {
-      return reduce(i64_to_res(mc[j], m, t32) + (double)sample_cbd21(seed, kStreamPkE0, (uint64_t)j), m);
-    }, tb.fwd_tw + (size_t)i * N, m,
-    [&](int t, double v) { c0[t] = reduce(v + mulmod(c1[t], b[t], m), m); });
-  ntt_fwd_out<LOGN>(s, [&](int j) { return (double)sample_cbd21(seed, kStreamPkE1, (uint64_t)j); },
-                    tb.fwd_tw + (size_t)i * N, m,
-                    [&](int t, double v) { c1[t] = reduce(v + mulmod(c1[t], a[t], m), m); });
+  const double* kb = pk + (size_t)i * N;
+  const double* ka = pk + (size_t)(pk_nl + i) * N;
+  // v in the evaluation domain, parked in the last half that needs it; every
+  // later read of slot t is by the thread that wrote it
+  double* vt = h1 ? c1 : c0;
+  double x[NttShape<LOGN>::PER];
+  sample_coeffs<LOGN>(seed, kStreamPkV, x, [&](uint64_t u, int) { return (double)ternary(u); });
+  ntt_fwd_regs_out<LOGN>(s, x, tw, m, [&](int t, double v) { vt[t] = v; });
+  if (h0)
+    encrypt_message<LOGN>(s, msg + (size_t)c * N, seed, kStreamPkE0, i, tb,
+                          [&](int t, double v) { c0[t] = reduce(v + mulmod(vt[t], kb[t], m), m); });
+  if (h1) {
+    sample_coeffs<LOGN>(seed, kStreamPkE1, x, [&](uint64_t u, int) { return (double)cbd21(u); });
+    ntt_fwd_regs_out<LOGN>(s, x, tw, m, [&](int t, double v) { c1[t] = reduce(v + mulmod(c1[t], ka[t], m), m); });
+  }
 }
 
 // c0 + c1 s -> canonical coefficient residues (uint64), block i = limb i
@@ -645,8 +695,13 @@ hipError_t launch_pk_gen(const LaunchCtx& L, const double* sk, uint64_t seed, in
 template <int LOGN>
 static void encrypt_pk_impl(const LaunchCtx& L, const int64_t* msg, int nct, const double* pk, int pk_nl, uint64_t seed,
                             int lv, double* ct) {
-  hipLaunchKernelGGL(k_encrypt_pk<LOGN>, dim3(nct * (lv + 1)), dim3(NttShape<LOGN>::T), 0, L.stream, msg, pk, pk_nl,
-                     seed, lv, ct, L.tb);
+  const dim3 block(NttShape<LOGN>::T);
+  if (few_transforms(2 * nct * (lv + 1)))
+    hipLaunchKernelGGL((k_encrypt_pk<LOGN, true>), dim3(2 * nct * (lv + 1)), block, 0, L.stream, msg, pk, pk_nl, seed, lv,
+                       ct, L.tb);
+  else
+    hipLaunchKernelGGL((k_encrypt_pk<LOGN, false>), dim3(nct * (lv + 1)), block, 0, L.stream, msg, pk, pk_nl, seed, lv, ct,
+                       L.tb);
 }
 hipError_t launch_encrypt_pk(const LaunchCtx& L, const int64_t* msg, int nct, const double* pk, int pk_nl,
                              uint64_t seed, int lv, double* ct) {
@@ -658,8 +713,14 @@ hipError_t launch_encrypt_pk(const LaunchCtx& L, const int64_t* msg, int nct, co
 template <int LOGN>
 static void encrypt_impl(const LaunchCtx& L, const int64_t* msg, int nct, const double* sk, uint64_t seed, int lv,
                          double* ct, double* const* ct_tab) {
-  hipLaunchKernelGGL(k_encrypt<LOGN>, dim3(nct * (lv + 1)), dim3(NttShape<LOGN>::T), 0, L.stream, msg, sk, seed, lv, ct,
-                     ct_tab, L.tb);
+  const dim3 block(NttShape<LOGN>::T);
+  if (few_transforms(2 * nct * (lv + 1))) {
+    hipLaunchKernelGGL(k_encrypt_half<LOGN>, dim3(2 * nct * (lv + 1)), block, 0, L.stream, msg, seed, lv, ct, ct_tab, L.tb);
+    hipLaunchKernelGGL(k_encrypt_join, dim3((1 << LOGN) / 256, lv + 1, nct), dim3(256), 0, L.stream, sk, lv, 1 << LOGN, ct,
+                       ct_tab, L.tb.mods);
+  } else {
+    hipLaunchKernelGGL(k_encrypt<LOGN>, dim3(nct * (lv + 1)), block, 0, L.stream, msg, sk, seed, lv, ct, ct_tab, L.tb);
+  }
 }
 hipError_t launch_encrypt(const LaunchCtx& L, const int64_t* msg, int nct, const double* sk, uint64_t seed, int lv,
                           double* ct, double* const* ct_tab) {

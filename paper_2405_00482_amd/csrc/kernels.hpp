@@ -115,6 +115,11 @@ struct DiagArgs {
   double* part;            // [slices][2][K][N]
 };
 
+// Whether `blocks` workgroups of one transform each are one round, one
+// workgroup per CU: then a transform repeated or moved to a workgroup of its
+// own costs nothing.
+inline bool few_transforms(int blocks) { return blocks <= 256; }
+
 // Whether a key-switching step with `alpha` special primes and `blocks` target
 // limbs makes both of its transforms in one launch, each target repeating the
 // transform of its source limb: while one round of workgroups, one per CU,
@@ -122,7 +127,7 @@ struct DiagArgs {
 // 2^12 / 2^13 / 2^14 15 -> 11, 29 -> 20, 54 -> 36, ModDown 17 -> 11, 31 -> 20,
 // 47 -> 38; beyond the line, 300 targets at 2^14 62 -> 70, 372 at 2^13 level
 // (one call 104).  With alpha > 1 a target would repeat alpha transforms.
-inline bool fuse_transforms(int alpha, int blocks) { return alpha == 1 && blocks <= 256; }
+inline bool fuse_transforms(int alpha, int blocks) { return alpha == 1 && few_transforms(blocks); }
 
 hipError_t launch_ntt(const LaunchCtx& L, NttOp op, const void* in, void* out, int nblocks, LimbMap map);
 hipError_t launch_keygen(const LaunchCtx& L, uint64_t seed, double* sk, int n_mod);
