@@ -55,6 +55,7 @@ struct pvfl_batch {
   hipStream_t cap_stream = nullptr;  // private stream the graph is captured on
   hipStream_t cap_stream2 = nullptr;  // second branch of the captured graph
   hipEvent_t ev_fork = nullptr, ev_join = nullptr;
+  bool shared_pt = false;  // every product reads the same plaintexts, as many of them
   bool has_X = false, has_v = false, has_y = false;
   ~pvfl_batch() {
     if (graph_exec) (void)hipGraphExecDestroy(graph_exec);
@@ -307,6 +308,9 @@ extern "C" pvfl_status pvfl_batch_create(pvfl_ctx* c, int32_t count, const pvfl_
     b->max_rows = std::max(b->max_rows, p->info.m);
     b->pt_bytes += 8.0 * (double)p->info.n_pts * b->K * N;
   }
+  b->shared_pt = std::all_of(prods.begin(), prods.end(), [&](const BatchProd& B) {
+    return B.pt == prods[0].pt && B.mprime == prods[0].mprime;
+  });
   b->inv_scale = std::pow(2.0, -p0->info.out_log2_scale);
   b->has_X = X_dev != nullptr;
   b->has_v = v_dev != nullptr;
@@ -439,6 +443,7 @@ static pvfl_status batch_product(pvfl_batch* b, void* stream) {
   a.pc = b->pc;
   a.pc_stride = 2 * Q;
   a.part = b->part;
+  a.shared_pt = b->shared_pt;
   {
     // algorithmic bytes: each distinct rotation key once, every plaintext once, digits and P*c once,
     // and each product's 2K-limb accumulator written once (the chunk partial sums the kernel

@@ -56,6 +56,7 @@ struct BatchDiagArgs {
   const double* pc;      // product p at pc + p * pc_stride, [2][lv+1][N]
   size_t pc_stride;
   double* part;          // [slot][2][K][N]
+  int shared_pt;         // every product reads the same plaintexts
 };
 
 // pg: products per group (1, 2, 4)
