@@ -6,6 +6,7 @@
 
 #include "kernels.hpp"
 #include "ntt_core.hpp"
+#include "split_ntt.hpp"
 
 namespace pvfl {
 
@@ -81,20 +82,36 @@ __device__ __forceinline__ int orbit_shift(int t, int rot, int half) {
   return (t & half) | ((t + rot) & (half - 1));
 }
 
-// Key switching with one special prime, both transforms of a step in one
-// workgroup (N <= 2^14).
-// ModUp: coefficients x of limb task.src0 (slots in(t)) converted to the
-// target limb's prime.  Barrier before writing LDS again (the transforms do).
+// Key switching with one special prime: the conversions between its two
+// transforms.  A digit is one limb and P one prime, so that the products over
+// the other primes of a digit or of P are empty: nothing to multiply by.
+struct ModUpOne {  // coefficients |x| < q of limb task.src0 to the target limb's prime
+  ModQ ms, m;
+  __device__ __forceinline__ ModUpOne(const KsTask& task, const DevTabs& tb) : ms(tb.mods[task.src0]), m(tb.mods[task.prime]) {}
+  __device__ __forceinline__ double operator()(double x) const { return reduce(x < 0.0 ? x + ms.q : x, m); }
+};
+struct ModDownOne {  // coefficients of the special limb, less its half, to limb i's prime
+  int prime;
+  ModQ mp, m;
+  double hp, h, pinv;
+  __device__ __forceinline__ ModDownOne(int i, const KsLevel* __restrict__ kl, const DevTabs& tb)
+      : prime(kl->n_q_total), mp(tb.mods[kl->n_q_total]), m(tb.mods[i]), hp(kl->down_half[kl->lv + 1]),
+        h(kl->down_half[i]), pinv(kl->down_pinv[i]) {}
+  __device__ __forceinline__ double operator()(double x) const { return reduce(canon(x + hp, mp) - h, m); }
+  __device__ __forceinline__ double result(double u, double v) const { return reduce(mulmod(u - v, pinv, m), m); }
+};
+
+// Both transforms of a step in one workgroup (N <= 2^14).
+// ModUp: coefficients x of limb task.src0 (slots in(t)), converted.  Barrier
+// before writing LDS again (the transforms do).
 template <int LOGN, class In>
-__device__ __forceinline__ void modup_source(double* s, In in, const KsTask& task, const KsLevel* __restrict__ kl,
-                                             const DevTabs& tb, double (&x)[16]) {
+__device__ __forceinline__ void modup_source(double* s, In in, const KsTask& task, const DevTabs& tb, double (&x)[16]) {
   constexpr int N = 1 << LOGN;
   const int si = task.src0;
-  const ModQ ms = tb.mods[si], m = tb.mods[task.prime];
-  const double ih = kl->up_inv_hat[si], hat = task.hat[0];
-  ntt_inv_in_regs<LOGN>(s, in, tb.inv_tw + (size_t)si * N, ms, tb.ninv[si], x);
+  const ModUpOne conv(task, tb);
+  ntt_inv_in_regs<LOGN>(s, in, tb.inv_tw + (size_t)si * N, conv.ms, tb.ninv[si], x);
 #pragma unroll
-  for (int w = 0; w < 16; ++w) x[w] = reduce(mulmod(canon(mulmod(canon(x[w], ms), ih, ms), ms), hat, m), m);
+  for (int w = 0; w < 16; ++w) x[w] = conv(x[w]);
 }
 // ModDown of ciphertext limb i: the special limb's slots in(t), the limb's own
 // slots u (as slots_from_lds orders them), results to out(t, v).
@@ -102,22 +119,49 @@ template <int LOGN, class In, class Out>
 __device__ __forceinline__ void moddown_limb(double* s, In in, const double (&u)[16], int i,
                                              const KsLevel* __restrict__ kl, const DevTabs& tb, Out out) {
   constexpr int N = 1 << LOGN, T = NttShape<LOGN>::T;
-  const int lv = kl->lv, pi = kl->n_q_total;
-  const ModQ mp = tb.mods[pi], m = tb.mods[i];
-  const double hp = kl->down_half[lv + 1], ih = kl->down_inv_hat[0];
-  const double h = kl->down_half[i], hat = kl->down_hat[i], pinv = kl->down_pinv[i];
+  const ModDownOne conv(i, kl, tb);
   double c[16], v[16];
-  ntt_inv_in_regs<LOGN>(s, in, tb.inv_tw + (size_t)pi * N, mp, tb.ninv[pi], c);
+  ntt_inv_in_regs<LOGN>(s, in, tb.inv_tw + (size_t)conv.prime * N, conv.mp, tb.ninv[conv.prime], c);
 #pragma unroll
-  for (int w = 0; w < 16; ++w) {
-    const double y = canon(mulmod(canon(c[w] + hp, mp), ih, mp), mp);
-    c[w] = reduce(mulmod(y, hat, m) - h, m);
-  }
-  ntt_fwd_regs<LOGN>(s, c, tb.fwd_tw + (size_t)i * N, m);
+  for (int w = 0; w < 16; ++w) c[w] = conv(c[w]);
+  ntt_fwd_regs<LOGN>(s, c, tb.fwd_tw + (size_t)i * N, conv.m);
   slots_from_lds<LOGN>(s, v);
 #pragma unroll
-  for (int w = 0; w < 16; ++w)
-    out((int)opaque_tid() + (w >> 1) * T + (w & 1) * (N / 2), reduce(mulmod(u[w] - v[w], pinv, m), m));
+  for (int w = 0; w < 16; ++w) out((int)opaque_tid() + (w >> 1) * T + (w & 1) * (N / 2), conv.result(u[w], v[w]));
+}
+
+// One block of a split limb's inverse (SplitNtt), to y[h 4096 ...].
+template <int LOGN, class In>
+__device__ __forceinline__ void split_inverse(double* s, int h, In in, int pi, const DevTabs& tb, double* __restrict__ y) {
+  const SplitNtt<LOGN> sp(h);
+  double c[16];
+  sp.inverse(s, in, tb.inv_tw + ((size_t)pi << LOGN), tb.mods[pi], c);
+#pragma unroll
+  for (int w = 0; w < 16; ++w) y[h * 4096 + (int)threadIdx.x + w * 256] = c[w];
+}
+// Block h of a ModUp target limb from the source limb's blocks y.
+template <int LOGN, class Y>
+__device__ __forceinline__ void split_modup(double* s, int h, Y y, const KsTask& task, const DevTabs& tb,
+                                            double* __restrict__ dst) {
+  const SplitNtt<LOGN> sp(h);
+  double v[16];
+  sp.chain(s, y, task.src0, task.prime, tb, ModUpOne(task, tb), v);
+#pragma unroll
+  for (int w = 0; w < 16; ++w) dst[sp.slot(w)] = v[w];
+}
+// Block h of ciphertext limb i after ModDown: the limb's own slots u, the
+// special limb's blocks y.
+template <int LOGN, class U, class Y>
+__device__ __forceinline__ void split_moddown(double* s, int h, U u, Y y, int i, const KsLevel* __restrict__ kl,
+                                              const DevTabs& tb, double* __restrict__ out) {
+  const SplitNtt<LOGN> sp(h);
+  const ModDownOne conv(i, kl, tb);
+  double uv[16], v[16];
+#pragma unroll
+  for (int w = 0; w < 16; ++w) uv[w] = u[sp.slot(w)];
+  sp.chain(s, y, conv.prime, i, tb, conv, v);
+#pragma unroll
+  for (int w = 0; w < 16; ++w) out[sp.slot(w)] = conv.result(uv[w], v[w]);
 }
 
 }  // namespace pvfl

@@ -443,8 +443,40 @@ NTT_KERNEL(LOGN) void k_modup_one(const double* __restrict__ ct, const double* c
     return;
   }
   double x[16];
-  modup_source<LOGN>(s, [&](int t) { return src[t]; }, task, kl, tb, x);
+  modup_source<LOGN>(s, [&](int t) { return src[t]; }, task, tb, x);
   ntt_fwd_regs_out<LOGN>(s, x, tb.fwd_tw + (size_t)pi * N, tb.mods[pi], [&](int t, double v) { dst[t] = v; });
+}
+
+// The same with each limb on N / 2^12 workgroups (SplitNtt): the inverses'
+// blocks of every source limb, then the blocks of every target limb.
+#define SPLIT_KERNEL __global__ __launch_bounds__(256)
+template <int LOGN>
+SPLIT_KERNEL void k_modup_split_inv(const double* __restrict__ ct, const double* const* __restrict__ ct_tab,
+                                    size_t ct_stride, int lv, double* __restrict__ y, DevTabs tb) {
+  using Sp = SplitNtt<LOGN>;
+  __shared__ double s[Sp::LDS];
+  const int h = blockIdx.x % Sp::S, b = blockIdx.x / Sp::S, i = b % (lv + 1), c = b / (lv + 1);
+  const double* src = (ct_tab ? ct_tab[c] : ct + (size_t)c * ct_stride) + (size_t)(lv + 1 + i) * Sp::N;
+  split_inverse<LOGN>(s, h, [&](int t) { return src[t]; }, i, tb, y + (size_t)b * Sp::N);
+}
+template <int LOGN>
+SPLIT_KERNEL void k_modup_split(const double* __restrict__ y, const double* __restrict__ ct,
+                                const double* const* __restrict__ ct_tab, size_t ct_stride,
+                                const KsLevel* __restrict__ kl, double* __restrict__ digits, size_t dig_stride, DevTabs tb) {
+  using Sp = SplitNtt<LOGN>;
+  constexpr int N = Sp::N;
+  __shared__ double s[Sp::LDS];
+  const int nt = kl->n_tasks, h = blockIdx.x % Sp::S, b = blockIdx.x / Sp::S;
+  const KsTask& task = kl->up_task[b % nt];
+  const int c = b / nt, lv = kl->lv;
+  double* dst = digits + (size_t)c * dig_stride + ((size_t)task.digit * kl->K + task.limb) * N;
+  if (task.nsrc == 0) {  // limb of the digit itself: residues kept as they are
+    const double* src = (ct_tab ? ct_tab[c] : ct + (size_t)c * ct_stride) + (size_t)(lv + 1 + task.src0) * N;
+#pragma unroll
+    for (int w = 0; w < 16; ++w) dst[h * 4096 + threadIdx.x + w * 256] = src[h * 4096 + threadIdx.x + w * 256];
+    return;
+  }
+  split_modup<LOGN>(s, h, gmem(y + (size_t)(c * (lv + 1) + task.src0) * N), task, tb, dst);
 }
 
 // ---------------------------------------------------------------------------
@@ -524,6 +556,27 @@ NTT_KERNEL(LOGN) void k_moddown_one(const double* __restrict__ u, const KsLevel*
 #pragma unroll
   for (int w = 0; w < 16; ++w) uv[w] = ui[(int)opaque_tid() + (w >> 1) * T + (w & 1) * (N / 2)];
   moddown_limb<LOGN>(s, [&](int t) { return up[t]; }, uv, i, kl, tb, [&](int t, double v) { oi[t] = v; });
+}
+
+// Each limb on N / 2^12 workgroups, as k_modup_split
+template <int LOGN>
+SPLIT_KERNEL void k_moddown_split_inv(const double* __restrict__ u, const KsLevel* __restrict__ kl, double* __restrict__ y,
+                                      DevTabs tb) {
+  using Sp = SplitNtt<LOGN>;
+  __shared__ double s[Sp::LDS];
+  const int h = blockIdx.x % Sp::S, x = blockIdx.x / Sp::S;
+  const double* src = u + ((size_t)x * kl->K + kl->lv + 1) * Sp::N;
+  split_inverse<LOGN>(s, h, [&](int t) { return src[t]; }, kl->n_q_total, tb, y + (size_t)x * Sp::N);
+}
+template <int LOGN>
+SPLIT_KERNEL void k_moddown_split(const double* __restrict__ u, const double* __restrict__ y, const KsLevel* __restrict__ kl,
+                                  double* __restrict__ out, double* const* __restrict__ out_tab, DevTabs tb) {
+  using Sp = SplitNtt<LOGN>;
+  constexpr int N = Sp::N;
+  __shared__ double s[Sp::LDS];
+  const int lv = kl->lv, h = blockIdx.x % Sp::S, b = blockIdx.x / Sp::S, i = b % (lv + 1), x = b / (lv + 1);
+  double* oi = out_tab ? out_tab[x >> 1] + ((size_t)(x & 1) * (lv + 1) + i) * N : out + ((size_t)x * (lv + 1) + i) * N;
+  split_moddown<LOGN>(s, h, gmem(u + ((size_t)x * kl->K + i) * N), gmem(y + (size_t)x * N), i, kl, tb, oi);
 }
 
 // Rescale by q_lv (drop the last limb, coefficient-wise rounding) on polys
@@ -767,6 +820,16 @@ hipError_t launch_rotkey_gen(const LaunchCtx& L, const double* sk, const RotKeyL
 template <int LOGN>
 static void modup_impl(const LaunchCtx& L, const double* ct, const double* const* ct_tab, size_t ct_stride, int nct,
                        int lv, int alpha, const KsLevel* kl_dev, int n_tasks, double* y, double* digits, size_t dig_stride) {
+  if constexpr (LOGN == 13 || LOGN == 14) {
+    constexpr int S = SplitNtt<LOGN>::S;
+    if (split_transforms(alpha, nct * n_tasks * S)) {
+      hipLaunchKernelGGL(k_modup_split_inv<LOGN>, dim3(nct * (lv + 1) * S), dim3(256), 0, L.stream, ct, ct_tab, ct_stride, lv,
+                         y, L.tb);
+      hipLaunchKernelGGL(k_modup_split<LOGN>, dim3(nct * n_tasks * S), dim3(256), 0, L.stream, y, ct, ct_tab, ct_stride,
+                         kl_dev, digits, dig_stride, L.tb);
+      return;
+    }
+  }
   if constexpr (LOGN <= 14) {
     if (fuse_transforms(alpha, nct * n_tasks)) {
       hipLaunchKernelGGL(k_modup_one<LOGN>, dim3(nct * n_tasks), dim3(NttShape<LOGN>::T), 0, L.stream, ct, ct_tab, ct_stride,
@@ -789,6 +852,15 @@ hipError_t launch_modup(const LaunchCtx& L, const double* ct, size_t ct_stride, 
 template <int LOGN>
 static void moddown_impl(const LaunchCtx& L, const double* u, int npoly, int lv, int alpha, const KsLevel* kl_dev,
                          double* y, double* out, double* const* out_tab) {
+  if constexpr (LOGN == 13 || LOGN == 14) {
+    constexpr int S = SplitNtt<LOGN>::S;
+    if (split_transforms(alpha, npoly * (lv + 1) * S)) {
+      hipLaunchKernelGGL(k_moddown_split_inv<LOGN>, dim3(npoly * S), dim3(256), 0, L.stream, u, kl_dev, y, L.tb);
+      hipLaunchKernelGGL(k_moddown_split<LOGN>, dim3(npoly * (lv + 1) * S), dim3(256), 0, L.stream, u, y, kl_dev, out,
+                         out_tab, L.tb);
+      return;
+    }
+  }
   if constexpr (LOGN <= 14) {
     if (fuse_transforms(alpha, npoly * (lv + 1))) {
       hipLaunchKernelGGL(k_moddown_one<LOGN>, dim3(npoly * (lv + 1)), dim3(NttShape<LOGN>::T), 0, L.stream, u, kl_dev, out,

@@ -129,6 +129,13 @@ inline bool few_transforms(int blocks) { return blocks <= 256; }
 // (one call 104).  With alpha > 1 a target would repeat alpha transforms.
 inline bool fuse_transforms(int alpha, int blocks) { return alpha == 1 && few_transforms(blocks); }
 
+// Whether it splits every limb over N / 2^12 workgroups, `blocks` in all
+// (SplitNtt): again while one round holds them.  One ciphertext, one launch
+// and the split's two, us: ModUp at 2^13 / 2^14 17 -> 9 + 7, 31 -> 14 + 9,
+// ModDown 18 -> 10 + 7, 33 -> 16 + 8 (the rotations' steps gain nothing at 2^13
+// and stay in one launch).
+inline bool split_transforms(int alpha, int blocks) { return alpha == 1 && blocks <= 256; }
+
 hipError_t launch_ntt(const LaunchCtx& L, NttOp op, const void* in, void* out, int nblocks, LimbMap map);
 hipError_t launch_keygen(const LaunchCtx& L, uint64_t seed, double* sk, int n_mod);
 // nct ciphertexts [nct][2][lv+1][N] from messages [nct][N]; ciphertext c uses seed + c

@@ -115,12 +115,13 @@ __device__ __forceinline__ void pass_bases(int (&base)[16 >> S], int ls) {
 // lies inside one butterfly group of stage lg0 (group g0 = base >> (LOGN -
 // lg0)); at stage lg0 + st it spans 2^st groups g0 * 2^st + k, whose
 // twiddles are contiguous in the table, so a pass reads 2^S - 1 twiddles per
-// set.  No reduction here: a butterfly adds less than q in magnitude (the
+// set.  `root` > 1: the transform is the block root - R of a larger one's after
+// its first log2 R stages (R the power of two below or at root).  No reduction here: a butterfly adds less than q in magnitude (the
 // mulmod output is below q), and the caller re-centres often enough that
 // every value stays below 2^51.
 template <int LOGN, int S>
 __device__ __forceinline__ void ct_pass_regs(double (&x)[16], int lg0, const int (&base)[16 >> S],
-                                             const double* __restrict__ tw, ModQ m) {
+                                             const double* __restrict__ tw, ModQ m, int root = 1) {
   constexpr int SET = 1 << S;
 #pragma unroll
   for (int q = 0; q < (16 >> S); ++q) {
@@ -129,7 +130,7 @@ __device__ __forceinline__ void ct_pass_regs(double (&x)[16], int lg0, const int
     for (int st = 0; st < S; ++st) {
       const int half = SET >> (st + 1);
       double w[1 << (S > 0 ? S - 1 : 0)];
-      const double* tws = tw + (1 << (lg0 + st)) + (g0 << st);
+      const double* tws = tw + (root << (lg0 + st)) + (g0 << st);
 #pragma unroll
       for (int k = 0; k < (1 << st); ++k) w[k] = tws[k];
 #pragma unroll
@@ -199,7 +200,8 @@ __device__ __forceinline__ void wave_lds_sync() {
 // s[lds_pad(j)] after the call (which ends with a barrier).  The call begins
 // with a barrier, so `s` may still be in use by the caller before it.
 template <int LOGN>
-__device__ __forceinline__ void ntt_fwd_regs(double* s, const double (&c)[16], const double* __restrict__ tw, ModQ m) {
+__device__ __forceinline__ void ntt_fwd_regs(double* s, const double (&c)[16], const double* __restrict__ tw, ModQ m,
+                                             int root = 1) {
   static_assert(LOGN >= 12 && LOGN <= 14, "one wave owns 1024 elements of an LDS-resident limb");
   double x[16];
   const int tid = opaque_tid();
@@ -212,7 +214,7 @@ __device__ __forceinline__ void ntt_fwd_regs(double* s, const double (&c)[16], c
   for (int u = 8; u < 16; ++u) x[u] = c[u];
   {
     const int base[1] = {tid};
-    ct_pass_regs<LOGN, 4>(x, 0, base, tw, m);
+    ct_pass_regs<LOGN, 4>(x, 0, base, tw, m, root);
     __syncthreads();
     lds_store_c<4, LOGN - 4>(s, x, base);
   }
@@ -222,7 +224,7 @@ __device__ __forceinline__ void ntt_fwd_regs(double* s, const double (&c)[16], c
     int base[1];
     pass_bases<LOGN, 4>(base, LS);
     lds_load_c<4, LS>(s, x, base);
-    ct_pass_regs<LOGN, 4>(x, 4, base, tw, m);
+    ct_pass_regs<LOGN, 4>(x, 4, base, tw, m, root);
     recentre(x, m);
     lds_store_c<4, LS>(s, x, base);
   }
@@ -232,7 +234,7 @@ __device__ __forceinline__ void ntt_fwd_regs(double* s, const double (&c)[16], c
     int base[1];
     pass_bases<LOGN, 4>(base, LS);
     lds_load_c<4, LS>(s, x, base);
-    ct_pass_regs<LOGN, 4>(x, 8, base, tw, m);
+    ct_pass_regs<LOGN, 4>(x, 8, base, tw, m, root);
     if constexpr (LOGN == 12) recentre(x, m);
     lds_store_c<4, LS>(s, x, base);
   }
@@ -243,7 +245,7 @@ __device__ __forceinline__ void ntt_fwd_regs(double* s, const double (&c)[16], c
 #pragma unroll
     for (int q = 0; q < NQ; ++q) base[q] = 16 * tid + (q << S);
     lds_load_c<S, 0>(s, x, base);
-    ct_pass_regs<LOGN, S>(x, 12, base, tw, m);
+    ct_pass_regs<LOGN, S>(x, 12, base, tw, m, root);
     recentre(x, m);
     lds_store_c<S, 0>(s, x, base);
   }
@@ -270,7 +272,8 @@ __device__ __forceinline__ void ntt_fwd(double* s, Load load, const double* __re
 // differences through their twiddle).
 template <int LOGN, int S>
 __device__ __forceinline__ void gs_pass_regs(double (&x)[16], int lg1, const int (&base)[16 >> S],
-                                             const double* __restrict__ itw, ModQ m, const double* scale = nullptr) {
+                                             const double* __restrict__ itw, ModQ m, int root = 1,
+                                             const double* scale = nullptr) {
   static_assert(S <= 4, "the growth of the sums");
   constexpr int SET = 1 << S;
 #pragma unroll
@@ -281,7 +284,7 @@ __device__ __forceinline__ void gs_pass_regs(double (&x)[16], int lg1, const int
       const int half = 1 << st;
       const int gbase = base[q] >> (LOGN - lg);  // group of element u = 0 at this stage
       double w[1 << (S > 0 ? S - 1 : 0)];
-      const double* tws = itw + (1 << lg) + gbase;
+      const double* tws = itw + (root << lg) + gbase;
 #pragma unroll
       for (int k = 0; k < (SET >> (st + 1)); ++k) w[k] = tws[k];
       const bool scaled = scale && st == S - 1;
@@ -309,9 +312,10 @@ __device__ __forceinline__ void gs_pass_regs(double (&x)[16], int lg1, const int
 // passes -- with wave-local LDS exchanges; after one workgroup barrier the
 // last four stages (spans N/16 .. N/2) run on the thread's own coefficients
 // {tid + u N/16}.
+// ninv null: not scaled; root: as in ct_pass_regs.
 template <int LOGN>
 __device__ __forceinline__ void ntt_inv_regs(double* s, double (&c)[16], const double* __restrict__ itw, ModQ m,
-                                             double ninv) {
+                                             const double* ninv, int root) {
   static_assert(LOGN >= 12 && LOGN <= 14, "one wave owns 1024 elements of an LDS-resident limb");
   double x[16];
   const int tid = opaque_tid();
@@ -321,7 +325,7 @@ __device__ __forceinline__ void ntt_inv_regs(double* s, double (&c)[16], const d
 #pragma unroll
     for (int q = 0; q < NQ; ++q) base[q] = 16 * tid + (q << S);
     lds_load_c<S, 0>(s, x, base);
-    gs_pass_regs<LOGN, S>(x, LOGN - 1, base, itw, m);
+    gs_pass_regs<LOGN, S>(x, LOGN - 1, base, itw, m, root);
     lds_store_c<S, 0>(s, x, base);
     wave_lds_sync();
   }
@@ -330,7 +334,7 @@ __device__ __forceinline__ void ntt_inv_regs(double* s, double (&c)[16], const d
     int base[1];
     pass_bases<LOGN, 4>(base, LS);
     lds_load_c<4, LS>(s, x, base);
-    gs_pass_regs<LOGN, 4>(x, 11, base, itw, m);
+    gs_pass_regs<LOGN, 4>(x, 11, base, itw, m, root);
     lds_store_c<4, LS>(s, x, base);
   }
   wave_lds_sync();
@@ -339,17 +343,23 @@ __device__ __forceinline__ void ntt_inv_regs(double* s, double (&c)[16], const d
     int base[1];
     pass_bases<LOGN, 4>(base, LS);
     lds_load_c<4, LS>(s, x, base);
-    gs_pass_regs<LOGN, 4>(x, 7, base, itw, m);
+    gs_pass_regs<LOGN, 4>(x, 7, base, itw, m, root);
     lds_store_c<4, LS>(s, x, base);
   }
   __syncthreads();
   {  // spans N/16 .. N/2 on the thread's coefficients tid + u N/16
     const int base[1] = {tid};
     lds_load_c<4, LOGN - 4>(s, x, base);
-    gs_pass_regs<LOGN, 4>(x, 3, base, itw, m, &ninv);
+    gs_pass_regs<LOGN, 4>(x, 3, base, itw, m, root, ninv);
 #pragma unroll
     for (int u = 0; u < 16; ++u) c[u] = x[u];
   }
+}
+
+template <int LOGN>
+__device__ __forceinline__ void ntt_inv_regs(double* s, double (&c)[16], const double* __restrict__ itw, ModQ m,
+                                             double ninv) {
+  ntt_inv_regs<LOGN>(s, c, itw, m, &ninv, 1);
 }
 
 // inverse transform handing coefficient j to store(j, v)

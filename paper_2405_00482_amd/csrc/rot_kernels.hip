@@ -177,7 +177,7 @@ ROT_KERNEL(LOGN) void k_rot_modup_one(RotBatch b, int pre, const KsLevel* __rest
   const auto* src = gmem(b.it[it].ct) + (size_t)(kl->lv + 1 + task.src0) * N;
   double* dst = digits + (size_t)it * dig_stride + ((size_t)task.digit * kl->K + task.limb) * N;
   double x[16];
-  modup_source<LOGN>(s, [&](int t) { return src[orbit_shift(t, rot, N / 2)]; }, task, kl, tb, x);
+  modup_source<LOGN>(s, [&](int t) { return src[orbit_shift(t, rot, N / 2)]; }, task, tb, x);
   ntt_fwd_regs_out<LOGN>(s, x, tb.fwd_tw + (size_t)pi * N, tb.mods[pi], [&](int t, double v) { dst[t] = v; });
 }
 
