@@ -82,6 +82,28 @@ __device__ __forceinline__ int orbit_shift(int t, int rot, int half) {
   return (t & half) | ((t + rot) & (half - 1));
 }
 
+// Base conversion of a thread's coefficients j = tid + w T: the sum over `n`
+// limbs of y_u[j] hat(u) mod m, less `h`, centred.  Source by source, so that
+// a source's loads are in flight together; one limb alone has hat = 1.
+template <int LOGN, class Y, class Hat>
+__device__ __forceinline__ void convert_coeffs(Y y, int n, Hat hat, double h, ModQ m, double (&x)[NttShape<LOGN>::PER]) {
+  constexpr int N = 1 << LOGN, T = NttShape<LOGN>::T, PER = NttShape<LOGN>::PER;
+#pragma unroll
+  for (int w = 0; w < PER; ++w) x[w] = y[(int)opaque_tid() + w * T];
+  if (n > 1) {
+    const double h0 = hat(0);
+#pragma unroll
+    for (int w = 0; w < PER; ++w) x[w] = mulmod(x[w], h0, m);
+    for (int u = 1; u < n; ++u) {
+      const double hu = hat(u);
+#pragma unroll
+      for (int w = 0; w < PER; ++w) x[w] += mulmod(y[(size_t)u * N + (int)opaque_tid() + w * T], hu, m);
+    }
+  }
+#pragma unroll
+  for (int w = 0; w < PER; ++w) x[w] = reduce(x[w] - h, m);
+}
+
 // Key switching with one special prime: the conversions between its two
 // transforms.  A digit is one limb and P one prime, so that the products over
 // the other primes of a digit or of P are empty: nothing to multiply by.

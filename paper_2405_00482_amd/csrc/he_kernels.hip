@@ -413,12 +413,9 @@ NTT_KERNEL(LOGN) void k_modup_conv(const double* __restrict__ y, const double* _
     for (int t = threadIdx.x; t < N; t += T) dst[t] = src[t];
     return;
   }
-  const double* yc = y + (size_t)c * (lv + 1) * N;
-  ntt_fwd_out<LOGN>(s, [&](int j) {
-      double acc = 0.0;
-      for (int u = 0; u < nsrc; ++u) acc += mulmod(yc[(size_t)(src0 + u) * N + j], task.hat[u], m);
-      return reduce(acc, m);
-    }, tb.fwd_tw + (size_t)pi * N, m, [&](int t, double v) { dst[t] = v; });
+  double x[NttShape<LOGN>::PER];
+  convert_coeffs<LOGN>(gmem(y + (size_t)(c * (lv + 1) + src0) * N), nsrc, [&](int u) { return task.hat[u]; }, 0.0, m, x);
+  ntt_fwd_regs_out<LOGN>(s, x, tb.fwd_tw + (size_t)pi * N, m, [&](int t, double v) { dst[t] = v; });
 }
 
 // Both steps in one launch for alpha = 1 (a digit is one limb): every target
@@ -517,26 +514,25 @@ NTT_KERNEL(LOGN) void k_moddown_q(const double* __restrict__ u, const double* __
   const double pinv = kl->down_pinv[i];
   const double* ui = u + ((size_t)x * K + i) * N;
   double* oi = out_tab ? out_tab[x >> 1] + ((size_t)(x & 1) * (lv + 1) + i) * N : out + ((size_t)x * (lv + 1) + i) * N;
-  auto conv = [&](int c) {
-    double acc = -h;
-    for (int k = 0; k < alpha; ++k) acc += mulmod(yx[(size_t)k * N + c], kl->down_hat[k * kMaxLimbs + i], m);
-    return reduce(acc, m);
+  double c[NttShape<LOGN>::PER];
+  auto conv = [&] {
+    convert_coeffs<LOGN>(gmem(yx), alpha, [&](int k) { return kl->down_hat[k * kMaxLimbs + i]; }, h, m, c);
   };
   if constexpr (LOGN <= 14) {
     constexpr int T = NttShape<LOGN>::T;
-    double c[16], v[16], uv[16];  // u loaded before the transform: one memory latency instead of eight
+    double v[16], uv[16];  // u loaded before the transform: one memory latency instead of eight
 #pragma unroll
     for (int w = 0; w < 16; ++w) uv[w] = ui[(int)opaque_tid() + (w >> 1) * T + (w & 1) * (N / 2)];
-#pragma unroll
-    for (int w = 0; w < 16; ++w) c[w] = conv((int)opaque_tid() + w * T);
+    conv();
     ntt_fwd_regs<LOGN>(s, c, tb.fwd_tw + (size_t)i * N, m);
     slots_from_lds<LOGN>(s, v);
 #pragma unroll
     for (int w = 0; w < 16; ++w)
       oi[(int)opaque_tid() + (w >> 1) * T + (w & 1) * (N / 2)] = reduce(mulmod(uv[w] - v[w], pinv, m), m);
   } else {
-    ntt_fwd_out<LOGN>(s, conv, tb.fwd_tw + (size_t)i * N, m,
-                      [&](int t, double v) { oi[t] = reduce(mulmod(ui[t] - v, pinv, m), m); });
+    conv();
+    ntt_fwd_regs_out<LOGN>(s, c, tb.fwd_tw + (size_t)i * N, m,
+                           [&](int t, double v) { oi[t] = reduce(mulmod(ui[t] - v, pinv, m), m); });
   }
 }
 

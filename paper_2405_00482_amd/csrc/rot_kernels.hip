@@ -155,13 +155,11 @@ ROT_KERNEL(LOGN) void k_rot_modup_conv(const double* __restrict__ y, const KsLev
   if (nsrc == 0) return;  // the digit's own limb: read from c1
   const int pi = task->prime;
   const ModQ m = tb.mods[pi];
-  const double* yc = y + ((size_t)it * (kl->lv + 1) + task->src0) * N;
   double* dst = digits + (size_t)it * dig_stride + ((size_t)task->digit * kl->K + task->limb) * N;
-  ntt_fwd_out<LOGN>(s, [&](int j) {
-      double acc = 0.0;
-      for (int u = 0; u < nsrc; ++u) acc += mulmod(yc[(size_t)u * N + j], task->hat[u], m);
-      return reduce(acc, m);
-    }, tb.fwd_tw + (size_t)pi * N, m, [&](int t, double v) { dst[t] = v; });
+  double x[NttShape<LOGN>::PER];
+  convert_coeffs<LOGN>(gmem(y + ((size_t)it * (kl->lv + 1) + task->src0) * N), nsrc, [&](int u) { return task->hat[u]; },
+                       0.0, m, x);
+  ntt_fwd_regs_out<LOGN>(s, x, tb.fwd_tw + (size_t)pi * N, m, [&](int t, double v) { dst[t] = v; });
 }
 
 // block (item, task), alpha = 1: both ModUp transforms (k_modup_one)
@@ -259,10 +257,9 @@ ROT_KERNEL(LOGN) void k_rot_down_q(RotBatch b, int pre, int add, const KsLevel* 
   const auto* cx = gmem(ct) + (size_t)(x * (lv + 1) + i) * N;
   const auto* in = gmem(inner) + ((size_t)(2 * it + x) * kl->K + i) * N;
   double* o = b.it[it].out + (size_t)(x * (lv + 1) + i) * N;
-  auto conv = [&](int c) {
-    double acc = -h;
-    for (int k = 0; k < alpha; ++k) acc += mulmod(yx[(size_t)k * N + c], kl->down_hat[k * kMaxLimbs + i], m);
-    return reduce(acc, m);
+  double c[NttShape<LOGN>::PER];
+  auto conv = [&] {
+    convert_coeffs<LOGN>(gmem(yx), alpha, [&](int k) { return kl->down_hat[k * kMaxLimbs + i]; }, h, m, c);
   };
   if constexpr (LOGN <= 14) {
     double u[16];
@@ -282,16 +279,16 @@ ROT_KERNEL(LOGN) void k_rot_down_q(RotBatch b, int pre, int add, const KsLevel* 
       for (int w = 0; w < 16; ++w) u[w] += mulmod(cx[(int)opaque_tid() + (w >> 1) * T + (w & 1) * H], pmod, m);
     }
     recentre(u, m);
-    double c[16], v[16];
-#pragma unroll
-    for (int w = 0; w < 16; ++w) c[w] = conv((int)opaque_tid() + w * T);
+    double v[16];
+    conv();
     ntt_fwd_regs<LOGN>(s, c, tb.fwd_tw + (size_t)i * N, m);
     slots_from_lds<LOGN>(s, v);
 #pragma unroll
     for (int w = 0; w < 16; ++w)
       o[(int)opaque_tid() + (w >> 1) * T + (w & 1) * H] = reduce(mulmod(u[w] - v[w], pinv, m), m);
   } else {
-    ntt_fwd_out<LOGN>(s, conv, tb.fwd_tw + (size_t)i * N, m, [&](int t, double v) {
+    conv();
+    ntt_fwd_regs_out<LOGN>(s, c, tb.fwd_tw + (size_t)i * N, m, [&](int t, double v) {
       double u;
       if (inner) {
         u = in[t];
