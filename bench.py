@@ -542,15 +542,15 @@ def main():
     kd_bytes = kd["bytes"] / max(kd["launches"], 1)
     kd_traffic = measured_traffic(launch_key, KERNEL_SYMBOL["fused_diagonal"])
     # its arithmetic in FP64 operations (each instruction one): per (product,
-    # rotated diagonal, limb, index) 2 beta key products and the 2 plaintext
-    # products at 6 each (multiply, FMA, multiply, round, FMA, add), 2 (beta - 1)
-    # + 2 additions, and P c0's addition on the Q limbs; diagonal 0 (no
-    # rotation) only its 2 plaintext products and 2 additions
+    # rotated diagonal, limb, index) two exact sums of beta key products (3
+    # operations for the first, 4 for each further), P c0's addition on the Q
+    # limbs, two folds and two plaintext products at 4 each; diagonal 0 (no
+    # rotation) only its two plaintext products
     lv1, alpha = len(d["q"]), len(d["p"])
     beta, K = -(-lv1 // alpha), lv1 + alpha
     elems = binfo["pt_bytes"] / 8
     elems0 = sum(p.info["row_blocks"] * p.info["col_blocks"] for p in plans) * K * ctx.N
-    kd_ops = (elems - elems0) * (12 * beta + 12 + 2 * (beta - 1) + 2 + lv1 / K) + elems0 * (12 + 2)
+    kd_ops = (elems - elems0) * (2 * (4 * beta - 1) + lv1 / K + 16) + elems0 * 8
     roofline_ks = {"bound": "hbm", "kernel": KERNEL_SYMBOL["fused_diagonal"],
                    "achieved": kd_bytes / kd_s / 1e9 if kd_s > 0 else 0.0, "peak": HBM_PEAK_GBS, "unit": "GB/s",
                    "frac": (kd_bytes / kd_s / 1e9 / HBM_PEAK_GBS) if kd_s > 0 else 0.0, "traffic": kd_traffic,
