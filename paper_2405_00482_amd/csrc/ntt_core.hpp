@@ -116,9 +116,10 @@ __device__ __forceinline__ void pass_bases(int (&base)[16 >> S], int ls) {
 // lg0)); at stage lg0 + st it spans 2^st groups g0 * 2^st + k, whose
 // twiddles are contiguous in the table, so a pass reads 2^S - 1 twiddles per
 // set.  `root` > 1: the transform is the block root - R of a larger one's after
-// its first log2 R stages (R the power of two below or at root).  No reduction here: a butterfly adds less than q in magnitude (the
-// mulmod output is below q), and the caller re-centres often enough that
-// every value stays below 2^51.
+// its first log2 R stages (R the power of two below or at root).  No reduction
+// here: a butterfly adds less than q in magnitude (the mulmod output is below
+// q), and the caller re-centres often enough that every value stays below
+// 2^51.
 template <int LOGN, int S>
 __device__ __forceinline__ void ct_pass_regs(double (&x)[16], int lg0, const int (&base)[16 >> S],
                                              const double* __restrict__ tw, ModQ m, int root = 1) {
@@ -141,6 +142,34 @@ __device__ __forceinline__ void ct_pass_regs(double (&x)[16], int lg0, const int
         x[q * SET + u] = U + V;
         x[q * SET + u + half] = U - V;
       }
+    }
+  }
+}
+
+// Four stages from lg0 on one set per thread whose group g0 is the same for the
+// whole wave: its 15 twiddles go through the constant address space into
+// scalar registers.  Vector loads take the vector cache 16 cycles each and
+// wait for the stores of slots that a loop over limbs has issued just before.
+// 1024 polynomials of 5 limbs at 2^14, import and export: 677 -> 664 us (its
+// first use in the forward passes alone: 669); a batch's step 7.385 -> 7.36 ms.
+__device__ __forceinline__ void ct_uniform_pass(double (&x)[16], int lg0, int g0, const double* __restrict__ tw, ModQ m) {
+  const auto* ctw = (const __attribute__((address_space(4))) double*)(uint64_t)tw;
+  double w[16];
+#pragma unroll
+  for (int k = 1; k < 16; ++k) {
+    const int st = k < 2 ? 0 : k < 4 ? 1 : k < 8 ? 2 : 3;
+    w[k] = ctw[(1 << (lg0 + st)) + (g0 << st) + (k - (1 << st))];
+  }
+#pragma unroll
+  for (int st = 0; st < 4; ++st) {
+    const int half = 16 >> (st + 1);
+#pragma unroll
+    for (int u = 0; u < 16; ++u) {
+      if (u & half) continue;
+      const double U = x[u];
+      const double V = mulmod(x[u + half], w[(1 << st) + (u >> (4 - st))], m);
+      x[u] = U + V;
+      x[u + half] = U - V;
     }
   }
 }
@@ -199,7 +228,7 @@ __device__ __forceinline__ void wave_lds_sync() {
 // The result is left in LDS in bit-reversed order, centred: read it with
 // s[lds_pad(j)] after the call (which ends with a barrier).  The call begins
 // with a barrier, so `s` may still be in use by the caller before it.
-template <int LOGN>
+template <int LOGN, bool BLOCK = false>
 __device__ __forceinline__ void ntt_fwd_regs(double* s, const double (&c)[16], const double* __restrict__ tw, ModQ m,
                                              int root = 1) {
   static_assert(LOGN >= 12 && LOGN <= 14, "one wave owns 1024 elements of an LDS-resident limb");
@@ -214,7 +243,10 @@ __device__ __forceinline__ void ntt_fwd_regs(double* s, const double (&c)[16], c
   for (int u = 8; u < 16; ++u) x[u] = c[u];
   {
     const int base[1] = {tid};
-    ct_pass_regs<LOGN, 4>(x, 0, base, tw, m, root);
+    if constexpr (BLOCK)
+      ct_pass_regs<LOGN, 4>(x, 0, base, tw, m, root);
+    else
+      ct_uniform_pass(x, 0, 0, tw, m);
     __syncthreads();
     lds_store_c<4, LOGN - 4>(s, x, base);
   }
@@ -224,7 +256,10 @@ __device__ __forceinline__ void ntt_fwd_regs(double* s, const double (&c)[16], c
     int base[1];
     pass_bases<LOGN, 4>(base, LS);
     lds_load_c<4, LS>(s, x, base);
-    ct_pass_regs<LOGN, 4>(x, 4, base, tw, m, root);
+    if constexpr (LOGN == 14 && !BLOCK)  // a group of stage 4 is one wave's 1024 elements
+      ct_uniform_pass(x, 4, __builtin_amdgcn_readfirstlane(base[0] >> 10), tw, m);
+    else
+      ct_pass_regs<LOGN, 4>(x, 4, base, tw, m, root);
     recentre(x, m);
     lds_store_c<4, LS>(s, x, base);
   }
@@ -267,13 +302,10 @@ __device__ __forceinline__ void ntt_fwd(double* s, Load load, const double* __re
 // one group of stage lg1-S+1; at stage lg1-st it spans 2^(S-1-st) groups with
 // contiguous twiddles.  From centred inputs the sums double at every stage, so
 // that the differences of the fourth stage are below 8q < 2^51, which mulmod
-// takes: no reduction inside a pass of S <= 4 stages.  `scale`, if not null,
-// multiplies the pass's results (the sums of its last stage directly, the
-// differences through their twiddle).
+// takes: no reduction inside a pass of S <= 4 stages.
 template <int LOGN, int S>
 __device__ __forceinline__ void gs_pass_regs(double (&x)[16], int lg1, const int (&base)[16 >> S],
-                                             const double* __restrict__ itw, ModQ m, int root = 1,
-                                             const double* scale = nullptr) {
+                                             const double* __restrict__ itw, ModQ m, int root = 1) {
   static_assert(S <= 4, "the growth of the sums");
   constexpr int SET = 1 << S;
 #pragma unroll
@@ -287,16 +319,42 @@ __device__ __forceinline__ void gs_pass_regs(double (&x)[16], int lg1, const int
       const double* tws = itw + (root << lg) + gbase;
 #pragma unroll
       for (int k = 0; k < (SET >> (st + 1)); ++k) w[k] = tws[k];
-      const bool scaled = scale && st == S - 1;
-      if (scaled) w[0] = reduce(mulmod(w[0], *scale, m), m);
 #pragma unroll
       for (int u = 0; u < SET; ++u) {
         if (u & half) continue;
         const double U = x[q * SET + u];
         const double V = x[q * SET + u + half];
-        x[q * SET + u] = scaled ? mulmod(U + V, *scale, m) : U + V;
+        x[q * SET + u] = U + V;
         x[q * SET + u + half] = mulmod(U - V, w[u >> (st + 1)], m);
       }
+    }
+  }
+  recentre(x, m);
+}
+
+// Four stages ending at lg0 on one set per thread whose group g0 of stage lg0
+// is the same for the whole wave (ct_uniform_pass backwards).  `scale`, if not
+// null, multiplies the results: the sums of the last stage directly, the
+// differences through their twiddle.
+__device__ __forceinline__ void gs_uniform_pass(double (&x)[16], int lg0, int g0, const double* __restrict__ itw, ModQ m,
+                                                const double* scale = nullptr) {
+  const auto* ctw = (const __attribute__((address_space(4))) double*)(uint64_t)itw;
+  double w[16];
+#pragma unroll
+  for (int k = 1; k < 16; ++k) {
+    const int st = k < 2 ? 0 : k < 4 ? 1 : k < 8 ? 2 : 3;
+    w[k] = ctw[(1 << (lg0 + st)) + (g0 << st) + (k - (1 << st))];
+  }
+  if (scale) w[1] = reduce(mulmod(w[1], *scale, m), m);
+#pragma unroll
+  for (int st = 3; st >= 0; --st) {
+    const int half = 8 >> st;
+#pragma unroll
+    for (int u = 0; u < 16; ++u) {
+      if (u & half) continue;
+      const double U = x[u], V = x[u + half];
+      x[u] = scale && st == 0 ? mulmod(U + V, *scale, m) : U + V;
+      x[u + half] = mulmod(U - V, w[(1 << st) + (u >> (4 - st))], m);
     }
   }
   recentre(x, m);
@@ -312,10 +370,11 @@ __device__ __forceinline__ void gs_pass_regs(double (&x)[16], int lg1, const int
 // passes -- with wave-local LDS exchanges; after one workgroup barrier the
 // last four stages (spans N/16 .. N/2) run on the thread's own coefficients
 // {tid + u N/16}.
-// ninv null: not scaled; root: as in ct_pass_regs.
-template <int LOGN>
+// BLOCK: the block `root` of a larger transform (as in ct_pass_regs), not
+// scaled.
+template <int LOGN, bool BLOCK = false>
 __device__ __forceinline__ void ntt_inv_regs(double* s, double (&c)[16], const double* __restrict__ itw, ModQ m,
-                                             const double* ninv, int root) {
+                                             double ninv, int root = 1) {
   static_assert(LOGN >= 12 && LOGN <= 14, "one wave owns 1024 elements of an LDS-resident limb");
   double x[16];
   const int tid = opaque_tid();
@@ -343,23 +402,23 @@ __device__ __forceinline__ void ntt_inv_regs(double* s, double (&c)[16], const d
     int base[1];
     pass_bases<LOGN, 4>(base, LS);
     lds_load_c<4, LS>(s, x, base);
-    gs_pass_regs<LOGN, 4>(x, 7, base, itw, m, root);
+    if constexpr (LOGN == 14 && !BLOCK)  // as ntt_fwd_regs
+      gs_uniform_pass(x, 4, __builtin_amdgcn_readfirstlane(base[0] >> 10), itw, m);
+    else
+      gs_pass_regs<LOGN, 4>(x, 7, base, itw, m, root);
     lds_store_c<4, LS>(s, x, base);
   }
   __syncthreads();
   {  // spans N/16 .. N/2 on the thread's coefficients tid + u N/16
     const int base[1] = {tid};
     lds_load_c<4, LOGN - 4>(s, x, base);
-    gs_pass_regs<LOGN, 4>(x, 3, base, itw, m, root, ninv);
+    if constexpr (BLOCK)
+      gs_pass_regs<LOGN, 4>(x, 3, base, itw, m, root);
+    else
+      gs_uniform_pass(x, 0, 0, itw, m, &ninv);
 #pragma unroll
     for (int u = 0; u < 16; ++u) c[u] = x[u];
   }
-}
-
-template <int LOGN>
-__device__ __forceinline__ void ntt_inv_regs(double* s, double (&c)[16], const double* __restrict__ itw, ModQ m,
-                                             double ninv) {
-  ntt_inv_regs<LOGN>(s, c, itw, m, &ninv, 1);
 }
 
 // inverse transform handing coefficient j to store(j, v)

@@ -66,7 +66,7 @@ struct SplitNtt {
       e = step(e);
     }
     __syncthreads();
-    ntt_inv_regs<12>(s, c, itw, m, nullptr, S + h);
+    ntt_inv_regs<12, true>(s, c, itw, m, 0.0, S + h);
   }
 
   // the coefficients j + k 4096 from the blocks' values j, y[k 4096 + j]
@@ -99,7 +99,7 @@ struct SplitNtt {
   // forward transform of the block; slot w of the thread in v[w], centred
   __device__ __forceinline__ void forward(double* s, const double (&c)[16], const double* __restrict__ tw, ModQ m,
                                           double (&v)[16]) const {
-    ntt_fwd_regs<12>(s, c, tw, m, S + h);
+    ntt_fwd_regs<12, true>(s, c, tw, m, S + h);
     uint32_t e = e0;
 #pragma unroll
     for (int w = 0; w < 16; ++w) {
