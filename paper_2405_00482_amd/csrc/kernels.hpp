@@ -125,8 +125,9 @@ inline bool few_transforms(int blocks) { return blocks <= 256; }
 // transform of its source limb: while one round of workgroups, one per CU,
 // holds the targets.  Two launches and one, us: ModUp of one ciphertext at
 // 2^12 / 2^13 / 2^14 15 -> 11, 29 -> 20, 54 -> 36, ModDown 17 -> 11, 31 -> 20,
-// 47 -> 38; beyond the line, 300 targets at 2^14 62 -> 70, 372 at 2^13 no gain
-// (one call 104).  With alpha > 1 a target would repeat alpha transforms.
+// 47 -> 38 (since then, without products by one, 10, 17, 31 and 10, 18, 33);
+// beyond the line, 300 targets at 2^14 62 -> 70, 372 at 2^13 no gain.  With
+// alpha > 1 a target would repeat alpha transforms.
 inline bool fuse_transforms(int alpha, int blocks) { return alpha == 1 && few_transforms(blocks); }
 
 // Whether it splits every limb over N / 2^12 workgroups, `blocks` in all
