@@ -29,21 +29,38 @@ namespace pvfl {
 // What bounds it: per (product, diagonal, index) 49 binary64 operations, 40
 // bytes from LDS and, over PG products, 8 plaintext bytes plus 16 BETA / PG
 // key bytes through the vector cache, which takes one wave load per 16
-// cycles.  At PG = 4 the three are near balance, and the chip's clock falls to
-// 1.9 - 2.1 GHz under the load.  Four products of one index share the key
+// cycles whatever its width.  Four products of one index share the key
 // loads; two products of two indices (half the products per key load)
-// measured slower.  64 products at N = 2^14, BETA = 4 (15.9 GB from memory,
-// 2.6 ms at the read rate): 3.83 -> 3.48 ms; 16 products of 512 diagonals at
-// 2^15 (keys from L2, operations 4.7 ms): 8.6 -> 6.9 ms.  Tried: loads one, two
-// and three diagonals ahead of their use (3.5 - 3.8 and 6.7 - 7.6 ms), two
-// indices per thread with 16-byte loads (3.6 - 4.3 and 7.4 - 9.2 ms).
+// measured slower.  A load takes 16 bytes per lane and brings a wave's values
+// of two diagonals (swap_halves), half the vector cache's work for two
+// vector instructions; with 8-byte loads of one diagonal that cache was the
+// busiest unit, 2.5 of 3.5 ms.  64 products at N = 2^14, BETA = 4 (15.6 GB from
+// memory, 2.6 ms at the read rate): 3.83 -> 3.48 (exact sums, four products)
+// -> 3.25 ms; 16 products of 512 diagonals at 2^15 (keys from L2, operations
+// 4.7 ms): 8.6 -> 6.9 -> 6.3 (shared plaintexts) -> 6.2 ms.  Tried on the form
+// of 8-byte loads: loads one, two and three diagonals ahead of their use
+// (3.5 - 3.8 and 6.7 - 7.6 ms), two indices per thread (3.6 - 4.3 and 7.4 - 9.2).
 // ---------------------------------------------------------------------------
 // Row stride of the staged windows (doubles): a compile-time constant for the
 // usual chunk lengths, so that every row of the stage is one LDS address plus
 // an immediate offset.
 template <int CHX>
 __host__ __device__ constexpr int stage_row(int ch) {
-  return 256 + (CHX ? CHX : ch);
+  return (256 + (CHX ? CHX : ch) + 1) & ~1;
+}
+
+typedef double PairOfDoubles __attribute__((ext_vector_type(2), aligned(8)));
+// A wave's 64 values of two rows from one 16-byte load per lane: lanes 0..31
+// loaded the value pairs of the first row, lanes 32..63 those of the second.
+// Swapping the upper half of x with the lower half of y leaves in x the first
+// row and in y the second, value 2 l in lane l < 32 and value 2 (l - 32) + 1 in
+// lane l >= 32.
+__device__ __forceinline__ void swap_halves(PairOfDoubles v, double& r0, double& r1) {
+  const uint64_t x = (uint64_t)__double_as_longlong(v.x), y = (uint64_t)__double_as_longlong(v.y);
+  const auto lo = __builtin_amdgcn_permlane32_swap((uint32_t)x, (uint32_t)y, false, false);
+  const auto hi = __builtin_amdgcn_permlane32_swap((uint32_t)(x >> 32), (uint32_t)(y >> 32), false, false);
+  r0 = __longlong_as_double((long long)((uint64_t)lo[0] | ((uint64_t)hi[0] << 32)));
+  r1 = __longlong_as_double((long long)((uint64_t)lo[1] | ((uint64_t)hi[1] << 32)));
 }
 
 template <int PG, int BETA, int CHX, bool SHARED>
@@ -62,7 +79,10 @@ __global__ __launch_bounds__(256) void k_diag_batch(BatchDiagArgs a) {
   const DiagGroup& G = a.groups[w.grp];
   const int N = a.N, half = N >> 1, K = a.K;
   const int t0 = task.tile * TILE;
-  const unsigned tl = threadIdx.x;
+  const unsigned tid = threadIdx.x;
+  // the thread's index of the tile (swap_halves), and where its value pairs start
+  const bool upper = tid & 32u;
+  const unsigned pair = (tid & ~63u) + 2 * (tid & 31u), tl = pair + (upper ? 1u : 0u);
   const size_t limbN = (size_t)r * N;
   const int pi = a.limb_prime[r];
   const int klimb = a.key_limb[r];
@@ -76,7 +96,10 @@ __global__ __launch_bounds__(256) void k_diag_batch(BatchDiagArgs a) {
   // Stage the digit rows and P c0 (zero on the special limbs) of every
   // product: all of a thread's loads are issued before any is stored, so that
   // a task waits once for its windows and not once per row.
-  for (int x = (int)tl; x < span; x += TILE) {
+  // Even and odd places of a row lie in separate halves: the shifted reads of
+  // the two half-waves are then stride one.
+  const int oddrow = win >> 1;
+  for (int x = (int)tid; x < span; x += TILE) {
     const size_t at = (size_t)((t0 & half) | ((t0 + w.i0 + x) & (half - 1)));
     double v[PG][BETA + 1];
 #pragma unroll
@@ -91,7 +114,7 @@ __global__ __launch_bounds__(256) void k_diag_batch(BatchDiagArgs a) {
 #pragma unroll
     for (int p = 0; p < PG; ++p)
 #pragma unroll
-      for (int j = 0; j <= BETA; ++j) stage[(size_t)(p * (BETA + 1) + j) * win + x] = v[p][j];
+      for (int j = 0; j <= BETA; ++j) stage[(size_t)(p * (BETA + 1) + j) * win + (x & 1) * oddrow + (x >> 1)] = v[p][j];
   }
   __syncthreads();
   int mp[PG];
@@ -126,7 +149,7 @@ __global__ __launch_bounds__(256) void k_diag_batch(BatchDiagArgs a) {
         if (p >= np) continue;
         const double* pcs = stage + (size_t)(p * (BETA + 1) + BETA) * win;
         const double pv = gmem(ptp[p])[tl];
-        acc_mac(pv, pcs[tl], hi0[p], lo0[p]);
+        acc_mac(pv, pcs[(upper ? oddrow : 0) + (pair >> 1)], hi0[p], lo0[p]);
         acc_mac(pv, gmem(a.pc)[(size_t)G.prod[p] * a.pc_stride + Qoff + limbN + t0 + tl], hi1[p], lo1[p]);
       }
     }
@@ -136,54 +159,84 @@ __global__ __launch_bounds__(256) void k_diag_batch(BatchDiagArgs a) {
   // The slots of a chunk of at most 64 diagonals sit in one register across
   // the wave: a scalar load per diagonal would have to be waited for together
   // with the LDS reads.
-  const int lane_slot = CHX && a.slot_of_rot ? a.slot_of_rot[min(w.i0 + (int)(tl & 63u), w.i1 - 1)] : 0;
-  for (; i < w.i1; ++i) {
-    // key limbs (b_j, a_j) of rotation i, whose key sits at this slot of the key set
-    const int slot = CHX ? __builtin_amdgcn_readlane(lane_slot, i - w.i0) : a.slot_of_rot[i];
-    const double* key = a.keys + (size_t)slot * a.key_stride + (size_t)klimb * N + t0;
-    double kb[BETA], ka[BETA], pv[PG];
+  const int lane_slot = CHX && a.slot_of_rot ? a.slot_of_rot[min(w.i0 + (int)(tid & 63u), w.i1 - 1)] : 0;
+  // a row's place idx + o (o = i - i0): even o at `even` + o / 2, odd o at `odd` + (o - 1) / 2
+  const unsigned even = (upper ? oddrow : 0) + (pair >> 1), odd = (upper ? 1 : oddrow) + (pair >> 1);
+  for (; i < w.i1; i += 2) {
+    // Diagonals i and i + 1 (the last one alone: i again, unused).  Key limbs
+    // (b_j, a_j) of both rotations, whose keys sit at these slots of the key set
+    const bool two = i + 1 < w.i1;
+    const int i1 = two ? i + 1 : i;
+    const int slot0 = CHX ? __builtin_amdgcn_readlane(lane_slot, i - w.i0) : a.slot_of_rot[i];
+    const int slot1 = CHX ? __builtin_amdgcn_readlane(lane_slot, i1 - w.i0) : a.slot_of_rot[i1];
+    const double* key = a.keys + (size_t)klimb * N + t0 + pair + (upper ? (size_t)slot1 : (size_t)slot0) * a.key_stride;
+    double kb[2][BETA], ka[2][BETA], pv[2][PG];
+    PairOfDoubles lb[BETA], la[BETA], lp[PG];
 #pragma unroll
     for (int j = 0; j < BETA; ++j) {
-      kb[j] = scalar_base(key + (size_t)(2 * j) * a.key_limbs * N)[tl];
-      ka[j] = scalar_base(key + (size_t)(2 * j + 1) * a.key_limbs * N)[tl];
+      lb[j] = *(const __attribute__((address_space(1))) PairOfDoubles*)(key + (size_t)(2 * j) * a.key_limbs * N);
+      la[j] = *(const __attribute__((address_space(1))) PairOfDoubles*)(key + (size_t)(2 * j + 1) * a.key_limbs * N);
     }
-    // Plaintexts of diagonal i (row 0 for a product without it, so that the
+    // Plaintexts of the diagonals (row 0 for a product without one, so that the
     // loads are unconditional).  They are read once: streamed past L2, so that
     // they do not evict the key tile the other product groups still need.
+    auto row = [&](int p) {
+      const int r0 = i < mp[p] ? i : 0, r1 = i1 < mp[p] ? i1 : r0;
+      return (const __attribute__((address_space(1))) PairOfDoubles*)(
+          scalar_base(ptp[p] + (size_t)r0 * KN) + (pair + (upper ? (unsigned)(r1 - r0) * (unsigned)KN : 0u)));
+    };
     if constexpr (SHARED) {  // one load for the group, from L2 for the groups after the first
-      pv[0] = scalar_base(ptp[0] + (size_t)i * KN)[tl];
-#pragma unroll
-      for (int p = 1; p < PG; ++p) pv[p] = pv[0];
+      lp[0] = *row(0);
     } else {
 #pragma unroll
-      for (int p = 0; p < PG; ++p)
-        pv[p] = __builtin_nontemporal_load(scalar_base(ptp[p] + (size_t)(i < mp[p] ? i : 0) * KN) + tl);
+      for (int p = 0; p < PG; ++p) lp[p] = __builtin_nontemporal_load(row(p));
     }
-    const double* st = stage + (tl + (unsigned)(i - w.i0));
-    auto term = [&](int p) {
+#pragma unroll
+    for (int j = 0; j < BETA; ++j) {
+      swap_halves(lb[j], kb[0][j], kb[1][j]);
+      swap_halves(la[j], ka[0][j], ka[1][j]);
+    }
+#pragma unroll
+    for (int p = 0; p < PG; ++p) {
+      if (!SHARED || p == 0) {
+        swap_halves(lp[p], pv[0][p], pv[1][p]);
+      } else {
+        pv[0][p] = pv[0][0];
+        pv[1][p] = pv[1][0];
+      }
+    }
+    const int o = i - w.i0;
+    const double* st0 = stage + ((o & 1 ? odd : even) + (unsigned)(o >> 1));
+    const double* st1 = stage + ((o & 1 ? even : odd) + (unsigned)((o + 1) >> 1));
+    auto term = [&](int p, int d) {
+      const double* st = d ? st1 : st0;
       const double d0 = st[(p * (BETA + 1)) * win];
       double h0, l0, h1, l1;
-      acc_first(d0, kb[0], cin, h0, l0);
-      acc_first(d0, ka[0], cin, h1, l1);
+      acc_first(d0, kb[d][0], cin, h0, l0);
+      acc_first(d0, ka[d][0], cin, h1, l1);
 #pragma unroll
       for (int j = 1; j < BETA; ++j) {
         const double dj = st[(p * (BETA + 1) + j) * win];
-        acc_mac(dj, kb[j], h0, l0);
-        acc_mac(dj, ka[j], h1, l1);
+        acc_mac(dj, kb[d][j], h0, l0);
+        acc_mac(dj, ka[d][j], h1, l1);
       }
       l0 += st[(p * (BETA + 1) + BETA) * win];
-      acc_mac(pv[p], acc_fold(h0, l0, m), hi0[p], lo0[p]);
-      acc_mac(pv[p], acc_fold(h1, l1, m), hi1[p], lo1[p]);
+      acc_mac(pv[d][p], acc_fold(h0, l0, m), hi0[p], lo0[p]);
+      acc_mac(pv[d][p], acc_fold(h1, l1, m), hi1[p], lo1[p]);
     };
-    if (i < mp_all) {  // every product: one block without branches
+    if (two && i1 < mp_all) {  // both diagonals of every product: one block without branches
 #pragma unroll
-      for (int p = 0; p < PG; ++p) term(p);
+      for (int d = 0; d < 2; ++d)
+#pragma unroll
+        for (int p = 0; p < PG; ++p) term(p, d);
     } else {
 #pragma unroll
-      for (int p = 0; p < PG; ++p)
-        if (i < mp[p]) term(p);
+      for (int p = 0; p < PG; ++p) {
+        if (i < mp[p]) term(p, 0);
+        if (two && i1 < mp[p]) term(p, 1);
+      }
     }
-    if (++cnt >= 8) {  // fold the sums after 8 (9 in the chunk holding diagonal 0) terms
+    if ((cnt += 2) >= 8) {  // fold the sums after 8 (9 in the chunk holding diagonal 0) terms
 #pragma unroll
       for (int p = 0; p < PG; ++p) {
         lo0[p] = reduce(acc_fold(hi0[p], lo0[p], m), m);
