@@ -50,6 +50,7 @@ __host__ __device__ constexpr int stage_row(int ch) {
 }
 
 typedef double PairOfDoubles __attribute__((ext_vector_type(2), aligned(8)));
+typedef const __attribute__((address_space(1))) PairOfDoubles* GlobalPair;
 // A wave's 64 values of two rows from one 16-byte load per lane: lanes 0..31
 // loaded the value pairs of the first row, lanes 32..63 those of the second.
 // Swapping the upper half of x with the lower half of y leaves in x the first
@@ -162,6 +163,8 @@ __global__ __launch_bounds__(256) void k_diag_batch(BatchDiagArgs a) {
   const int lane_slot = CHX && a.slot_of_rot ? a.slot_of_rot[min(w.i0 + (int)(tid & 63u), w.i1 - 1)] : 0;
   // a row's place idx + o (o = i - i0): even o at `even` + o / 2, odd o at `odd` + (o - 1) / 2
   const unsigned even = (upper ? oddrow : 0) + (pair >> 1), odd = (upper ? 1 : oddrow) + (pair >> 1);
+  const double* keyl = a.keys + (size_t)klimb * N + t0;
+  const unsigned pair_next = pair + (upper ? (unsigned)KN : 0u);
   for (; i < w.i1; i += 2) {
     // Diagonals i and i + 1 (the last one alone: i again, unused).  Key limbs
     // (b_j, a_j) of both rotations, whose keys sit at these slots of the key set
@@ -169,21 +172,22 @@ __global__ __launch_bounds__(256) void k_diag_batch(BatchDiagArgs a) {
     const int i1 = two ? i + 1 : i;
     const int slot0 = CHX ? __builtin_amdgcn_readlane(lane_slot, i - w.i0) : a.slot_of_rot[i];
     const int slot1 = CHX ? __builtin_amdgcn_readlane(lane_slot, i1 - w.i0) : a.slot_of_rot[i1];
-    const double* key = a.keys + (size_t)klimb * N + t0 + pair + (upper ? (size_t)slot1 : (size_t)slot0) * a.key_stride;
+    const auto* key0 = scalar_base(keyl + (size_t)slot0 * a.key_stride);
+    const auto* key1 = scalar_base(keyl + (size_t)slot1 * a.key_stride);
+    const auto* key = (upper ? key1 : key0) + pair;
     double kb[2][BETA], ka[2][BETA], pv[2][PG];
     PairOfDoubles lb[BETA], la[BETA], lp[PG];
 #pragma unroll
     for (int j = 0; j < BETA; ++j) {
-      lb[j] = *(const __attribute__((address_space(1))) PairOfDoubles*)(key + (size_t)(2 * j) * a.key_limbs * N);
-      la[j] = *(const __attribute__((address_space(1))) PairOfDoubles*)(key + (size_t)(2 * j + 1) * a.key_limbs * N);
+      lb[j] = *(GlobalPair)(key + (size_t)(2 * j) * a.key_limbs * N);
+      la[j] = *(GlobalPair)(key + (size_t)(2 * j + 1) * a.key_limbs * N);
     }
     // Plaintexts of the diagonals (row 0 for a product without one, so that the
     // loads are unconditional).  They are read once: streamed past L2, so that
     // they do not evict the key tile the other product groups still need.
     auto row = [&](int p) {
-      const int r0 = i < mp[p] ? i : 0, r1 = i1 < mp[p] ? i1 : r0;
-      return (const __attribute__((address_space(1))) PairOfDoubles*)(
-          scalar_base(ptp[p] + (size_t)r0 * KN) + (pair + (upper ? (unsigned)(r1 - r0) * (unsigned)KN : 0u)));
+      const bool next = two && i1 < mp[p];  // else both halves read the one row
+      return (GlobalPair)(scalar_base(ptp[p] + (size_t)(i < mp[p] ? i : 0) * KN) + (next ? pair_next : pair));
     };
     if constexpr (SHARED) {  // one load for the group, from L2 for the groups after the first
       lp[0] = *row(0);
