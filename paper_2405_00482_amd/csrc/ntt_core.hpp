@@ -287,16 +287,6 @@ __device__ __forceinline__ void ntt_fwd_regs(double* s, const double (&c)[16], c
   __syncthreads();
 }
 
-// forward transform of coefficients produced by load(j)
-template <int LOGN, class Load>
-__device__ __forceinline__ void ntt_fwd(double* s, Load load, const double* __restrict__ tw, ModQ m) {
-  constexpr int T = NttShape<LOGN>::T;
-  double c[16];
-#pragma unroll
-  for (int w = 0; w < 16; ++w) c[w] = load((int)opaque_tid() + w * T);
-  ntt_fwd_regs<LOGN>(s, c, tw, m);
-}
-
 // S Gentleman-Sande stages lg1, lg1-1, ..., lg1-S+1 (span doubling each
 // stage); sets {base + u * 2^ls}, 2^ls = span of the first stage.  The set is
 // one group of stage lg1-S+1; at stage lg1-st it spans 2^(S-1-st) groups with
@@ -420,17 +410,6 @@ __device__ __forceinline__ void ntt_inv_regs(double* s, double (&c)[16], const d
     for (int u = 0; u < 16; ++u) c[u] = x[u];
   }
 }
-
-// inverse transform handing coefficient j to store(j, v)
-template <int LOGN, class Store>
-__device__ __forceinline__ void ntt_inv(double* s, Store store, const double* __restrict__ itw, ModQ m, double ninv) {
-  constexpr int T = NttShape<LOGN>::T;
-  double c[16];
-  ntt_inv_regs<LOGN>(s, c, itw, m, ninv);
-#pragma unroll
-  for (int w = 0; w < 16; ++w) store((int)opaque_tid() + w * T, c[w]);
-}
-
 
 // Orbit order <-> bit-reversed index, computed instead of read from a table.
 // Slot t < N/2 holds the exponent e = 5^t mod 2N, at bit-reversed index
