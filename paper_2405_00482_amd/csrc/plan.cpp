@@ -417,8 +417,10 @@ static pvfl_status run_diag_lazy(const pvfl_plan* p, int count, const double* co
     }
     return PVFL_OK;
   }
-  // the first row block's output is written before the next block reads the inputs
-  for (int x = 0; RB > 1 && !bs && x < CB; ++x)
+  // a row block's output is written before the next block reads the inputs; giant
+  // steps write it after every input, before the next input is read
+  const bool read_again = RB > 1 || (bs && CB > 1);
+  for (int x = 0; read_again && x < CB; ++x)
     if (ct_of(x) < out + (size_t)RB * 2 * Q && out < ct_of(x) + 2 * Q) copied = true;
   for (int x = 0; copied && x < CB; ++x)
     HIP_TRY(hipMemcpyAsync(copies + (size_t)x * 2 * Q, cts[x / CB1] + (size_t)(x % CB1) * 2 * Q, 2 * Q * sizeof(double),
