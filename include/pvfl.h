@@ -320,6 +320,9 @@ pvfl_status pvfl_ct_add(pvfl_ctx* ctx, int32_t level, const void* a_dev, const v
  * aligned, at least pvfl_batch_workspace_bytes bytes for the same plans and
  * options): the batch keeps its launch tables and every intermediate there
  * and allocates no device memory.  The buffers must outlive the batch.
+ * Products may share plaintexts (one pt_dev for several, or one's inside
+ * another's at a whole number of plaintexts): pvfl_batch_encode makes each
+ * plaintext once, for the last product that names it.
  * opts (NULL = defaults {2, 32, 1, 1}): see pvfl_batch_opts.
  * pvfl_batch_encrypt: product k uses seed + k.
  * pvfl_batch_run: encode, encrypt, matmul, decrypt in order; with use_graph

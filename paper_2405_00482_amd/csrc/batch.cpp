@@ -6,6 +6,7 @@
 #include <cstring>
 #include <memory>
 #include <numeric>
+#include <unordered_map>
 #include <vector>
 
 #include "batch.hpp"
@@ -227,6 +228,22 @@ int total_pts(int count, const pvfl_plan* const* plans) {
   return n;
 }
 
+// The plaintexts to encode, (product, plaintext) in product order.  One that
+// several products name is made once, for the last of them, as if the products
+// were encoded one after the other: at N = 2^15 the encoder parks a plaintext's
+// coefficients in the plaintext itself (encode_limbs), so two workgroups at one
+// plaintext would overwrite each other's.
+std::vector<int2> encode_work(const std::vector<BatchProd>& prods, const std::vector<int>& n_pts, size_t pt_doubles) {
+  std::unordered_map<const double*, int> last;
+  for (size_t k = 0; k < prods.size(); ++k)
+    for (int j = 0; j < n_pts[k]; ++j) last[prods[k].pt + j * pt_doubles] = (int)k;
+  std::vector<int2> work;
+  for (size_t k = 0; k < prods.size(); ++k)
+    for (int j = 0; j < n_pts[k]; ++j)
+      if (last[prods[k].pt + j * pt_doubles] == (int)k) work.push_back(make_int2((int)k, j));
+  return work;
+}
+
 std::vector<int> mprimes_of(int count, const pvfl_plan* const* plans) {
   std::vector<int> mp(count);
   for (int k = 0; k < count; ++k) mp[k] = plans[k]->info.mprime;
@@ -275,7 +292,7 @@ extern "C" pvfl_status pvfl_batch_create(pvfl_ctx* c, int32_t count, const pvfl_
   const int N = c->N;
   std::vector<BatchProd> prods(count);
   std::vector<EncodeArgs> apt(count), act(count);
-  std::vector<int2> encw;
+  std::vector<int> n_pts(count);
   std::vector<const double*> ct_tab(count);
   std::vector<double*> ct_out_tab(count), out_tab(count);
   for (int k = 0; k < count; ++k) {
@@ -301,7 +318,7 @@ extern "C" pvfl_status pvfl_batch_create(pvfl_ctx* c, int32_t count, const pvfl_
     apt[k].scale = p->pt_scale;
     act[k] = geometry_of(p, v_dev ? v_dev[k] : nullptr, p->info.n);
     act[k].scale = std::pow(2.0, c->log2_scale);
-    for (int j = 0; j < p->info.n_pts; ++j) encw.push_back(make_int2(k, j));
+    n_pts[k] = p->info.n_pts;
     ct_tab[k] = B.ct;
     ct_out_tab[k] = B.ct_out;
     out_tab[k] = B.out;
@@ -323,8 +340,9 @@ extern "C" pvfl_status pvfl_batch_create(pvfl_ctx* c, int32_t count, const pvfl_
   b->n_tasks = (int)S.tasks.size();
   b->n_slots = S.n_slots;
   b->n_work = (int)S.work.size();
+  const std::vector<int2> encw = encode_work(prods, n_pts, (size_t)b->K * N);
   b->n_enc_work = (int)encw.size();
-  const Layout L = make_layout(c, count, b->n_enc_work, S, b->lv, b->K, b->beta);
+  const Layout L = make_layout(c, count, total_pts(count, plans), S, b->lv, b->K, b->beta);
   if (!ws_dev) return fail(PVFL_E_INVALID, "the batch needs a workspace of pvfl_batch_workspace_bytes bytes");
   if (ws_bytes < L.total)
     return fail(PVFL_E_SHAPE, "workspace of " + std::to_string(ws_bytes) + " bytes, the batch needs " +
@@ -374,7 +392,7 @@ extern "C" pvfl_status pvfl_batch_encode(pvfl_batch* b, void* stream) {
   CrtTabs crt;
   pvfl_status st = enc_tables_for(c, &et, &crt);
   if (st != PVFL_OK) return st;
-  KernelTimer kt(c, stream, PVFL_TIMING_ENCODE, b->pt_bytes);
+  KernelTimer kt(c, stream, PVFL_TIMING_ENCODE, 8.0 * (double)b->n_enc_work * b->K * c->N);
   HIP_TRY(launch_encode_pt_batch(launch_ctx(c, stream), b->args_pt, b->enc_work, b->n_enc_work, b->prods, et,
                                  qp_map(c, b->lv, true)));
   kt.stop();
