@@ -573,6 +573,17 @@ size_t rot_scratch_doubles(const pvfl_ctx* c, int lv) {
 bool rot_inner_apart(int lv, int n) { return n * 2 * (lv + 1) <= 256; }
 size_t rot_inner_doubles(const pvfl_ctx* c, int lv) { return 2 * (size_t)c->ks_host[lv].K * c->N; }
 
+// The context's scratch as a single rotation at level lv leaves it: room for the
+// rotation with its key products apart, for two ciphertexts (an input rotated in
+// place) and for two more.  Every call that rotates goes through here, also the
+// ones that then use ctx_rot_scratch, so that after any of them a rotation or a
+// decoding of that size can be captured, and none that fits replaces memory that
+// a captured graph names.
+pvfl_status rotation_scratch(pvfl_ctx* c, int lv, double** out, size_t* n) {
+  *n = rot_scratch_doubles(c, lv) + rot_inner_doubles(c, lv);
+  return ctx_scratch(c, (*n + 4 * (size_t)(lv + 1) * c->N) * sizeof(double), out);
+}
+
 pvfl_status run_rotations(pvfl_ctx* c, const pvfl_rotkeys* keys, int lv, const RotJob* jobs, int n, bool pre, bool add,
                           double* scratch, size_t scratch_n, int at_once, const double* shared_digits, void* stream) {
   const KsLevel& kl = c->ks_host[lv];
@@ -620,9 +631,10 @@ extern "C" pvfl_status pvfl_rotate(pvfl_ctx* c, const pvfl_rotkeys* keys, int32_
   if (galois >= (uint32_t)(2 * N) || c->log5[galois] < 0) return fail(PVFL_E_INVALID, "Galois element not in <5>");
   const int rot = c->log5[galois];
   if (keys->slot_of_rot[rot] < 0) return fail(PVFL_E_NOKEY, "missing rotation key");
-  const size_t Q = (size_t)(level + 1) * N, per = rot_scratch_doubles(c, level) + rot_inner_doubles(c, level);
+  const size_t Q = (size_t)(level + 1) * N;
   double* ws;
-  pvfl_status st = ctx_scratch(c, (per + 2 * Q) * sizeof(double), &ws);
+  size_t per;
+  pvfl_status st = rotation_scratch(c, level, &ws, &per);
   if (st != PVFL_OK) return st;
   const double* ct = (const double*)ct_v;
   double* out = (double*)out_v;

@@ -132,6 +132,8 @@ pvfl_status ctx_rot_scratch(pvfl_ctx* c, size_t per, int want, void* stream, dou
 // doubles of scratch one rotation at level lv needs
 size_t rot_scratch_doubles(const pvfl_ctx* c, int lv);
 size_t rot_inner_doubles(const pvfl_ctx* c, int lv);
+// the context's scratch for one rotation: *n doubles, then two ciphertexts' room and more
+pvfl_status rotation_scratch(pvfl_ctx* c, int lv, double** out, size_t* n);
 bool rot_inner_apart(int lv, int n);
 struct RotJob {
   const double* ct;  // [2][lv+1][N]

@@ -546,8 +546,8 @@ static pvfl_status run_ras_in_ct(const pvfl_plan* p, const pvfl_rotkeys* keys, d
   pvfl_ctx* c = p->ctx;
   const size_t Q = (size_t)(p->lv + 1) * c->N;
   double* ws;
-  const size_t per = rot_scratch_doubles(c, p->lv) + rot_inner_doubles(c, p->lv);
-  pvfl_status st = ctx_scratch(c, per * sizeof(double), &ws);
+  size_t per;
+  pvfl_status st = rotation_scratch(c, p->lv, &ws, &per);
   if (st != PVFL_OK) return st;
   double* src = ct;
   double* dst = tmp;
@@ -572,17 +572,20 @@ static pvfl_status run_row(const pvfl_plan* p, const double* ct, const double* p
   const size_t Q2 = (size_t)(lv + 1) * N, Q1 = (size_t)lv * N, Q0 = (size_t)(lv - 1) * N;
   // one row: t1 and its rotate-and-sum partner at lv - 1; the indicator's
   // product t0 and its placement at lv - 2; the rotations' scratch
-  const size_t bufs = 4 * Q1 + 4 * Q0, rot = rot_scratch_doubles(c, lv - 1) +
-                                           (rot_inner_apart(lv - 1, std::min(m, kRotsPerLaunch)) ? rot_inner_doubles(c, lv - 1) : 0);
-  double* base;
+  const int rl = p->ras_rots.empty() ? lv - 2 : lv - 1;  // the highest level that rotates
+  const size_t bufs = 4 * Q1 + 4 * Q0, rot = rot_scratch_doubles(c, rl) +
+                                           (rot_inner_apart(rl, std::min(m, kRotsPerLaunch)) ? rot_inner_doubles(c, rl) : 0);
+  double *base, *single = nullptr;
   int rows;
-  pvfl_status st = ctx_rot_scratch(c, bufs + rot, std::min(m, kRotsPerLaunch), stream, &base, &rows);
+  size_t single_n;  // rot at least
+  pvfl_status st = p->galois.empty() ? PVFL_OK : rotation_scratch(c, rl, &single, &single_n);
   if (st != PVFL_OK) return st;
-  double* scratch = base ? base + (size_t)rows * bufs : nullptr;
+  if ((st = ctx_rot_scratch(c, bufs + rot, std::min(m, kRotsPerLaunch), stream, &base, &rows)) != PVFL_OK) return st;
+  double* scratch = base + (size_t)rows * bufs;
   if (rows == 0) {  // one row at a time: its buffers fit the caller's workspace
     rows = 1;
     base = ws;
-    if ((st = ctx_scratch(c, rot * sizeof(double), &scratch)) != PVFL_OK) return st;
+    scratch = single;
   }
   double* ta = base;                            // [rows][2][lv][N]
   double* tb = ta + (size_t)rows * 2 * Q1;      // [rows][2][lv][N]
@@ -810,14 +813,16 @@ extern "C" pvfl_status pvfl_ctmat_transpose(const pvfl_plan* p, const void* ct_i
   }
   if (jobs.empty()) return PVFL_OK;
   if (!keys) return fail(PVFL_E_NOKEY, "the conversion needs rotation keys");
-  double* scratch;
+  double *scratch, *single;
   int at_once;
+  size_t single_n;  // per at least
+  if ((st = rotation_scratch(c, p->lv, &single, &single_n)) != PVFL_OK) return st;
   const bool apart = rot_inner_apart(p->lv, std::min((int)jobs.size(), kRotsPerLaunch));
   const size_t per = rot_scratch_doubles(c, p->lv) + (apart ? rot_inner_doubles(c, p->lv) : 0);
   if ((st = ctx_rot_scratch(c, per, (int)jobs.size(), stream, &scratch, &at_once)) != PVFL_OK) return st;
   if (at_once == 0) {
     at_once = 1;
-    if ((st = ctx_scratch(c, per * sizeof(double), &scratch)) != PVFL_OK) return st;
+    scratch = single;
   }
   return run_rotations(c, keys, p->lv, jobs.data(), (int)jobs.size(), true, false, scratch, at_once * per, at_once,
                        nullptr, stream);
