@@ -542,7 +542,12 @@ pvfl_status ctx_rot_scratch(pvfl_ctx* c, size_t per, int want, void* stream, dou
     void* p = nullptr;
     size_t size = (size_t(16) << 20) / sizeof(double);
     while (size < target * per) size *= 2;
-    if (free_stream && hipMalloc(&p, size * sizeof(double)) == hipSuccess) {
+    // relaxed: the allocation is no part of what another stream may be capturing, and must not end that capture
+    hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
+    if (free_stream) (void)hipThreadExchangeStreamCaptureMode(&mode);
+    const bool got = free_stream && hipMalloc(&p, size * sizeof(double)) == hipSuccess;
+    if (free_stream) (void)hipThreadExchangeStreamCaptureMode(&mode);
+    if (got) {
       c->dev_allocs.push_back(p);
       c->rot_scratch = (double*)p;
       c->rot_scratch_n = size;
