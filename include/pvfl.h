@@ -171,6 +171,9 @@ size_t pvfl_bytes_pt(const pvfl_plan* plan);       /* all diagonal plaintexts */
  * ciphertexts (per-rotation ModDown, giant steps) also take less, down to one
  * rotation at a time: anything smaller is PVFL_E_SHAPE. */
 size_t pvfl_bytes_workspace(const pvfl_plan* plan);
+/* The smallest workspace a product takes (count = 1) or a sum of count products
+ * (pvfl_matmul_ct_pt_sum); 0 for plans that need none. */
+size_t pvfl_bytes_workspace_min(const pvfl_plan* plan, int32_t count);
 
 /* The hot path.
  * pvfl_matmul_ct_pt: out = the plan's product of the input ciphertexts and
@@ -197,7 +200,7 @@ pvfl_status pvfl_matmul_ct_pt(const pvfl_plan* plan, const void* ct_dev, const v
  * Plans: HYBRID, DIAG with lazy rotate-and-sum, CTMAT and COL.  Errors as
  * pvfl_matmul_ct_pt, plus PVFL_E_PLAN for ROW and in-ciphertext
  * rotate-and-sum plans and PVFL_E_SHAPE when the plan's smallest workspace
- * exceeds the array, before anything is enqueued. */
+ * (pvfl_bytes_workspace_min) exceeds the array, before anything is enqueued. */
 pvfl_status pvfl_matmul_ct_pt_noalloc(const pvfl_plan* plan, const void* ct_dev, const void* pt_dev,
                                       const pvfl_rotkeys* keys, void* out_dev, void* stream);
 size_t pvfl_noalloc_max_bytes(void);

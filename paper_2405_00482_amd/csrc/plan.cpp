@@ -344,6 +344,9 @@ extern "C" size_t pvfl_bytes_workspace(const pvfl_plan* p) { return p ? sizeof(d
 extern "C" size_t pvfl_bytes_workspace_sum(const pvfl_plan* p, int32_t count) {
   return p && count >= 1 ? sizeof(double) * ws_preferred(p, count) : 0;
 }
+extern "C" size_t pvfl_bytes_workspace_min(const pvfl_plan* p, int32_t count) {
+  return p && count >= 1 ? sizeof(double) * ws_doubles(p, count) : 0;
+}
 
 // the caller's workspace (plans with no workspace -- CTMAT, COL -- take NULL)
 static pvfl_status get_ws(const pvfl_plan* p, void* ws, size_t ws_bytes, double** out, int count = 1) {

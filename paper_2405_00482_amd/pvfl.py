@@ -160,6 +160,8 @@ def lib():
         L.pvfl_bytes_rotkeys.restype = sz
         L.pvfl_bytes_workspace_sum.argtypes = [_VP, i32]
         L.pvfl_bytes_workspace_sum.restype = sz
+        L.pvfl_bytes_workspace_min.argtypes = [_VP, i32]
+        L.pvfl_bytes_workspace_min.restype = sz
         L.pvfl_mlp_num_params.argtypes = [_VP]
         L.pvfl_mlp_num_params.restype = i32
         L.pvfl_plan_num_features.argtypes = []
@@ -465,13 +467,17 @@ class Plan(_Handle):
         o = _dev(out, "output", self.bytes("ct_out"))
         if ws is None:
             ws = self.workspace(n)
-        w = _dev(ws, "workspace", self.workspace_sum_bytes(n), str(ws.dtype)[6:]) if ws is not None else _ptr(None)
+        w = _dev(ws, "workspace", self.workspace_min_bytes(n), str(ws.dtype)[6:]) if ws is not None else _ptr(None)
         ws_bytes = 0 if ws is None else ws.numel() * ws.element_size()
         _check(lib().pvfl_matmul_ct_pt_sum(self.h, n, ca, pa, keys.h if keys is not None else None, o, w, ws_bytes,
                                            _stream()))
 
     def workspace_sum_bytes(self, count: int) -> int:
         return int(lib().pvfl_bytes_workspace_sum(self.h, count))
+
+    def workspace_min_bytes(self, count: int = 1) -> int:
+        """the smallest workspace a product (of count terms) takes; bytes("workspace") is the one it runs fastest with"""
+        return int(lib().pvfl_bytes_workspace_min(self.h, count))
 
     def _slots_bytes(self) -> int:
         return 8 * self.info["ct_out"] * (self.ctx.N // 2)
@@ -547,7 +553,7 @@ class Plan(_Handle):
         o = _dev(out, "output", self.bytes("ct_out"))
         if ws is None:
             ws = self.workspace()
-        w = _dev(ws, "workspace", self.bytes("workspace"), str(ws.dtype)[6:]) if ws is not None else _ptr(None)
+        w = _dev(ws, "workspace", self.workspace_min_bytes(), str(ws.dtype)[6:]) if ws is not None else _ptr(None)
         ws_bytes = 0 if ws is None else ws.numel() * ws.element_size()
         _check(lib().pvfl_matmul_ct_pt(self.h, c, p, keys.h if keys is not None else None, o, w, ws_bytes, _stream()))
 
