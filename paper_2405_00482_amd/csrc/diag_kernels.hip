@@ -199,18 +199,20 @@ __global__ __launch_bounds__(512) void k_diag_bsgs(DiagArgs a, int bs, int g) {
 
 // Alg. 3 ciphertext-matrix product (and the column-order one): out_k = sum_i
 // ct_i pt_{i,k}, i < nct, k < nout.  A workgroup holds the sums of OUTS outputs
-// at 64 indices of one limb and its waves share the ciphertexts, so that a
+// at 64 indices of one limb and its NW waves share the ciphertexts, so that a
 // ciphertext is read once per OUTS outputs; sums are exact (fp64_mod.hpp):
 // eight products of residues below q stay below 8 B^2 < 0.43 * 2^(2b + 5).
 // Bound by memory, each plaintext limb read once.  64 ciphertexts, 8 outputs,
 // 6 limbs at N = 2^14 (0.50 GB, 83 us at the read rate): one output per thread
-// 126 us, this 82.
-template <int OUTS>
-__global__ __launch_bounds__(512) void k_ctmat(const double* __restrict__ ct, const double* __restrict__ pt, int nct,
-                                               int nout, int lv, int N, const ModQ* __restrict__ mods,
-                                               double* __restrict__ out) {
-  __shared__ double red[2 * OUTS][8][64];
-  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6, nw = blockDim.x >> 6;
+// 128 us, this 83.  Both counts are compile-time constants: the registers and
+// the LDS are those of the waves there are (two waves with the LDS of eight
+// took 2 ciphertexts, 9 outputs, 8 limbs at N = 2^15 from 14 to 50 us).
+// STREAM: plaintext loads bypass the caches.
+template <int OUTS, int NW, bool STREAM>
+__global__ __launch_bounds__(64 * NW) void k_ctmat(const double* __restrict__ ct, const double* __restrict__ pt, int nct,
+                                                   int nout, int lv, int N, const ModQ* __restrict__ mods,
+                                                   double* __restrict__ out) {
+  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
   const int r = blockIdx.y, k0 = blockIdx.z * OUTS, nk = min(OUTS, nout - k0);
   const ModQ m = mods[r];
   const size_t Q = (size_t)(lv + 1) * N, off = (size_t)r * N + blockIdx.x * 64 + lane;
@@ -222,14 +224,17 @@ __global__ __launch_bounds__(512) void k_ctmat(const double* __restrict__ ct, co
     lo0[u] = lo1[u] = 0.0;
   }
   int cnt = 0;
-  for (int i = w; i < nct; i += nw) {
+  for (int i = w; i < nct; i += NW) {
     const auto* pi = gmem(pt) + ((size_t)i * nout + k0) * Q + off;
     const auto* ci = gmem(ct) + (size_t)i * 2 * Q + off;
     double p[OUTS];
 #pragma unroll
-    for (int u = 0; u < OUTS; ++u)  // past the last output: the first one's again, never stored
-      p[u] = __builtin_nontemporal_load(pi + (size_t)(u < nk ? u : 0) * Q);
+    for (int u = 0; u < OUTS; ++u) {  // past the last output: the first one's again, never stored
+      const auto* pu = pi + (size_t)(u < nk ? u : 0) * Q;
+      p[u] = STREAM ? __builtin_nontemporal_load(pu) : *pu;
+    }
     const double x0 = ci[0], x1 = ci[Q];
+    __builtin_amdgcn_sched_barrier(0);  // every load issued before the first is waited for
 #pragma unroll
     for (int u = 0; u < OUTS; ++u) {
       acc_mac(x0, p[u], hi0[u], lo0[u]);
@@ -245,17 +250,40 @@ __global__ __launch_bounds__(512) void k_ctmat(const double* __restrict__ ct, co
       cnt = 0;
     }
   }
+  if constexpr (NW == 1) {
 #pragma unroll
-  for (int u = 0; u < OUTS; ++u) {
-    red[2 * u][w][lane] = reduce(acc_fold(hi0[u], lo0[u], m), m);
-    red[2 * u + 1][w][lane] = reduce(acc_fold(hi1[u], lo1[u], m), m);
+    for (int u = 0; u < OUTS; ++u) {
+      if (u >= nk) break;
+      out[(size_t)(2 * (k0 + u)) * Q + off] = reduce(acc_fold(hi0[u], lo0[u], m), m);
+      out[(size_t)(2 * (k0 + u) + 1) * Q + off] = reduce(acc_fold(hi1[u], lo1[u], m), m);
+    }
+  } else {
+    __shared__ double red[2 * OUTS][NW][64];
+#pragma unroll
+    for (int u = 0; u < OUTS; ++u) {
+      red[2 * u][w][lane] = reduce(acc_fold(hi0[u], lo0[u], m), m);
+      red[2 * u + 1][w][lane] = reduce(acc_fold(hi1[u], lo1[u], m), m);
+    }
+    __syncthreads();
+    for (int h = w; h < 2 * nk; h += NW) {
+      double v = 0.0;
+#pragma unroll
+      for (int k = 0; k < NW; ++k) v += red[h][k][lane];
+      out[(size_t)(2 * k0 + h) * Q + off] = reduce(v, m);
+    }
   }
-  __syncthreads();
-  for (int h = w; h < 2 * nk; h += nw) {
-    double v = 0.0;
-    for (int k = 0; k < nw; ++k) v += red[h][k][lane];
-    out[(size_t)(2 * k0 + h) * Q + off] = reduce(v, m);
-  }
+}
+
+// One ciphertext: out_k = ct pt_k, thread = (index t, limb r, output k).  There
+// is no sum, so nothing to share and no exact sum's offset to make.
+__global__ __launch_bounds__(256) void k_ctmat_one(const double* __restrict__ ct, const double* __restrict__ pt, int lv,
+                                                   int N, const ModQ* __restrict__ mods, double* __restrict__ out) {
+  const int r = blockIdx.y, k = blockIdx.z;
+  const ModQ m = mods[r];
+  const size_t Q = (size_t)(lv + 1) * N, off = (size_t)r * N + blockIdx.x * 256 + threadIdx.x;
+  const double p = pt[(size_t)k * Q + off];
+  out[(size_t)k * 2 * Q + off] = reduce(mulmod(ct[off], p, m), m);
+  out[(size_t)k * 2 * Q + Q + off] = reduce(mulmod(ct[Q + off], p, m), m);
 }
 
 // ---------------------------------------------------------------------------
@@ -287,15 +315,56 @@ hipError_t launch_diag_bsgs(const LaunchCtx& L, const DiagArgs& a, int bs, int g
   return hipGetLastError();
 }
 
+template <int OUTS, bool STREAM>
+static void ctmat_run(const LaunchCtx& L, const double* ct, const double* pt, int nct, int nout, int lv, int N, int nw,
+                      double* out) {
+  const dim3 grid(N / 64, lv + 1, (nout + OUTS - 1) / OUTS), block(64 * nw);
+  auto* k = nw == 1 ? k_ctmat<OUTS, 1, STREAM> : nw == 2 ? k_ctmat<OUTS, 2, STREAM>
+          : nw == 4 ? k_ctmat<OUTS, 4, STREAM> : k_ctmat<OUTS, 8, STREAM>;
+  hipLaunchKernelGGL(k, grid, block, 0, L.stream, ct, pt, nct, nout, lv, N, L.tb.mods, out);
+}
+template <int OUTS>
+static void ctmat_outs(const LaunchCtx& L, const double* ct, const double* pt, int nct, int nout, int lv, int N, int nw,
+                       bool stream, double* out) {
+  if (stream)
+    ctmat_run<OUTS, true>(L, ct, pt, nct, nout, lv, N, nw, out);
+  else
+    ctmat_run<OUTS, false>(L, ct, pt, nct, nout, lv, N, nw, out);
+}
+
+// The outputs fall into as few equal parts of at most eight as they can: 9 of
+// 64 ciphertexts with 6 limbs at 2^14 take 85 us as 5 + 4, 128 as 8 + 1.  Waves
+// share the ciphertexts until the chip has 2048 of them, eight on a CU, and only
+// while each still has four: 256 ciphertexts, one output, 2 limbs at 2^12 take
+// 113 us with one wave per workgroup, 19 with eight; beyond the line 16
+// ciphertexts, one output, 8 limbs at 2^15 take 16.7 with one, 21 with eight.  One
+// ciphertext takes the kernel that shares nothing (9 outputs, 8 limbs at 2^15: 10.8
+// against 13.0 us).  Large plaintexts are streamed past the caches: beyond 64
+// MiB where many ciphertexts keep the loads at the memory's rate (the 403 MB of 64 x 8
+// with 6 limbs at 2^14: 83 us against 94; 101 MB of 64 x 2 just encoded: a transposed
+// product 465 against 468); with few, products from the same plaintexts find them in
+// the 256 MB last-level cache (107 MB of 3 x 17 with 8 limbs at 2^15: 32 us against 36).
 hipError_t launch_ctmat(const LaunchCtx& L, const double* ct, const double* pt, int nct, int nout, int lv, int N,
                         double* out) {
-  const int outs = nout >= 5 ? 8 : nout >= 3 ? 4 : nout;
-  const dim3 grid(N / 64, lv + 1, (nout + outs - 1) / outs), block(64 * waves_for(nct, 8));
+  if (nct == 1) {
+    hipLaunchKernelGGL(k_ctmat_one, dim3(N / 256, lv + 1, nout), dim3(256), 0, L.stream, ct, pt, lv, N, L.tb.mods, out);
+    return hipGetLastError();
+  }
+  const int parts = (nout + 7) / 8, outs = (nout + parts - 1) / parts;
+  const long waves = (long)(N / 64) * (lv + 1) * ((nout + outs - 1) / outs);
+  const size_t mib = (sizeof(double) * (size_t)nct * nout * (lv + 1) * N) >> 20;
+  const bool stream = mib >= (nct >= 16 ? 64 : 200);
+  int nw = 1;
+  while (nw < 8 && waves * nw < 2048 && nct >= 8 * nw) nw *= 2;
   switch (outs) {
-    case 1: hipLaunchKernelGGL(k_ctmat<1>, grid, block, 0, L.stream, ct, pt, nct, nout, lv, N, L.tb.mods, out); break;
-    case 2: hipLaunchKernelGGL(k_ctmat<2>, grid, block, 0, L.stream, ct, pt, nct, nout, lv, N, L.tb.mods, out); break;
-    case 4: hipLaunchKernelGGL(k_ctmat<4>, grid, block, 0, L.stream, ct, pt, nct, nout, lv, N, L.tb.mods, out); break;
-    default: hipLaunchKernelGGL(k_ctmat<8>, grid, block, 0, L.stream, ct, pt, nct, nout, lv, N, L.tb.mods, out); break;
+    case 1: ctmat_outs<1>(L, ct, pt, nct, nout, lv, N, nw, stream, out); break;
+    case 2: ctmat_outs<2>(L, ct, pt, nct, nout, lv, N, nw, stream, out); break;
+    case 3: ctmat_outs<3>(L, ct, pt, nct, nout, lv, N, nw, stream, out); break;
+    case 4: ctmat_outs<4>(L, ct, pt, nct, nout, lv, N, nw, stream, out); break;
+    case 5: ctmat_outs<5>(L, ct, pt, nct, nout, lv, N, nw, stream, out); break;
+    case 6: ctmat_outs<6>(L, ct, pt, nct, nout, lv, N, nw, stream, out); break;
+    case 7: ctmat_outs<7>(L, ct, pt, nct, nout, lv, N, nw, stream, out); break;
+    default: ctmat_outs<8>(L, ct, pt, nct, nout, lv, N, nw, stream, out); break;
   }
   return hipGetLastError();
 }
