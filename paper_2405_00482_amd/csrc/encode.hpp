@@ -38,16 +38,21 @@ struct OutFactors {
 
 // Workgroups that share one plaintext's nl limbs, each repeating its FFT (worth
 // 1.5 limbs' transforms): the number for which `count` plaintexts take the
-// least time on 256 CUs holding 4, 2 or 1 workgroups at N = 2^12, 2^13, 2^14+.
-// With more than a few rounds of workgroups it is one.  64 plaintexts of 4
-// limbs at 2^13: 38 -> 23 us; 128 of 6 limbs at 2^14: 87 -> 62 us; one
-// cleartext of 3 limbs at 2^13: 29 -> 16 us.
+// least time when the busiest of 256 CUs has w workgroups.  Each beyond its
+// first adds to the CU's time 0.4 of a workgroup alone at N = 2^12, 0.7 at 2^13
+// (they run side by side but share its vector units) and a whole one from 2^14
+// (256, 512, 1024 plaintexts of one workgroup each: 13.8, 19.1, 28.7 us with 2
+// limbs at 2^12; 27.6, 42.7, 80.0 with 3 at 2^13; 60, 114, 223 with 4 at 2^14).
+// With more than a few workgroups to a CU it is one.  64 plaintexts of 3 limbs at 2^13:
+// 26 us with one workgroup each, 16 with three; 256 of them: 28 with one, 32 with
+// two; 128 of 4 limbs at 2^14: 53 with one, 40 with two.
 inline int encode_parts(int logN, int count, int nl) {
-  const long slots = 256L * (logN <= 12 ? 4 : logN == 13 ? 2 : 1);
+  const double beside = logN <= 12 ? 0.4 : logN == 13 ? 0.7 : 1.0;
   int best = 1;
   double least = 0.0;
   for (int p = 1; p <= nl; ++p) {
-    const double t = (double)(((long)count * p + slots - 1) / slots) * (1.5 + (nl + p - 1) / p);
+    const long w = ((long)count * p + 255) / 256;
+    const double t = (1.5 + (nl + p - 1) / p) * (1.0 + beside * (w - 1));
     if (p == 1 || t < least) {
       best = p;
       least = t;
