@@ -178,11 +178,8 @@ __device__ __forceinline__ double crt_lift(const double* __restrict__ base, int 
   return crt_lift<NL>(r, ct, nl_rt);
 }
 
-// f(std::integral_constant<int, NL>) for the limb count nl: up to eight by number,
-// 0 (loops unrolled to kMaxLimbs under uniform conditions) beyond.  One and 512
-// ciphertexts at N = 2^15, by number and through the general form: 1 limb 88 and 166 us,
-// 292 and 429; 8 limbs 179 and 238, 1335 and 1409; at 2^13, 3 limbs, 27 and 66, 114 and
-// 185.  The gap narrows with the count, and each number is one more copy of the loop.
+// f(std::integral_constant<int, NL>) for the limb count nl: the usual output
+// levels by number, 0 for the others
 template <class F>
 __device__ __forceinline__ void with_limbs(int nl, F f) {
   switch (nl) {
@@ -192,7 +189,6 @@ __device__ __forceinline__ void with_limbs(int nl, F f) {
     case 4: f(std::integral_constant<int, 4>()); break;
     case 5: f(std::integral_constant<int, 5>()); break;
     case 6: f(std::integral_constant<int, 6>()); break;
-    case 7: f(std::integral_constant<int, 7>()); break;
     case 8: f(std::integral_constant<int, 8>()); break;
     default: f(std::integral_constant<int, 0>()); break;
   }
