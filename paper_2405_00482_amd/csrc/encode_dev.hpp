@@ -208,8 +208,9 @@ __device__ __forceinline__ void decode_to_lds(const double* __restrict__ base, i
     constexpr int NL = decltype(nl_c)::value;
     // the residues of U of the thread's 8 points (at most 32 values) in flight
     // together: one ciphertext's decode with read-out at 2^12 11.0 -> 10.2 us,
-    // at 2^13 15.8 -> 14.8
-    constexpr int U = NL == 0 ? 1 : NL <= 2 ? 8 : NL <= 4 ? 4 : 2;
+    // at 2^13 15.8 -> 14.8.  At 2^14 at most 16 values: of 2 limbs, 512 ciphertexts take
+    // 65 us with them and 77 with 32, one takes 20 either way
+    constexpr int U = NL == 0 ? 1 : NL <= 2 && LOGN < 14 ? 8 : NL <= 4 ? 4 : 2;
 #pragma unroll 1
     for (int k0 = opaque_tid(); k0 < M; k0 += U * T) {
       CrtResidues<NL> re[U], im[U];

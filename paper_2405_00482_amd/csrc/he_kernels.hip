@@ -302,6 +302,15 @@ NTT_KERNEL(LOGN) void k_encrypt_pk(const int64_t* __restrict__ msg, const double
   }
 }
 
+// Slot pairs of c0 + c1 s whose loads a thread has in flight, three a slot.  At 2^14 one
+// pair: all at once read 48 rows side by side, whose strides are powers of two where the
+// limb count is, and with every CU at it 128 ciphertexts of 2 / 4 / 3 limbs took 37 /
+// 71 / 55 us instead of 30 / 58 / 51 (one ciphertext 19 either way).  Smaller limbs read
+// shorter rows, several workgroups to a CU: there all at once is as fast for many and
+// faster for one (the exchange of 16 x 256 at 2^12 66.6 against 67.3 us).
+template <int LOGN>
+constexpr int kDecryptFlight = LOGN == 14 ? 1 : 8;
+
 // c0 + c1 s -> canonical coefficient residues (uint64), block i = limb i
 template <int LOGN>
 NTT_KERNEL(LOGN) void k_decrypt_u64(const double* __restrict__ ct, const double* __restrict__ sk, int lv,
@@ -314,7 +323,7 @@ NTT_KERNEL(LOGN) void k_decrypt_u64(const double* __restrict__ ct, const double*
   const double* c1 = ct + (size_t)(lv + 1 + i) * N;
   const double* sk_i = sk + (size_t)i * N;
   uint64_t* dst = out + (size_t)i * N;
-  ntt_inv_in<LOGN>(s, [&](int t) { return c0[t] + mulmod(c1[t], sk_i[t], m); }, tb.inv_tw + (size_t)i * N,
+  ntt_inv_in<LOGN, kDecryptFlight<LOGN>>(s, [&](int t) { return c0[t] + mulmod(c1[t], sk_i[t], m); }, tb.inv_tw + (size_t)i * N,
                    m, tb.ninv[i], [&](int j, double v) { dst[j] = f64_to_u64(canon(v, m)); });
 }
 
@@ -332,7 +341,7 @@ NTT_KERNEL(LOGN) void k_decrypt_f64(const double* __restrict__ ct, const double*
   const double* c1 = base + (size_t)(lv + 1 + i) * N;
   const double* sk_i = sk + (size_t)i * N;
   double* dst = out + ((size_t)c * (lv + 1) + i) * N;
-  ntt_inv_in<LOGN>(s, [&](int t) { return c0[t] + mulmod(c1[t], sk_i[t], m); }, tb.inv_tw + (size_t)i * N,
+  ntt_inv_in<LOGN, kDecryptFlight<LOGN>>(s, [&](int t) { return c0[t] + mulmod(c1[t], sk_i[t], m); }, tb.inv_tw + (size_t)i * N,
                    m, tb.ninv[i], [&](int j, double v) { dst[j] = canon(v, m); });
 }
 

@@ -626,21 +626,35 @@ __device__ __forceinline__ void ntt_fwd_out(double* s, Load load, const double* 
 
 // Inverse transform of the orbit-order values in(t) (|x| < 2^51); c[w] gets
 // coefficient tid + w*T times N^-1, centred.  LDS may still be read by other
-// threads on return: barrier before writing `s` again.
-template <int LOGN, class In>
+// threads on return: barrier before writing `s` again.  FLIGHT: slot pairs t, t +
+// N/2 whose loads are in flight together (N <= 2^14).
+template <int LOGN, int FLIGHT = 8, class In>
 __device__ __forceinline__ void ntt_inv_in_regs(double* s, In in, const double* __restrict__ itw,
                                                 ModQ m, double ninv,
                                                 double (&c)[NttShape<LOGN>::PER]) {
   constexpr int N = 1 << LOGN, T = NttShape<LOGN>::T;
   if constexpr (LOGN <= 14) {
-    double v[16];  // all loads of the thread's slots in flight together
+    if constexpr (FLIGHT == 8) {
+      double v[16];
 #pragma unroll
-    for (int w = 0; w < 8; ++w) {
-      const int t = (int)opaque_tid() + w * T;
-      v[2 * w] = in(t);
-      v[2 * w + 1] = in(t + N / 2);
+      for (int w = 0; w < 8; ++w) {
+        const int t = (int)opaque_tid() + w * T;
+        v[2 * w] = in(t);
+        v[2 * w + 1] = in(t + N / 2);
+      }
+      slots_to_lds<LOGN>(s, v, m);
+    } else {
+      static_assert(FLIGHT == 1);
+      OrbitWalk ow = OrbitWalk::start<LOGN>();
+#pragma unroll 1
+      for (int w = 0; w < 8; ++w) {
+        const int t = (int)opaque_tid() + w * T, j = ow.brv_index<LOGN>();
+        const double a = in(t), b = in(t + N / 2);
+        s[lds_pad(j)] = reduce(a, m);
+        s[lds_pad(j ^ (N - 1))] = reduce(b, m);
+        ow.next<LOGN>();
+      }
     }
-    slots_to_lds<LOGN>(s, v, m);
     __syncthreads();
     ntt_inv_regs<LOGN>(s, c, itw, m, ninv);
   } else {
@@ -678,12 +692,12 @@ __device__ __forceinline__ void ntt_inv_in_regs(double* s, In in, const double* 
 }
 
 // inverse transform of in(t), handing coefficient j to store(j, v)
-template <int LOGN, class In, class Store>
+template <int LOGN, int FLIGHT = 8, class In, class Store>
 __device__ __forceinline__ void ntt_inv_in(double* s, In in, const double* __restrict__ itw,
                                            ModQ m, double ninv, Store store) {
   constexpr int T = NttShape<LOGN>::T, PER = NttShape<LOGN>::PER;
   double c[PER];
-  ntt_inv_in_regs<LOGN>(s, in, itw, m, ninv, c);
+  ntt_inv_in_regs<LOGN, FLIGHT>(s, in, itw, m, ninv, c);
 #pragma unroll
   for (int w = 0; w < PER; ++w) store((int)opaque_tid() + w * T, c[w]);
 }
