@@ -30,7 +30,7 @@ struct pvfl_batch {
   const pvfl_rotkeys* keys = nullptr;
   int count = 0, pg = 4, CH = 64, lv = 0, K = 0, beta = 0, max_rows = 0;
   int n_enc_work = 0, n_work = 0, n_slots = 0;
-  size_t lds_asked = 0;  // stage of `group` products at 256 * vec indices: the options' limit
+  size_t lds_asked = 0;  // stage of `group` products at 256 * vec indices: what the options are limited by
   double inv_scale = 1.0;
   // every device pointer below lies in the caller's workspace
   BatchProd* prods = nullptr;
@@ -468,6 +468,8 @@ static pvfl_status batch_product(pvfl_batch* b, void* stream) {
     // writes instead are an intermediate of this kernel's own design, not counted)
     const double bytes = b->key_bytes_min + b->pt_bytes + 8.0 * (double)b->count * ((size_t)b->beta * KN + 2 * Q) +
                          8.0 * (double)b->count * 2 * KN;
+    // the limit of a stage of `group` products at 256 * vec indices, kept so that options
+    // refused for it stay refused; the kernel's own (products_per_item) fits wherever it does
     if (b->lds_asked > kDiagMaxLds) return hip_fail(hipErrorInvalidValue, "batch options: group and chunk exceed the LDS");
     KernelTimer kt(c, stream, PVFL_TIMING_DIAG, bytes);
     HIP_TRY(launch_diag_batch(L, a, b->pg, b->beta));

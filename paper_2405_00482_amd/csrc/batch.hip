@@ -26,7 +26,7 @@ namespace pvfl {
 // is staged in LDS once and the shifted reads of the loop become LDS reads.
 // Partial sums per (product, chunk) go to part[prod.part0 + i0 / CH].
 //
-// What bounds it: per (product, diagonal, index) 49 binary64 operations, 40
+// What bounds it: per (product, diagonal, index) 47 binary64 operations, 40
 // bytes from LDS and, over PG products, 8 plaintext bytes plus 16 BETA / PG
 // key bytes through the vector cache, which takes one wave load per 16
 // cycles whatever its width.  Four products of one index share the key
@@ -315,7 +315,6 @@ __global__ __launch_bounds__(NttShape<LOGN>::T) void k_encode_ct_batch(const Enc
   encode_ct_body<LOGN>(args[blockIdx.x], 0, et, s2, msg + (size_t)blockIdx.x * (1 << LOGN));
 }
 
-// read-out of product p's decoded slots z[p][N/2] into its y (lazy RaS)
 // output row idx of a product from its decoded slots slot(j): the lazy
 // rotate-and-sum, added in slot order
 template <class Slot>
@@ -339,8 +338,8 @@ __global__ __launch_bounds__(256) void k_readout_batch(const double* __restrict_
 }
 
 // Decode and read-out in one workgroup per product (N <= 2^14): the slots
-// stay in LDS and each row's sum reads them there.  Same values and the same
-// order of additions as k_decode followed by k_readout_batch.
+// stay in LDS and each row's sum reads them there, in the order of additions of
+// k_readout_batch.
 template <int LOGN>
 __global__ __launch_bounds__(NttShape<LOGN>::T) void k_decode_readout_batch(const double* __restrict__ res, int lv,
                                                                             CrtTabs ct, EncTabs et, double inv_scale,

@@ -136,7 +136,10 @@ __global__ __launch_bounds__(1024) void k_diag_lazy(DiagArgs a) {
 // made once per kGiants giant steps instead of once per diagonal.  Diagonal by
 // diagonal, 512 diagonals with 32 baby steps at N = 2^14 took 376 us and
 // another 12 us for their partial sums; this takes 121 (plaintexts and keys
-// alone: 82 us at the read rate).
+// alone: 82 us at the read rate).  Whole products of 256 diagonals at 2^14, 4 + 1
+// primes, with kGiants 8, 4 and 2, us: 16 giant steps 240, 241, 282; 8 of them 187, 199,
+// 241; 4 of them 226, 208, 272; 2 of them 303, 276, 266 (sums past the last giant step are
+// made and dropped).  8 to 16 giant steps are the fastest splits of these diagonals.
 constexpr int kGiants = 8;
 template <int BETA>
 __global__ __launch_bounds__(512) void k_diag_bsgs(DiagArgs a, int bs, int g) {

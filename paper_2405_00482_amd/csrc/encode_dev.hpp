@@ -110,7 +110,7 @@ __device__ __forceinline__ void fft_passes(double2* a, const double2* __restrict
 // barrier.  Radix-8 register passes: ceil(log2(M) / 3) LDS round trips.
 template <int LOGN>
 __device__ __forceinline__ void fft_dif_lds(double2* a, const double2* __restrict__ tw, bool conj) {
-  static_assert(LOGN <= 14, "the 2^15 ring's FFT is split in halves (encode_to_regs, k_decode)");
+  static_assert(LOGN <= 14, "the 2^15 ring's FFT is split in halves (encode15, k_decode15)");
   fft_passes<LOGN, 0>(a, tw, conj);
 }
 
@@ -178,8 +178,13 @@ __device__ __forceinline__ double crt_lift(const double* __restrict__ base, int 
   return crt_lift<NL>(r, ct, nl_rt);
 }
 
-// f(std::integral_constant<int, NL>) for the limb count nl: the usual output
-// levels by number, 0 for the others
+// f(std::integral_constant<int, NL>) for the limb count nl: one to six and eight by
+// number, 0 (loops unrolled to kMaxLimbs under uniform conditions) for the others.
+// One / 512 ciphertexts, by number and through the general form, us: 3 limbs at 2^13
+// 27 and 66 / 114 and 185, 8 limbs at 2^15 179 and 238 / 1335 and 1409.  Each number is
+// one more copy of the loop, and the kernels' other copies pay for it: with seven of its
+// own (2^15: 160 instead of 214 / 1193 instead of 1262) the three-limb read-out of one
+// ciphertext at 2^13 takes 15.8 instead of 14.9.
 template <class F>
 __device__ __forceinline__ void with_limbs(int nl, F f) {
   switch (nl) {

@@ -281,7 +281,10 @@ static size_t ws_doubles(const pvfl_plan* p, int count = 1) {
     case PVFL_PLAN_HYBRID:
     case PVFL_PLAN_DIAG:
       if (p->opts.lazy_moddown) {
-        // every term (count of them) brings col_blocks input ciphertexts
+        // every term (count of them) brings col_blocks input ciphertexts.  The
+        // fused kernel writes `slices` of each input's nchunk partial sums; the
+        // others' room is part of the smallest workspace a caller knows, and
+        // holds the giant steps' rotations.
         const size_t CB = (size_t)count * p->info.col_blocks, g = p->giants;
         const size_t bsgs = p->info.bsgs ? g * 2 * Q + digits + 2 * Q + Q : 0;
         // + 4Q at the end: in-ciphertext RaS temporaries
@@ -326,7 +329,7 @@ static size_t bsgs_sums(const pvfl_plan* p, int count) {
 }
 static size_t ws_preferred(const pvfl_plan* p, int count) {
   const size_t need = std::max<size_t>(ws_doubles(p, count), 1);
-  // giant steps' rotations, where the room of the spent partial sums does not hold them all (bsgs_at_once)
+  // giant steps' rotations, where the room of the spent partial sums does not hold them all
   if (p->info.bsgs) {
     const size_t per = bsgs_per(p), n = std::min<size_t>((size_t)p->giants - 1, kRotBatchBytes / sizeof(double) / per);
     const size_t room = n * per + inner_room(p, n);
